@@ -180,7 +180,11 @@ int32_t prepare_step(const void *target_logits, const void *draft_logits, int32_
 // process ends.  Host code must never use the array's name as an address
 // (on the host it is a stand-in for the symbol); the device address of each
 // device's copy comes from hipGetSymbolAddress.
-__device__ __align__(256) static unsigned char scratch[DSDE_STATIC_SCRATCH_BYTES];
+// DSDE_STATIC_SCRATCH_BYTES bound the statistics pass's share of the workspace
+// (which grows with the shape without limit and decides what is refused); the
+// draw's share has a bound of its own and lies behind it.
+constexpr size_t kScratchBytes = size_t(DSDE_STATIC_SCRATCH_BYTES) + dsde::kMaxDrawBytes;
+__device__ __align__(256) static unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
@@ -255,7 +259,7 @@ int32_t dsde_step_static(const void *target_logits, const void *draft_logits, in
   if (st != DSDE_OK) return st;
   // every region of the workspace a call reads is written earlier in the same
   // call, so the array needs no clearing between calls
-  if (dsde::workspace_layout(B, N, V, k_max).total > size_t(DSDE_STATIC_SCRATCH_BYTES))
+  if (dsde::workspace_layout(B, N, V, k_max).stats_total > size_t(DSDE_STATIC_SCRATCH_BYTES))
     return DSDE_WORKSPACE_TOO_SMALL;
   void *ws = nullptr;
   const int32_t sa = scratch_address(a.stream, &ws);

@@ -57,18 +57,53 @@ struct Gathered {
   float zt, zd;
 };
 
-// Largest vocabulary: the per-sequence kernel keeps the draw-weight totals of
-// every chunk of a row in LDS.
-constexpr int kMaxChunks = 512;
-static_assert(int64_t(kMaxChunks) * kChunk == DSDE_MAX_VOCAB, "vocabulary limit of the ABI");
+static_assert(DSDE_MAX_VOCAB % kChunk == 0, "vocabulary limit of the ABI");
+
+// The draw reads rows in units of 2048 logits; a unit's reference and, for
+// greedy rows, its argmax (draw_device.hpp).
+constexpr int kUnit = 2048;
+struct UnitRef {
+  float ref;
+  int32_t idx;
+};
+inline int64_t num_units(int64_t V) { return (V + kUnit - 1) / kUnit; }
+
+// What the draw of one sequence needs, decided by the acceptance.
+struct DrawJob {
+  int32_t kind;          // 0: residual of the first rejected pair, 1: bonus row, 2: greedy, token known,
+                         // 3: greedy, argmax of the bonus row, -1: nothing (flagged)
+  int32_t accepted;      // a_b
+  int32_t target_row;
+  int32_t draft_row;     // -1 for the bonus row
+  float scale;           // c = log2(e) / T_b
+  float mt, md;          // row reference shifts of the rejected pair
+  float inv_sp, inv_sq;  // 1 / row sums of the rejected pair
+  float u;               // draw uniform
+  int32_t token;         // greedy: the emitted token when it is already known
+};
 
 inline size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 
-struct WorkspaceLayout {
-  size_t work, pair_chunk, gathered, chunk_arg, total;
-};
-
 inline int64_t num_chunks(int64_t V) { return (V + kChunk - 1) / kChunk; }
+
+// The draw's cells (24 bytes per unit) and jobs pass from one kernel to the
+// next through the workspace.  Their space is bounded: batches with more than
+// kMaxDrawCells units, or more than kMaxDrawSeqs sequences, run the two draw
+// kernels over several ranges of sequences one after another.
+constexpr int64_t kMaxDrawCells = 131072;
+constexpr int32_t kMaxDrawSeqs = 32768;
+inline int32_t draw_seqs_per_pass(int32_t B, int64_t V) {
+  int64_t n = kMaxDrawCells / num_units(V);
+  if (n < 1) n = 1;
+  if (n > kMaxDrawSeqs) n = kMaxDrawSeqs;
+  return int32_t(n < B ? n : B);
+}
+static_assert(kMaxDrawCells >= DSDE_MAX_VOCAB / kUnit, "a pass holds at least one sequence");
+
+struct WorkspaceLayout {
+  size_t work, pair_chunk, gathered, chunk_arg, stats_total;  // the statistics pass
+  size_t jobs, sub, ref, total;                               // the draw
+};
 
 inline WorkspaceLayout workspace_layout(int32_t B, int64_t N, int64_t V, int32_t k_max) {
   const int64_t nc = num_chunks(V);
@@ -84,9 +119,19 @@ inline WorkspaceLayout workspace_layout(int32_t B, int64_t N, int64_t V, int32_t
   off += align_up(sizeof(Gathered) * slots);
   L.chunk_arg = off;
   off += align_up(sizeof(ChunkArg) * slots * size_t(nc));
+  L.stats_total = off;
+  const size_t seqs = size_t(draw_seqs_per_pass(B, V)), cells = seqs * size_t(num_units(V));
+  L.jobs = off;
+  off += align_up(sizeof(DrawJob) * seqs);
+  L.sub = off;
+  off += align_up(4 * sizeof(float) * cells);
+  L.ref = off;
+  off += align_up(sizeof(UnitRef) * cells);
   L.total = off;
   return L;
 }
+// Upper bound of L.total - L.stats_total for any shape.
+constexpr size_t kMaxDrawBytes = sizeof(DrawJob) * kMaxDrawSeqs + 24 * size_t(kMaxDrawCells) + 3 * 256;
 
 // Arguments of the signal update and the SL rule when they run fused behind
 // the verification (dsde_step).
@@ -129,11 +174,29 @@ struct VerifyArgs {
 };
 
 int launch_verify(const VerifyArgs &a);
-// The set-up and statistics kernels of one verification step (stats.hip).
-// With `entropy` false the bf16 statistics kernel leaves the draft entropy
-// accumulator (PairChunk::h) at zero.
-void launch_stats_pass(const VerifyArgs &a, WorkItem *work, PairChunk *part, Gathered *gath, ChunkArg *chunk_arg,
-                       bool entropy);
+// Whether the statistics pass of a call runs without the set-up kernel; the
+// kernel behind the pass then validates the layout (layout_fault) and
+// writes seq_err (stats.hip).
+bool stats_lookup(const VerifyArgs &a);
+// The set-up (unless `lookup`) and statistics kernels of one verification step
+// (stats.hip).  With `entropy` false the bf16 statistics kernel leaves the
+// draft entropy accumulator (PairChunk::h) at zero.
+void launch_stats_pass(const VerifyArgs &a, bool lookup, WorkItem *work, PairChunk *part, Gathered *gath,
+                       ChunkArg *chunk_arg, bool entropy);
+
+// The set-up kernel's layout check, dealt to the threads of one workgroup: 1 in
+// a thread that saw an SL outside [0, k_max] or a cu_sl that is not the prefix
+// sums of sl with cu_sl[B] = N.  The callers OR it over the workgroup.
+__device__ __forceinline__ int layout_fault(int32_t B, int64_t N, int32_t k_max, const int32_t *__restrict__ sl,
+                                            const int32_t *__restrict__ cu_sl) {
+  int bad = cu_sl[0] != 0 || int64_t(cu_sl[B]) != N;
+  for (int32_t q = threadIdx.x; q < B; q += blockDim.x) {
+    const int64_t s = sl[q];
+    if (s < 0 || s > k_max || int64_t(cu_sl[q + 1]) - int64_t(cu_sl[q]) != s) bad = 1;
+  }
+  return bad;
+}
+
 // Rows are 16-byte aligned and V a multiple of the vector width.
 bool rows_vectorizable(const VerifyArgs &a);
 int launch_kld_signal(int32_t B, int64_t N, const int32_t *sl, const int32_t *cu_sl, const float *kld,

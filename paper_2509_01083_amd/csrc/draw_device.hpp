@@ -1,8 +1,8 @@
-// Device routines of the draw shared by the per-sequence kernel and the
+// Device routines of the draw shared by the per-sequence kernels and the
 // vocabulary-shard kernels: the draw job, fp64 helpers of the latency-bound
-// steps, the combine of chunk partials, and the per-chunk passes of the draw
-// (residual max(0, p - q), p, bonus exponentials, bonus argmax) with their
-// sub-block totals.
+// steps, the combine of chunk partials, the draw-weight passes over units of
+// 2048 logits (residual max(0, p - q), p, bonus exponentials, bonus argmax),
+// and the inverse-CDF search over what those passes left behind.
 #pragma once
 
 #include <math.h>
@@ -14,29 +14,8 @@
 namespace dsde {
 namespace {
 
-constexpr int kVirt = kThreads / 64;          // chunk-layout threads played by one lane (4)
-
-// How many of a lane's chunk-layout threads one loop iteration handles: as
-// many as the registers allow loads in flight for.
-template <int DT, bool VEC>
-constexpr int kVirtUnroll = !VEC ? 1 : DT == DSDE_BF16 ? kVirt : 2;
-
-// What the draw of one sequence needs, decided by the acceptance.
-struct DrawJob {
-  int32_t kind;          // 0: residual of the first rejected pair, 1: bonus row, 2: greedy, token known,
-                         // 3: greedy, argmax of the bonus row, -1: nothing (flagged)
-  int32_t accepted;      // a_b
-  int32_t target_row;
-  int32_t draft_row;     // -1 for the bonus row
-  float scale;           // c = log2(e) / T_b
-  float mt, md;          // row reference shifts of the rejected pair
-  float inv_sp, inv_sq;  // 1 / row sums of the rejected pair
-  float u;               // draw uniform
-  int32_t token;         // greedy: the emitted token when it is already known
-};
-
-// The draw job as read from LDS, moved to scalar registers (it is the same in
-// every lane), which frees vector registers for the draw stream's loads.
+// The draw job as read from memory, moved to scalar registers (it is the same
+// in every lane), which frees vector registers for the draw stream's loads.
 __device__ __forceinline__ float uniform_f(float v) {
   return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
@@ -208,45 +187,103 @@ __device__ inline void combine_pairs(const PairChunk *__restrict__ part, int64_t
   }
 }
 
-// Raw bf16 chunk loads of the draw stream: the loads of issue_raw_bf16 and
-// the padding of pad_raw_bf16, with 32-bit word indices off a uniform row
-// base (word i0 + 256 q of the row, clamped to the last word), so that each
-// load takes one offset register and no 64-bit address arithmetic.
-__device__ __forceinline__ RawBf16 issue_row_bf16(const char *row, uint32_t i0, uint32_t last) {
-  const uint4 *p = (const uint4 *)row;
-  RawBf16 r;
-  r.v0 = stream_load(p + min(i0, last));
-  r.v1 = stream_load(p + min(i0 + 256u, last));
-  r.v2 = stream_load(p + min(i0 + 512u, last));
-  r.v3 = stream_load(p + min(i0 + 768u, last));
-  return r;
-}
-__device__ __forceinline__ RawBf16 pad_row_bf16(const RawBf16 &a, uint32_t i0, uint32_t last) {
-  const uint4 pad = make_uint4(kPadBf16x2, kPadBf16x2, kPadBf16x2, kPadBf16x2);
-  RawBf16 r;
-  r.v0 = i0 <= last ? a.v0 : pad;
-  r.v1 = i0 + 256u <= last ? a.v1 : pad;
-  r.v2 = i0 + 512u <= last ? a.v2 : pad;
-  r.v3 = i0 + 768u <= last ? a.v3 : pad;
-  return r;
+// ---------------------------------------------------------------------------
+// draw weights, one unit at a time
+// ---------------------------------------------------------------------------
+//
+// The draw reads a row in units of kUnit = 2048 consecutive logits, one unit
+// per wavefront and step, 32 logits per lane, and keeps for every unit the
+// weight totals of its four sub-blocks of 512 logits.  A wavefront needs
+// nothing from its neighbours to finish a unit (the chunk totals of a wider
+// layout need a barrier or four times the logits per wavefront), so the units
+// of one row can be dealt to any number of workgroups.  Lane l owns slots
+// i = 0..31 of its unit:
+//   bf16, 16-byte rows : logit 2048 u + 512 (i / 8) + 8 l + i % 8   (4 x uint4)
+//   fp32, 16-byte rows : logit 2048 u + 256 (i / 4) + 4 l + i % 4   (8 x float4)
+//   any other row      : as bf16, 32 scalar loads
+// Every wavefront load is contiguous, and slots 8 g .. 8 g + 7 lie in
+// sub-block g in every layout.
+constexpr int kUnitElts = kUnit / 64;
+constexpr int kSubs = 4;
+constexpr int kSubLen = kUnit / kSubs;
+
+template <int DT, bool VEC>
+__device__ __forceinline__ int64_t unit_token(int64_t unit, int i, int lane) {
+  if constexpr (VEC && DT == DSDE_FP32) return unit * kUnit + (i / 4) * 256 + 4 * lane + (i % 4);
+  return unit * kUnit + (i / 8) * 512 + 8 * lane + (i % 8);
 }
 
-// Sub-blocks: each chunk splits into 16 runs of 512 consecutive logits, and
-// the draw keeps the weight total of every run, so that after the chunk
-// search only one run (one 16-byte load per lane and row for bf16) has to be
-// read again and scanned.  Slot i of chunk-layout thread lane + 64 k lies in
-// sub-block sub_of(i, k) (from the layouts: bf16 16-byte rows put slot group
-// i / 8 of thread t at 2048 (i / 8) + 8 t, fp32 16-byte rows group i / 4 at
-// 1024 (i / 4) + 4 t, other rows slot i at 256 i + t).
-constexpr int kSubs = 16;
-constexpr int kSubLen = kChunk / kSubs;  // 512
+// One row's logits of a unit.  issue() loads them (indices clamped into the
+// row, so no load branches), pad() replaces what lies past V; callers that
+// read two rows issue both before they pad either.
 template <int DT, bool VEC>
-__device__ constexpr int sub_of(int i, int k) {
-  return VEC ? (DT == DSDE_BF16 ? 4 * (i / 8) + k : 2 * (i / 4) + (k >> 1)) : (i >> 1);
-}
+struct UnitRow {
+  float z[kUnitElts];
+  __device__ __forceinline__ void issue(const char *row, int64_t V, int64_t unit, int lane) {
+#pragma unroll
+    for (int i = 0; i < kUnitElts; ++i) {
+      const int64_t v = unit_token<DT, VEC>(unit, i, lane);
+      z[i] = load_logit(row, DT, v < V ? v : V - 1);
+    }
+  }
+  __device__ __forceinline__ void pad(int64_t V, int64_t unit, int lane) {
+#pragma unroll
+    for (int i = 0; i < kUnitElts; ++i)
+      if (unit_token<DT, VEC>(unit, i, lane) >= V) z[i] = kPadF32;
+  }
+  __device__ __forceinline__ float at(int i) const { return z[i]; }
+};
+template <>
+struct UnitRow<DSDE_BF16, true> {
+  u32x4_t v[4];
+  __device__ __forceinline__ void issue(const char *row, int64_t V, int64_t unit, int lane) {
+    const u32x4_t *p = (const u32x4_t *)row;
+    const uint32_t last = uint32_t(V / 8 - 1), i0 = uint32_t(unit) * 256u + uint32_t(lane);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) v[g] = __builtin_nontemporal_load(p + min(i0 + 64u * g, last));
+  }
+  __device__ __forceinline__ void pad(int64_t V, int64_t unit, int lane) {
+    const uint32_t last = uint32_t(V / 8 - 1), i0 = uint32_t(unit) * 256u + uint32_t(lane);
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      if (i0 + 64u * g > last) v[g] = u32x4_t{kPadBf16x2, kPadBf16x2, kPadBf16x2, kPadBf16x2};
+  }
+  __device__ __forceinline__ float at(int i) const {
+    const uint32_t x = v[i >> 3][(i >> 1) & 3];
+    return (i & 1) ? bf_hi(x) : bf_lo(x);
+  }
+};
+template <>
+struct UnitRow<DSDE_FP32, true> {
+  f32x4_t v[8];
+  __device__ __forceinline__ void issue(const char *row, int64_t V, int64_t unit, int lane) {
+    const f32x4_t *p = (const f32x4_t *)row;
+    const uint32_t last = uint32_t(V / 4 - 1), i0 = uint32_t(unit) * 512u + uint32_t(lane);
+#pragma unroll
+    for (int g = 0; g < 8; ++g) v[g] = __builtin_nontemporal_load(p + min(i0 + 64u * g, last));
+  }
+  __device__ __forceinline__ void pad(int64_t V, int64_t unit, int lane) {
+    const uint32_t last = uint32_t(V / 4 - 1), i0 = uint32_t(unit) * 512u + uint32_t(lane);
+#pragma unroll
+    for (int g = 0; g < 8; ++g)
+      if (i0 + 64u * g > last) v[g] = f32x4_t{kPadF32, kPadF32, kPadF32, kPadF32};
+  }
+  __device__ __forceinline__ float at(int i) const { return v[i >> 2][i & 3]; }
+};
+
+// What a unit's pass leaves behind, in two arrays per sequence: sub[4 u + g],
+// the weight total of sub-block g, and ref[u].  Bonus rows: ref is the
+// reference their exponentials are taken against, max(z) c of the unit, or,
+// for a greedy row, its largest raw logit, with idx the smallest (row-local)
+// token holding it; a NaN ref marks a NaN or infinite logit in the unit.
+// Residual and p totals need no reference and leave ref unwritten.
+struct UnitCells {
+  float *sub;
+  UnitRef *ref;
+};
 
 // The draw weights, each evaluated by one routine wherever it is needed (the
-// chunk totals and the final scan), with no contraction of the product into
+// unit totals and the final scan), with no contraction of the product into
 // a neighbouring sum, so that both places see the same bits.
 __device__ __forceinline__ float residual_weight(float zt, float zd, const DrawJob &job) {
 #pragma clang fp contract(off)
@@ -262,294 +299,236 @@ __device__ __forceinline__ float bonus_weight(float z, float scale, float ref) {
   return fast_exp2(fmaf(z, scale, -ref));
 }
 
-// Per-lane sub-block sums -> the chunk's 64 row partials in LDS (sub-block j
-// total = out[j] + out[16 + j] + out[32 + j] + out[48 + j]) and the chunk
-// total.
-__device__ __forceinline__ double finish_chunk(const float (&a)[kSubs], float *out) {
-  const float r = lanes::row_transpose_sum16(a);
-  out[threadIdx.x & 63] = r;
-  return double(lanes::wave_sum(r));
-}
-
-// Chunk of one or two rows as 32 floats per chunk-layout thread, for the
-// generic layouts, calling f(i, k, zt, zd) per slot.  fp32 16-byte rows
-// handle two chunk-layout threads per iteration (register pressure); the
-// sub-block of a slot then depends on the iteration, so the sums of one
-// iteration go to kSubs / 2 partials first.
-template <int DT, bool VEC, bool TWO, typename F>
-__device__ __forceinline__ void generic_chunk_sums(const char *trow, const char *drow, int64_t V, int64_t ch,
-                                                   float (&a)[kSubs], F f) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int j = 0; j < kSubs; ++j) a[j] = 0.f;
-  if constexpr (VEC && DT == DSDE_FP32) {
-    for (int kk = 0; kk < 2; ++kk) {
-      float b[kSubs / 2];
-#pragma unroll
-      for (int g = 0; g < kSubs / 2; ++g) b[g] = 0.f;
-#pragma unroll
-      for (int k2 = 0; k2 < 2; ++k2) {
-        float zt[kEltsPerThread], zd[kEltsPerThread];
-        load_chunk_f32<DT, VEC>(trow, V, ch, lane + 64 * (2 * kk + k2), zt);
-        if constexpr (TWO) load_chunk_f32<DT, VEC>(drow, V, ch, lane + 64 * (2 * kk + k2), zd);
-#pragma unroll
-        for (int i = 0; i < kEltsPerThread; ++i) b[i / 4] += f(zt[i], TWO ? zd[i] : 0.f);
-      }
-#pragma unroll
-      for (int g = 0; g < kSubs / 2; ++g) {  // sub-block 2 g + kk
-        a[2 * g] = kk == 0 ? b[g] : a[2 * g];
-        a[2 * g + 1] = kk == 1 ? b[g] : a[2 * g + 1];
-      }
-    }
-  } else {
-#pragma unroll kVirtUnroll<DT, VEC>
-    for (int k = 0; k < kVirt; ++k) {
-      float zt[kEltsPerThread], zd[kEltsPerThread];
-      load_chunk_f32<DT, VEC>(trow, V, ch, lane + 64 * k, zt);
-      if constexpr (TWO) load_chunk_f32<DT, VEC>(drow, V, ch, lane + 64 * k, zd);
-#pragma unroll
-      for (int i = 0; i < kEltsPerThread; ++i) a[sub_of<DT, VEC>(i, k)] += f(zt[i], TWO ? zd[i] : 0.f);
-    }
-  }
-}
-
-// Total of the residual weights max(0, p - q) over one chunk of the rejected
-// pair, by one wavefront (lane l plays the chunk-layout threads l + 64 k), and
-// its sub-block partials.
-template <int DT, bool VEC>
-__device__ inline double residual_chunk(const char *trow, const char *drow, int64_t V, int64_t ch,
-                                        const DrawJob &job, float *sub) {
-  const int lane = threadIdx.x & 63;
+// Sums a lane's 32 weights f(i) into its four sub-block sums, and those over
+// the wavefront: lane l receives the total of sub-block l % 4.
+template <typename F>
+__device__ __forceinline__ float unit_totals(F f) {
   float a[kSubs];
-  if constexpr (DT == DSDE_BF16 && VEC) {
-    // every load of the chunk (both rows, all four chunk-layout threads: 32 KiB
-    // per wavefront) is issued before any value is used; each chunk-layout
-    // thread's four sub-block sums then go into one wave sum as well, which
-    // keeps the compiler's order of use equal to the order of issue (loads
-    // return in that order) and gives the chunk total
-    RawBf16 rt[kVirt], rd[kVirt];
 #pragma unroll
-    for (int k = 0; k < kVirt; ++k) {
-      rt[k] = issue_raw_bf16(trow, V, ch, lane + 64 * k);
-      rd[k] = issue_raw_bf16(drow, V, ch, lane + 64 * k);
-    }
-    float sw[kVirt];
+  for (int g = 0; g < kSubs; ++g) {
+    float s = 0.f;
 #pragma unroll
-    for (int k = 0; k < kVirt; ++k) {
-      const RawBf16 t_ = pad_raw_bf16(rt[k], V, ch, lane + 64 * k), d_ = pad_raw_bf16(rd[k], V, ch, lane + 64 * k);
-      float tk = 0.f;
-#pragma unroll
-      for (int g = 0; g < kEltsPerThread / 8; ++g) {
-        float s = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s += residual_weight(pick_bf16(t_, 8 * g + e), pick_bf16(d_, 8 * g + e), job);
-        a[sub_of<DT, VEC>(8 * g, k)] = s;
-        tk += s;
-      }
-      sw[k] = wave_sum(tk);
-    }
-    sub[lane] = lanes::row_transpose_sum16(a);
-    double w = 0.0;
-#pragma unroll
-    for (int k = 0; k < kVirt; ++k) w += double(sw[k]);
-    return w;
-  } else {
-    generic_chunk_sums<DT, VEC, true>(trow, drow, V, ch, a,
-                                      [&](float zt, float zd) { return residual_weight(zt, zd, job); });
+    for (int e = 0; e < 8; ++e) s += f(8 * g + e);
+    a[g] = s;
   }
-  return finish_chunk(a, sub);
+  return lanes::wave_sum4(a);
 }
-
-// Total of p over one chunk of the rejected pair's target row (the draw's
-// fallback when the residual has no mass), and its sub-block partials.
-template <int DT, bool VEC>
-__device__ inline double target_p_chunk(const char *trow, int64_t V, int64_t ch, const DrawJob &job, float *sub) {
-  float a[kSubs];
-  generic_chunk_sums<DT, VEC, false>(trow, nullptr, V, ch, a,
-                                     [&](float zt, float) { return target_p_weight(zt, job); });
-  return finish_chunk(a, sub);
-}
-
-// Bonus row, one chunk, by one wavefront: the chunk reference ref = max(z) c,
-// the total of 2^(z c - ref) and its sub-block partials, and whether a NaN or
-// +-inf logit was seen (+inf shows in the max, NaN in the sum, -inf in the
-// min; padding is finite).
-template <int DT, bool VEC>
-__device__ inline void bonus_chunk(const char *trow, int64_t V, int64_t ch, float scale, double *w_out,
-                                   float *ref_out, int *bad_out, float *sub) {
+__device__ __forceinline__ void store_totals(float total, float *sub, int32_t unit) {
   const int lane = threadIdx.x & 63;
+  if (lane < kSubs) sub[int64_t(unit) * kSubs + lane] = total;
+}
+
+// Residual weights max(0, p - q) of one unit of the rejected pair.
+template <int DT, bool VEC>
+__device__ __forceinline__ void residual_unit(const char *trow, const char *drow, int64_t V, int32_t unit,
+                                              const DrawJob &job, const UnitCells &c) {
+  const int lane = threadIdx.x & 63;
+  UnitRow<DT, VEC> t, d;
+  t.issue(trow, V, unit, lane);
+  d.issue(drow, V, unit, lane);
+  t.pad(V, unit, lane);
+  d.pad(V, unit, lane);
+  store_totals(unit_totals([&](int i) { return residual_weight(t.at(i), d.at(i), job); }), c.sub, unit);
+}
+
+// p of one unit of the rejected pair's target row (the draw's fallback when
+// the residual has no mass).
+template <int DT, bool VEC>
+__device__ __forceinline__ void target_p_unit(const char *trow, int64_t V, int32_t unit, const DrawJob &job,
+                                              const UnitCells &c) {
+  const int lane = threadIdx.x & 63;
+  UnitRow<DT, VEC> t;
+  t.issue(trow, V, unit, lane);
+  t.pad(V, unit, lane);
+  store_totals(unit_totals([&](int i) { return target_p_weight(t.at(i), job); }), c.sub, unit);
+}
+
+// Bonus row, one unit: the exponentials 2^(z c - ref) against the unit's own
+// reference.  +inf shows in the maximum, -inf in the minimum, NaN in the
+// totals; padding is finite.
+template <int DT, bool VEC>
+__device__ __forceinline__ void bonus_unit(const char *trow, int64_t V, int32_t unit, float scale,
+                                           const UnitCells &c) {
+  const int lane = threadIdx.x & 63;
+  UnitRow<DT, VEC> t;
+  t.issue(trow, V, unit, lane);
+  t.pad(V, unit, lane);
   float m = -INFINITY, lo = INFINITY;
-  float a[kSubs];
-  if constexpr (VEC && DT == DSDE_BF16) {
-    // one load: the raw chunk stays in registers for both passes
-    const uint32_t last = uint32_t(V / 8 - 1), i0 = uint32_t(ch) * 1024u + uint32_t(lane);
-    RawBf16 r[kVirt];
 #pragma unroll
-    for (int k = 0; k < kVirt; ++k) r[k] = issue_row_bf16(trow, i0 + 64u * k, last);
-#pragma unroll
-    for (int k = 0; k < kVirt; ++k) r[k] = pad_row_bf16(r[k], i0 + 64u * k, last);
-#pragma unroll
-    for (int k = 0; k < kVirt; ++k)
-#pragma unroll
-      for (int i = 0; i < kEltsPerThread; ++i) {
-        const float z = pick_bf16(r[k], i);
-        m = fmaxf(m, z);
-        lo = fminf(lo, z);
-      }
-    const float ref = wave_max(m) * scale;
-#pragma unroll
-    for (int k = 0; k < kVirt; ++k)
-#pragma unroll
-      for (int g = 0; g < kEltsPerThread / 8; ++g) {
-        float s = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s += bonus_weight(pick_bf16(r[k], 8 * g + e), scale, ref);
-        a[sub_of<DT, VEC>(8 * g, k)] = s;
-      }
-    *ref_out = ref;
-  } else {
-    // first pass: max and min; second pass over the same logits (now in
-    // cache): the exponentials against the chunk reference
-#pragma unroll kVirtUnroll<DT, VEC>
-    for (int k = 0; k < kVirt; ++k) {
-      float z[kEltsPerThread];
-      load_chunk_f32<DT, VEC>(trow, V, ch, lane + 64 * k, z);
-#pragma unroll
-      for (int i = 0; i < kEltsPerThread; ++i) {
-        m = fmaxf(m, z[i]);
-        lo = fminf(lo, z[i]);
-      }
-    }
-    const float ref = wave_max(m) * scale;
-    generic_chunk_sums<DT, VEC, false>(trow, nullptr, V, ch, a,
-                                       [&](float z, float) { return bonus_weight(z, scale, ref); });
-    *ref_out = ref;
+  for (int i = 0; i < kUnitElts; ++i) {
+    const float z = t.at(i);
+    m = fmaxf(m, z);
+    lo = fminf(lo, z);
   }
-  const double w = finish_chunk(a, sub);
-  const int bad = __ballot(m == INFINITY || lo == -INFINITY) != 0;
-  *w_out = w;
-  *bad_out = bad || !isfinite(w) || !isfinite(*ref_out);
+  const float ref = lanes::wave_max(m) * scale;
+  const float w = unit_totals([&](int i) { return bonus_weight(t.at(i), scale, ref); });
+  const bool bad = __ballot(m == INFINITY || lo == -INFINITY || !isfinite(w)) != 0 || !isfinite(ref);
+  store_totals(w, c.sub, unit);
+  if (lane == 0) c.ref[unit] = UnitRef{bad ? NAN : ref, 0};
 }
 
-
-// Greedy bonus row, one chunk, by one wavefront: the largest raw logit, the
-// smallest token id holding it, and whether a NaN or +-inf logit was seen.
+// Greedy bonus row, one unit: the largest raw logit and the smallest token
+// holding it.  A NaN shows in the sum (|z| <= 2^64 keeps finite sums finite).
 template <int DT, bool VEC>
-__device__ inline void bonus_argmax_chunk(const char *trow, int64_t V, int64_t ch, float *zmax_out, int32_t *idx_out,
-                                          int *bad_out) {
+__device__ __forceinline__ void bonus_argmax_unit(const char *trow, int64_t V, int32_t unit, const UnitCells &c) {
   const int lane = threadIdx.x & 63;
-  if constexpr (VEC && DT == DSDE_BF16) {
-    // pass 1 over the raw chunk in registers: max, min, and a sum that a NaN
-    // propagates through (|z| <= 2^64 keeps finite sums finite); pass 2: the
-    // lanes holding the maximum find its first token (slots of one
-    // chunk-layout thread ascend in token order)
-    RawBf16 r[kVirt];
+  UnitRow<DT, VEC> t;
+  t.issue(trow, V, unit, lane);
+  t.pad(V, unit, lane);
+  float m = -INFINITY, lo = INFINITY, sum = 0.f;
 #pragma unroll
-    for (int k = 0; k < kVirt; ++k) r[k] = load_raw_bf16(trow, V, ch, lane + 64 * k);
-    float m = -INFINITY, lo = INFINITY, sum = 0.f;
+  for (int i = 0; i < kUnitElts; ++i) {
+    const float z = t.at(i);
+    m = fmaxf(m, z);
+    lo = fminf(lo, z);
+    sum += z;
+  }
+  const float M = lanes::wave_max(m);
+  uint32_t best = 0xffffffffu;
+  if (m == M) {  // a lane's slots ascend in token order: its first equal slot is its smallest token
 #pragma unroll
-    for (int k = 0; k < kVirt; ++k)
-#pragma unroll
-      for (int i = 0; i < kEltsPerThread; ++i) {
-        const float z = pick_bf16(r[k], i);
-        m = fmaxf(m, z);
-        lo = fminf(lo, z);
-        sum += z;
-      }
-    const float M = wave_max(m);
-    uint32_t best = 0xffffffffu;
-    if (m == M) {
-#pragma unroll
-      for (int k = 0; k < kVirt; ++k)
-#pragma unroll
-        for (int i = kEltsPerThread - 1; i >= 0; --i)
-          if (pick_bf16(r[k], i) == M) {
-            const uint32_t idx = uint32_t(Layout<DT, VEC>::index(ch, i, lane + 64 * k));
-            best = idx < best ? idx : best;
-          }
-    }
-    best = lanes::wave_min(best);
-    *zmax_out = M;
-    *idx_out = int32_t(best);
-    *bad_out = __ballot(m == INFINITY || lo == -INFINITY || sum != sum) != 0;
-  } else {
-    float m = -INFINITY;
-    uint32_t best = 0xffffffffu;
-    int bad = 0;
-#pragma unroll kVirtUnroll<DT, VEC>
-    for (int k = 0; k < kVirt; ++k) {
-      float z[kEltsPerThread];
-      load_chunk_f32<DT, VEC>(trow, V, ch, lane + 64 * k, z);
-#pragma unroll
-      for (int i = 0; i < kEltsPerThread; ++i) {
-        const float v = z[i];  // padding is finite and below every admissible logit
-        if (!isfinite(v)) bad = 1;
-        const uint32_t idx = uint32_t(Layout<DT, VEC>::index(ch, i, lane + 64 * k));
-        if (v > m || (v == m && idx < best)) {
-          m = v;
-          best = idx;
-        }
-      }
-    }
-    const float M = wave_max(m);
-    uint32_t cand = m == M ? best : 0xffffffffu;
-    cand = lanes::wave_min(cand);
-    *zmax_out = M;
-    *idx_out = int32_t(cand);
-    *bad_out = __ballot(bad) != 0;
+    for (int i = kUnitElts - 1; i >= 0; --i)
+      if (t.at(i) == M) best = uint32_t(unit_token<DT, VEC>(unit, i, lane));
+  }
+  best = lanes::wave_min(best);
+  const bool bad = __ballot(m == INFINITY || lo == -INFINITY || sum != sum) != 0;
+  if (lane == 0) c.ref[unit] = UnitRef{bad ? NAN : M, int32_t(best)};
+}
+
+// Every unit of a row that this wavefront takes: units first, first + step, ...
+template <int DT, bool VEC>
+__device__ __forceinline__ void draw_units(const DrawJob &job, const char *target, const char *draft, int64_t V,
+                                           int32_t nu, int32_t first, int32_t step, const UnitCells &c) {
+  const size_t esz = DT == DSDE_BF16 ? 2 : 4;
+  const char *trow = target + size_t(job.target_row) * size_t(V) * esz;
+  if (job.kind == 0) {
+    const char *drow = draft + size_t(job.draft_row) * size_t(V) * esz;
+    for (int32_t u = first; u < nu; u += step) residual_unit<DT, VEC>(trow, drow, V, u, job, c);
+  } else if (job.kind == 1) {
+    for (int32_t u = first; u < nu; u += step) bonus_unit<DT, VEC>(trow, V, u, job.scale, c);
+  } else if (job.kind == 3) {
+    for (int32_t u = first; u < nu; u += step) bonus_argmax_unit<DT, VEC>(trow, V, u, c);
   }
 }
 
+// ---------------------------------------------------------------------------
+// the search
+// ---------------------------------------------------------------------------
 
-// The inverse-CDF draw inside one row, by one wavefront, from the totals a
-// chunk pass left behind: weight(ch) is chunk ch's draw weight (fp64, in the
-// row's scale), subs holds 64 row partials of the 16 sub-block totals per
-// chunk (chunk-major), and target is the weight to pass, in [0, row total).
-// The rule at every level (chunk, sub-block, element) is the draw's: the last
-// position with positive weight whose exclusive prefix is <= the target.
-// Bonus rows (mode 2) carry a reference per chunk, chunk_ref(ch), and the row
-// scale row_ref.  Returns the row-local token id in every lane.
-template <int DT, bool VEC, typename WF, typename RF>
-__device__ inline int32_t draw_in_row(int32_t nc, WF weight, RF chunk_ref, float row_ref, double target,
-                                      const float *subs, const char *trow, const char *drow, int64_t V, int mode,
-                                      const DrawJob &job) {
+// A unit's cell as one lane holds it.  The first 64 units of a row are kept in
+// registers by the callers (lane u: unit u), which covers vocabularies up to
+// 131,072; later units are read again where they are needed.
+struct UnitCell {
+  float4 s;
+  UnitRef r;
+};
+__device__ __forceinline__ UnitCell load_cell(const UnitCells &c, int32_t unit, int32_t nu, bool with_ref) {
+  UnitCell x;
+  x.s = make_float4(0.f, 0.f, 0.f, 0.f);
+  x.r = UnitRef{0.f, 0};
+  if (unit < nu) {
+    x.s = *reinterpret_cast<const float4 *>(c.sub + int64_t(unit) * kSubs);
+    if (with_ref) x.r = c.ref[unit];
+  }
+  return x;
+}
+__device__ __forceinline__ double cell_sum(const UnitCell &x) {
+  return (double(x.s.x) + double(x.s.y)) + (double(x.s.z) + double(x.s.w));
+}
+// The unit's weight in the row's scale (mode 2: the bonus exponentials, whose
+// units carry a reference each; modes 0 and 1 share one scale).
+__device__ __forceinline__ double cell_weight(const UnitCell &x, int mode, float row_ref) {
+  const double w = cell_sum(x);
+  return mode == 2 ? w * exp2_taylor(double(x.r.ref) - double(row_ref)) : w;
+}
+
+// Row total of the weights, in every lane, by one wavefront in a fixed order.
+__device__ __forceinline__ double row_total(const UnitCells &c, int32_t nu, const UnitCell &cell0, int mode,
+                                            float row_ref) {
   const int lane = threadIdx.x & 63;
-  int32_t best = -1;
-  double best_excl = 0.0, base = 0.0;
-  for (int32_t c0 = 0; c0 < nc; c0 += 64) {
-    const int32_t ch = c0 + lane;
-    const double w = ch < nc ? weight(ch) : 0.0;
+  double part = lane < nu ? cell_weight(cell0, mode, row_ref) : 0.0;
+  for (int32_t u = lane + 64; u < nu; u += 64) part += cell_weight(load_cell(c, u, nu, mode == 2), mode, row_ref);
+  return lanes::wave_sum(part);
+}
+
+// Largest reference of a bonus row's units (sampled rows: the row's scale;
+// greedy rows: the row maximum), and whether a unit is marked bad.
+__device__ __forceinline__ float row_reference(const UnitCells &c, int32_t nu, const UnitCell &cell0, bool *bad) {
+  const int lane = threadIdx.x & 63;
+  float m = -INFINITY;
+  bool b = false;
+  for (int32_t u = lane; u < nu; u += 64) {
+    const float r = u < 64 ? cell0.r.ref : c.ref[u].ref;
+    b |= r != r;
+    m = fmaxf(m, r);
+  }
+  *bad = __ballot(b) != 0;
+  return lanes::wave_max(m);
+}
+
+// The smallest token of a greedy bonus row's maximum M: the first unit that
+// reaches it.
+__device__ __forceinline__ int32_t row_argmax(const UnitCells &c, int32_t nu, const UnitCell &cell0, float M) {
+  const int lane = threadIdx.x & 63;
+  int32_t best = 0x7fffffff;  // token ids ascend with the unit: the smallest id belongs to the first unit
+  for (int32_t u = lane; u < nu; u += 64) {
+    const UnitRef r = u < 64 ? cell0.r : c.ref[u];
+    if (r.ref == M && r.idx < best) best = r.idx;
+  }
+  return lanes::wave_min(best);
+}
+
+// The inverse-CDF draw inside one row, by one wavefront, from the unit cells:
+// target is the weight to pass, in [0, row total), in the row's scale.  The
+// rule at every level (unit, sub-block, element) is the draw's: the last
+// position with positive weight whose exclusive prefix is <= the target
+// (prefixes tile exactly: each position's start is the previous one's end),
+// which also covers rounding past the total.  Returns the row-local token id
+// in every lane.
+template <int DT, bool VEC>
+__device__ __forceinline__ int32_t draw_in_row(const UnitCells &c, int32_t nu, const UnitCell &cell0, float row_ref,
+                                               double target, const char *trow, const char *drow, int64_t V, int mode,
+                                               const DrawJob &job) {
+  const int lane = threadIdx.x & 63;
+  int32_t unit = 0;
+  double unit_excl = 0.0, base = 0.0;
+  float4 us = make_float4(0.f, 0.f, 0.f, 0.f);
+  float uref = 0.f;
+  for (int32_t u0 = 0; u0 < nu; u0 += 64) {
+    const int32_t u = u0 + lane;
+    const UnitCell x = u0 == 0 ? cell0 : load_cell(c, u, nu, mode == 2);
+    const double w = u < nu ? cell_weight(x, mode, row_ref) : 0.0;
     const lanes::Scan<double> sc = lanes::wave_scan(w);
     const double incl = base + sc.incl;
     const double excl = lane == 0 ? base : base + sc.excl;
-    const uint64_t cand = __ballot(ch < nc && w > 0.0 && excl <= target);
+    const uint64_t cand = __ballot(u < nu && w > 0.0 && excl <= target);
     if (cand) {
       const int l = 63 - __builtin_clzll(cand);
-      best = c0 + l;
-      best_excl = lanes::readlane(excl, l);
+      unit = u0 + l;
+      unit_excl = lanes::readlane(excl, l);
+      us = make_float4(lanes::readlane(x.s.x, l), lanes::readlane(x.s.y, l), lanes::readlane(x.s.z, l),
+                       lanes::readlane(x.s.w, l));
+      uref = lanes::readlane(x.r.ref, l);
     }
     base = lanes::readlane(incl, 63);
   }
-  const int32_t chunk = best >= 0 ? best : 0;
-  double rem = target - best_excl;
+  double rem = target - unit_excl;
   if (rem < 0.0) rem = 0.0;
-  const float ref = mode == 2 ? chunk_ref(chunk) : 0.f;
-  if (mode == 2) rem *= exp2_taylor(double(row_ref) - double(ref));  // into the chunk's own scale
+  if (mode == 2) rem *= exp2_taylor(double(row_ref) - double(uref));  // into the unit's own scale
 
-  // the sub-block
-  double sbw = 0.0;
-  if (lane < kSubs) {
-    const float *r = subs + int64_t(chunk) * 64;
-    sbw = double(((r[lane] + r[16 + lane]) + r[32 + lane]) + r[48 + lane]);
-  }
-  const lanes::Scan<double> ss = lanes::wave_scan(sbw);
-  const uint64_t scand = __ballot(lane < kSubs && sbw > 0.0 && ss.excl <= rem);
-  const int sb = scand ? 63 - __builtin_clzll(scand) : 0;
-  double rem2 = rem - lanes::readlane(ss.excl, sb);
+  // the sub-block: the four totals in order (uniform over the wavefront)
+  const double b1 = double(us.x), b2 = b1 + double(us.y), b3 = b2 + double(us.z);
+  int sb = 0;
+  double sub_excl = 0.0;
+  if (us.y > 0.f && b1 <= rem) sb = 1, sub_excl = b1;
+  if (us.z > 0.f && b2 <= rem) sb = 2, sub_excl = b2;
+  if (us.w > 0.f && b3 <= rem) sb = 3, sub_excl = b3;
+  double rem2 = rem - sub_excl;
   if (rem2 < 0.0) rem2 = 0.0;
 
-  // its 512 logits, 8 consecutive per lane
-  const int64_t run0 = int64_t(chunk) * kChunk + int64_t(sb) * kSubLen + 8 * lane;
+  // its 512 logits, 8 consecutive per lane, with the weights evaluated by the
+  // routines of the totals; the lane holding the target walks its own eight
+  const int64_t run0 = int64_t(unit) * kUnit + int64_t(sb) * kSubLen + 8 * lane;
   float w[8];
   {
     float zt[8];
@@ -564,11 +543,11 @@ __device__ inline int32_t draw_in_row(int32_t nc, WF weight, RF chunk_ref, float
       for (int i = 0; i < 8; ++i) w[i] = target_p_weight(zt[i], job);
     } else {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) w[i] = bonus_weight(zt[i], job.scale, ref);
+      for (int i = 0; i < 8; ++i) w[i] = bonus_weight(zt[i], job.scale, uref);
     }
   }
   double run_total = 0.0;
-  int last = -1;
+  int last = -1;  // this lane's last positive weight
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     run_total += double(w[i]);

@@ -15,11 +15,11 @@
 //           update on those KLD values, and the SL rule follows as in
 //           dsde_step.
 //   call 3  shard_mass_kernel: one workgroup per sequence streams the draw
-//           row(s) of its slice once, keeps chunk and sub-block totals in the
-//           workspace and reports the slice's mass.
+//           row(s) of its slice once, keeps the unit cells in the workspace
+//           and reports the slice's mass.
 //   call 4  shard_pick_kernel: every workgroup finds the slice holding the
 //           inverse-CDF point (a fixed-order fp64 prefix over the slices);
-//           the shard owning it draws inside its slice from the totals.
+//           the shard owning it draws inside its slice from the cells.
 #include <math.h>
 #include <stddef.h>
 
@@ -44,23 +44,32 @@ static_assert(sizeof(dsde_shard_mass) == 32, "mass layout");
 
 constexpr int kShardThreads = 256;
 constexpr int kShardWaves = kShardThreads / 64;
+constexpr int kMassThreads = 512;  // a slice of 16,384 logits: one unit per wavefront
 
 // ---- call 1 --------------------------------------------------------------
 
 // One workgroup per sequence: the chunk partials of each drafted pair folded
-// into the slice partial (the combine of the per-sequence kernel).
+// into the slice partial (the combine of the per-sequence kernel).  `lookup`:
+// the statistics pass ran without its set-up kernel, so the layout is checked
+// and seq_err written here.
 template <int GL>
 __global__ __launch_bounds__(kShardThreads) void shard_combine_kernel(
     const PairChunk *__restrict__ part, const ChunkArg *__restrict__ chunk_arg, const Gathered *__restrict__ gath,
     const int32_t *__restrict__ sl, const int32_t *__restrict__ cu_sl, const int32_t *__restrict__ draft_tokens,
-    const float *__restrict__ temperature, const uint32_t *__restrict__ seq_err, int32_t k_max, int32_t nc,
-    int64_t v_begin, int64_t V_shard, dsde_shard_partial *__restrict__ out) {
+    const float *__restrict__ temperature, uint32_t *__restrict__ seq_err, bool lookup, int32_t B, int64_t N,
+    int32_t k_max, int32_t nc, int64_t v_begin, int64_t V_shard, dsde_shard_partial *__restrict__ out) {
   __shared__ float st_mt[DSDE_MAX_K + 1], st_md[DSDE_MAX_K + 1], st_zmax[DSDE_MAX_K + 1];
   __shared__ double st_sp[DSDE_MAX_K + 1], st_sq[DSDE_MAX_K + 1], st_a[DSDE_MAX_K + 1], st_h[DSDE_MAX_K + 1];
   __shared__ int st_bad[DSDE_MAX_K + 1], st_arg[DSDE_MAX_K + 1];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int32_t b = blockIdx.x;
-  if (seq_err[b] & DSDE_ERR_LAYOUT) return;  // the layout is invalid: no position is indexed
+  if (lookup) {  // no set-up kernel ran
+    const int bad = __syncthreads_or(layout_fault(B, N, k_max, sl, cu_sl));
+    if (t == 0) seq_err[b] = bad ? DSDE_ERR_LAYOUT : 0u;
+    if (bad) return;
+  } else if (seq_err[b] & DSDE_ERR_LAYOUT) {
+    return;  // the layout is invalid: no position is indexed
+  }
   const int32_t s = sl[b], first = cu_sl[b];
   const bool greedy = temperature[b] == 0.0f;
   const int64_t slot0 = int64_t(b) * k_max;
@@ -268,22 +277,18 @@ __global__ __launch_bounds__(64) void shard_accept_kernel(
 
 // ---- call 3 --------------------------------------------------------------
 
-// One workgroup per sequence: the draw weight of the slice, wavefront w taking
-// chunks w, w + 4, ...; chunk totals, references, flags and sub-block
-// partials go to the workspace at cell b * nc + ch.
+// One workgroup per sequence: the draw weight of the slice, unit by unit; the
+// cells of sequence b go to the workspace at b * nu.
 template <int DT, bool VEC>
-__global__ __launch_bounds__(kShardThreads) void shard_mass_kernel(
-    const void *__restrict__ target, const void *__restrict__ draft, int64_t V, int32_t nc, int64_t v_begin,
+__global__ __launch_bounds__(kMassThreads) void shard_mass_kernel(
+    const void *__restrict__ target, const void *__restrict__ draft, int64_t V, int32_t nu, int64_t v_begin,
     const dsde_shard_partial *__restrict__ part, const DrawJob *__restrict__ jobs, dsde_shard_mass *__restrict__ mass,
-    double *__restrict__ ch_w, float *__restrict__ ch_ref, int32_t *__restrict__ ch_bad, float *__restrict__ sub) {
-  __shared__ float s_zmax[kMaxChunks];
-  __shared__ int32_t s_idx[kMaxChunks], s_bad[kMaxChunks];
+    float *sub, UnitRef *ref) {
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int32_t b = blockIdx.x;
   const DrawJob job = uniform_job(jobs[b]);
-  const size_t esz = DT == DSDE_BF16 ? 2 : 4;
-  const int64_t cell0 = int64_t(b) * nc;
+  const UnitCells cells{sub + int64_t(b) * nu * kSubs, ref + int64_t(b) * nu};
   dsde_shard_mass m;
   m.mass = 0.0;
   m.p_mass = 0.0;
@@ -291,93 +296,32 @@ __global__ __launch_bounds__(kShardThreads) void shard_mass_kernel(
   m.zmax = -INFINITY;
   m.argmax = -1;
   m.bad = 0;
-  if (job.kind == 0) {
-    const char *trow = (const char *)target + size_t(job.target_row) * size_t(V) * esz;
-    const char *drow = (const char *)draft + size_t(job.draft_row) * size_t(V) * esz;
-    for (int32_t ch = wave; ch < nc; ch += kShardWaves) {
-      const double w = residual_chunk<DT, VEC>(trow, drow, V, ch, job, sub + (cell0 + ch) * 64);
-      if (lane == 0) ch_w[cell0 + ch] = w;
-    }
-    __syncthreads();
-    if (wave == 0) {
-      double acc = 0.0;
-      for (int32_t ch = lane; ch < nc; ch += 64) acc += ch_w[cell0 + ch];
-      m.mass = wave_sum_f64(acc);
-      // this slice's share of p for the rejected pair, from its call-1 partial
-      const dsde_shard_partial pp = part[job.draft_row];
-      m.p_mass = pp.sp * exp2_taylor(double(pp.mt) - double(job.mt)) * double(job.inv_sp);
-      if (lane == 0) mass[b] = m;
-    }
-  } else if (job.kind == 1) {
-    const char *trow = (const char *)target + size_t(job.target_row) * size_t(V) * esz;
-    for (int32_t ch = wave; ch < nc; ch += kShardWaves) {
-      double w;
-      float ref;
-      int bd;
-      bonus_chunk<DT, VEC>(trow, V, ch, job.scale, &w, &ref, &bd, sub + (cell0 + ch) * 64);
-      if (lane == 0) {
-        ch_w[cell0 + ch] = w;
-        ch_ref[cell0 + ch] = ref;
-        ch_bad[cell0 + ch] = bd;
-      }
-    }
-    __syncthreads();
-    if (wave == 0) {
-      float ref = -INFINITY;
-      int bd = 0;
-      for (int32_t ch = lane; ch < nc; ch += 64) {
-        ref = fmaxf(ref, ch_ref[cell0 + ch]);
-        bd |= ch_bad[cell0 + ch];
-      }
-      ref = wave_max(ref);
-      bd = lanes::wave_or(bd);
-      double acc = 0.0;
-      if (!bd)
-        for (int32_t ch = lane; ch < nc; ch += 64)
-          acc += ch_w[cell0 + ch] * exp2_taylor(double(ch_ref[cell0 + ch]) - double(ref));
-      m.mass = wave_sum_f64(acc);
-      m.ref = ref;
-      m.bad = bd;
-      if (lane == 0) mass[b] = m;
-    }
-  } else if (job.kind == 3) {
-    const char *trow = (const char *)target + size_t(job.target_row) * size_t(V) * esz;
-    for (int32_t ch = wave; ch < nc; ch += kShardWaves) {
-      float zmax;
-      int32_t idx;
-      int bd;
-      bonus_argmax_chunk<DT, VEC>(trow, V, ch, &zmax, &idx, &bd);
-      if (lane == 0) {
-        s_zmax[ch] = zmax;
-        s_idx[ch] = idx;
-        s_bad[ch] = bd;
-      }
-    }
-    __syncthreads();
-    if (wave == 0) {
-      // the chunk holding the slice maximum (the earliest on ties)
-      float best = -INFINITY;
-      int32_t bch = 0x7fffffff;
-      int bd = 0;
-      for (int32_t ch = lane; ch < nc; ch += 64) {
-        bd |= s_bad[ch];
-        if (bch == 0x7fffffff || s_zmax[ch] > best) {
-          best = s_zmax[ch];
-          bch = ch;
-        }
-      }
-      bd = lanes::wave_or(bd);
-      const float M = wave_max(best);
-      int32_t cand = bch != 0x7fffffff && best == M ? bch : 0x7fffffff;
-      cand = lanes::wave_min(cand);
-      m.zmax = M;
-      m.argmax = int32_t(v_begin + s_idx[cand]);
-      m.bad = bd;
-      if (lane == 0) mass[b] = m;
-    }
-  } else if (t == 0) {
-    mass[b] = m;
+  if (job.kind < 0 || job.kind == 2) {
+    if (t == 0) mass[b] = m;
+    return;
   }
+  draw_units<DT, VEC>(job, (const char *)target, (const char *)draft, V, nu, wave, kMassThreads / 64, cells);
+  __syncthreads();
+  if (wave != 0) return;
+  const UnitCell cell0 = load_cell(cells, lane, nu, job.kind != 0);
+  if (job.kind == 0) {
+    m.mass = row_total(cells, nu, cell0, 0, 0.f);
+    // this slice's share of p for the rejected pair, from its call-1 partial
+    const dsde_shard_partial pp = part[job.draft_row];
+    m.p_mass = pp.sp * exp2_taylor(double(pp.mt) - double(job.mt)) * double(job.inv_sp);
+  } else {
+    bool bad;
+    const float r = row_reference(cells, nu, cell0, &bad);
+    m.bad = bad;
+    if (job.kind == 1) {
+      m.ref = r;
+      if (!bad) m.mass = row_total(cells, nu, cell0, 2, r);
+    } else {
+      m.zmax = r;
+      if (!bad) m.argmax = int32_t(v_begin + row_argmax(cells, nu, cell0, r));
+    }
+  }
+  if (lane == 0) mass[b] = m;
 }
 
 // ---- call 4 --------------------------------------------------------------
@@ -389,10 +333,9 @@ __global__ __launch_bounds__(kShardThreads) void shard_mass_kernel(
 template <int DT, bool VEC>
 __global__ __launch_bounds__(kShardThreads) void shard_pick_kernel(
     int32_t G, int32_t gself, const dsde_shard_mass *__restrict__ masses, int32_t B, const void *__restrict__ target,
-    const void *__restrict__ draft, int64_t V, int32_t nc, int64_t v_begin, int32_t k_max,
+    const void *__restrict__ draft, int64_t V, int32_t nu, int64_t v_begin, int32_t k_max,
     const DrawJob *__restrict__ jobs, int32_t pad_id, int32_t *__restrict__ accepted, int32_t *__restrict__ tokens,
-    int32_t *__restrict__ drawn, uint32_t *__restrict__ seq_err, double *__restrict__ ch_w,
-    const float *__restrict__ ch_ref, float *__restrict__ sub) {
+    int32_t *__restrict__ drawn, uint32_t *__restrict__ seq_err, float *sub, UnitRef *ref) {
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int32_t b = blockIdx.x;
@@ -497,23 +440,14 @@ __global__ __launch_bounds__(kShardThreads) void shard_pick_kernel(
   const size_t esz = DT == DSDE_BF16 ? 2 : 4;
   const char *trow = (const char *)target + size_t(job.target_row) * size_t(V) * esz;
   const char *drow = job.draft_row >= 0 ? (const char *)draft + size_t(job.draft_row) * size_t(V) * esz : nullptr;
-  const int64_t cell0 = int64_t(b) * nc;
+  const UnitCells cells{sub + int64_t(b) * nu * kSubs, ref + int64_t(b) * nu};
   if (mode == 1) {  // the slice's p totals, which call 3 did not keep
-    for (int32_t ch = wave; ch < nc; ch += kShardWaves) {
-      const double p = target_p_chunk<DT, VEC>(trow, V, ch, job, sub + (cell0 + ch) * 64);
-      if (lane == 0) ch_w[cell0 + ch] = p;
-    }
+    for (int32_t u = wave; u < nu; u += kShardWaves) target_p_unit<DT, VEC>(trow, V, u, job, cells);
     __syncthreads();
   }
   if (wave != 0) return;
-  const int32_t local = draw_in_row<DT, VEC>(
-      nc,
-      [&](int32_t ch) -> double {
-        return mode == 2 ? ch_w[cell0 + ch] * exp2_taylor(double(ch_ref[cell0 + ch]) - double(row_ref))
-                         : ch_w[cell0 + ch];
-      },
-      [&](int32_t ch) -> float { return ch_ref[cell0 + ch]; }, row_ref, rem, sub + cell0 * 64, trow, drow, V, mode,
-      job);
+  const UnitCell cell0 = load_cell(cells, lane, nu, mode == 2);
+  const int32_t local = draw_in_row<DT, VEC>(cells, nu, cell0, row_ref, rem, trow, drow, V, mode, job);
   if (lane == 0) {
     const int32_t token = int32_t(v_begin + local);
     tok[job.accepted] = token;
@@ -574,19 +508,23 @@ int launch_shard_stats(const ShardRows &r, int64_t V, const int32_t *sl, const i
   ChunkArg *cargs = (ChunkArg *)(ws + L.stats.chunk_arg);
   // the shard partial always carries the entropy accumulator: whether a
   // caller wants the entropy is known only when the partials are combined
-  launch_stats_pass(a, work, pc, gath, cargs, true);
+  const bool lookup = r.N > 0 && stats_lookup(a);  // N = 0: the set-up kernel alone, it writes seq_err
+  launch_stats_pass(a, lookup, work, pc, gath, cargs, true);
   if (r.N > 0) {
     const int32_t nc = int32_t(num_chunks(r.V_shard));
     const dim3 grid(unsigned(r.B)), block(kShardThreads);
     if (nc <= 16)
       shard_combine_kernel<16><<<grid, block, 0, r.stream>>>(pc, cargs, gath, sl, cu_sl, draft_tokens, temperature,
-                                                             seq_err, r.k_max, nc, r.v_begin, r.V_shard, part);
+                                                             seq_err, lookup, r.B, r.N, r.k_max, nc, r.v_begin,
+                                                             r.V_shard, part);
     else if (nc <= 32)
       shard_combine_kernel<32><<<grid, block, 0, r.stream>>>(pc, cargs, gath, sl, cu_sl, draft_tokens, temperature,
-                                                             seq_err, r.k_max, nc, r.v_begin, r.V_shard, part);
+                                                             seq_err, lookup, r.B, r.N, r.k_max, nc, r.v_begin,
+                                                             r.V_shard, part);
     else
       shard_combine_kernel<64><<<grid, block, 0, r.stream>>>(pc, cargs, gath, sl, cu_sl, draft_tokens, temperature,
-                                                             seq_err, r.k_max, nc, r.v_begin, r.V_shard, part);
+                                                             seq_err, lookup, r.B, r.N, r.k_max, nc, r.v_begin,
+                                                             r.V_shard, part);
   }
   return hipGetLastError() == hipSuccess ? DSDE_OK : DSDE_DEVICE_ERROR;
 }
@@ -617,13 +555,13 @@ int launch_shard_draw_mass(const ShardRows &r, const dsde_shard_partial *part, c
                            dsde_shard_mass *mass) {
   const ShardLayout L = shard_layout(r.B, r.N, r.V_shard, r.k_max);
   char *ws = (char *)r.workspace;
-  const int32_t nc = int32_t(num_chunks(r.V_shard));
+  const int32_t nu = int32_t(num_units(r.V_shard));
   (void)hipGetLastError();
   by_layout(r, [&](auto dt, auto vec) {
-    shard_mass_kernel<decltype(dt)::value, decltype(vec)::value><<<dim3(unsigned(r.B)), dim3(kShardThreads), 0,
+    shard_mass_kernel<decltype(dt)::value, decltype(vec)::value><<<dim3(unsigned(r.B)), dim3(kMassThreads), 0,
                                                                    r.stream>>>(
-        r.target, r.draft, r.V_shard, nc, r.v_begin, part, reinterpret_cast<const DrawJob *>(jobs), mass,
-        (double *)(ws + L.ch_w), (float *)(ws + L.ch_ref), (int32_t *)(ws + L.ch_bad), (float *)(ws + L.sub));
+        r.target, r.draft, r.V_shard, nu, r.v_begin, part, reinterpret_cast<const DrawJob *>(jobs), mass,
+        (float *)(ws + L.sub), (UnitRef *)(ws + L.ref));
   });
   return hipGetLastError() == hipSuccess ? DSDE_OK : DSDE_DEVICE_ERROR;
 }
@@ -633,14 +571,14 @@ int launch_shard_draw_pick(const ShardRows &r, int32_t G, int32_t g, const dsde_
                            int32_t *drawn, uint32_t *seq_err) {
   const ShardLayout L = shard_layout(r.B, r.N, r.V_shard, r.k_max);
   char *ws = (char *)r.workspace;
-  const int32_t nc = int32_t(num_chunks(r.V_shard));
+  const int32_t nu = int32_t(num_units(r.V_shard));
   (void)hipGetLastError();
   by_layout(r, [&](auto dt, auto vec) {
     shard_pick_kernel<decltype(dt)::value, decltype(vec)::value><<<dim3(unsigned(r.B)), dim3(kShardThreads), 0,
                                                                    r.stream>>>(
-        G, g, masses, r.B, r.target, r.draft, r.V_shard, nc, r.v_begin, r.k_max,
-        reinterpret_cast<const DrawJob *>(jobs), pad_id, accepted, tokens, drawn, seq_err, (double *)(ws + L.ch_w),
-        (const float *)(ws + L.ch_ref), (float *)(ws + L.sub));
+        G, g, masses, r.B, r.target, r.draft, r.V_shard, nu, r.v_begin, r.k_max,
+        reinterpret_cast<const DrawJob *>(jobs), pad_id, accepted, tokens, drawn, seq_err, (float *)(ws + L.sub),
+        (UnitRef *)(ws + L.ref));
   });
   return hipGetLastError() == hipSuccess ? DSDE_OK : DSDE_DEVICE_ERROR;
 }

@@ -7,26 +7,22 @@
 namespace dsde {
 
 // One shard's workspace: the statistics pass's buffers for the slice width,
-// then the draw's chunk totals of every sequence (call 3 writes them, call 4
+// then the draw's unit cells of every sequence (call 3 writes them, call 4
 // reads them).
 struct ShardLayout {
   WorkspaceLayout stats;
-  size_t ch_w, ch_ref, ch_bad, sub, total;
+  size_t sub, ref, total;
 };
 
 inline ShardLayout shard_layout(int32_t B, int64_t N, int64_t V_shard, int32_t k_max) {
   ShardLayout L;
   L.stats = workspace_layout(B, N, V_shard, k_max);
-  const size_t cells = size_t(B) * size_t(num_chunks(V_shard));
+  const size_t cells = size_t(B) * size_t(num_units(V_shard));
   size_t off = L.stats.total;
-  L.ch_w = off;
-  off += align_up(sizeof(double) * cells);
-  L.ch_ref = off;
-  off += align_up(sizeof(float) * cells);
-  L.ch_bad = off;
-  off += align_up(sizeof(int32_t) * cells);
   L.sub = off;
-  off += align_up(sizeof(float) * 64 * cells);
+  off += align_up(4 * sizeof(float) * cells);
+  L.ref = off;
+  off += align_up(sizeof(UnitRef) * cells);
   L.total = off;
   return L;
 }

@@ -11,7 +11,9 @@
 //                      SL_max per sequence or pooled over the batch.
 //   next_sl_kernel     one workgroup: SL_hat per sequence, the mean cap, the
 //                      rounded and clamped next lengths (also the last kernel
-//                      of the fused step, where it ORs its error bits).
+//                      of the fused sharded call 2, where it ORs its error
+//                      bits; the fused step runs the same code in a workgroup
+//                      of its last kernel).
 // Both cost their launch, not bytes.
 #include <math.h>
 
@@ -22,7 +24,6 @@ namespace dsde {
 namespace {
 
 constexpr int kSigThreads = 256;  // 4 sequences per workgroup
-constexpr int kCapThreads = 256;
 
 __global__ __launch_bounds__(kSigThreads) void kld_signal_kernel(
     int32_t B, int64_t N, const int32_t *__restrict__ sl, const int32_t *__restrict__ cu_sl,

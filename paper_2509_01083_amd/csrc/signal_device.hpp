@@ -196,6 +196,10 @@ __device__ __forceinline__ double sl_hat_of(double sf, double wvir, double sl_ma
   return pen <= 1.0 ? (1.0 - pen) * (sl_max - sl_min) + sl_min : sl_min;
 }
 
+// Threads of the workgroup that runs block_next_sl, wherever it runs: the order
+// of the cap's sum depends on it.
+constexpr int kCapThreads = 256;
+
 // Sequences per thread whose inputs block_next_sl keeps in registers between
 // its two passes (one memory round trip); larger batches load them twice.
 constexpr int kNextSlRegs = 4;
@@ -205,8 +209,8 @@ constexpr int kNextSlRegs = 4;
 // per-sequence token budget (optional) bounds each next length.  Per-thread
 // fp64 partial sums, wavefront butterflies, then the wavefront totals in order:
 // a fixed order, so the cap is bitwise reproducible.  seq_err bits are OR-ed
-// into what earlier kernels wrote when `or_err` is set (fused step), else
-// written.
+// (atomically: other workgroups of the fused step's last kernel may set bits
+// of their own) into what is there when `or_err` is set, else written.
 
 __device__ inline void block_next_sl(int32_t B, const float *sf, const float *wvir, const float *sl_max,
                                      float sl_min, int32_t sl_hi, const int32_t *budget, float *sl_hat,
@@ -220,7 +224,6 @@ __device__ inline void block_next_sl(int32_t B, const float *sf, const float *wv
   // with a small batch every input of both passes is loaded here at once
   float r_f[kNextSlRegs], r_w[kNextSlRegs], r_m[kNextSlRegs];
   int32_t r_bud[kNextSlRegs];
-  uint32_t r_err[kNextSlRegs];
   if (cached) {
 #pragma unroll
     for (int i = 0; i < kNextSlRegs; ++i) {
@@ -229,7 +232,6 @@ __device__ inline void block_next_sl(int32_t B, const float *sf, const float *wv
       r_w[i] = b < B ? wvir[b] : 0.f;
       r_m[i] = b < B ? sl_max[b] : 0.f;
       r_bud[i] = b < B && budget ? budget[b] : 0;
-      r_err[i] = b < B && or_err ? seq_err[b] : 0u;
     }
   }
   double part = 0.0;
@@ -276,11 +278,12 @@ __device__ inline void block_next_sl(int32_t B, const float *sf, const float *wv
   const double cap = n > 0 ? total / double(n) : NAN;
   if (t == 0) sl_cap[0] = float(cap);
   // pass 2: the rounded, clamped next length under the cap
-  auto next_of = [&](int32_t b, double f, double w, double mx, int32_t bud, uint32_t err) {
+  auto next_of = [&](int32_t b, double f, double w, double mx, int32_t bud) {
     const bool ok = isfinite(f) && isfinite(w) && isfinite(mx) && mx >= lo_f;
-    // or_err: only this thread writes seq_err[b] in this kernel, so a plain
-    // read-modify-write adds the signal bit to what earlier kernels set
-    seq_err[b] = or_err ? (ok ? err : err | DSDE_ERR_SIGNAL) : (ok ? 0u : DSDE_ERR_SIGNAL);
+    if (!or_err)
+      seq_err[b] = ok ? 0u : DSDE_ERR_SIGNAL;
+    else if (!ok)
+      atomicOr(&seq_err[b], DSDE_ERR_SIGNAL);
     int32_t next = lo;
     if (ok) {
       const double hat = sl_hat_of(f, w, mx, lo_f);
@@ -300,11 +303,11 @@ __device__ inline void block_next_sl(int32_t B, const float *sf, const float *wv
 #pragma unroll
     for (int i = 0; i < kNextSlRegs; ++i) {
       const int32_t b = t + i * nt;
-      if (b < B) next_of(b, r_f[i], r_w[i], r_m[i], r_bud[i], r_err[i]);
+      if (b < B) next_of(b, r_f[i], r_w[i], r_m[i], r_bud[i]);
     }
   } else {
     for (int32_t b = t; b < B; b += nt)
-      next_of(b, sf[b], wvir[b], sl_max[b], budget ? budget[b] : 0, or_err ? seq_err[b] : 0u);
+      next_of(b, sf[b], wvir[b], sl_max[b], budget ? budget[b] : 0);
   }
 }
 

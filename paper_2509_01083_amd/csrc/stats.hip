@@ -2,10 +2,11 @@
 // (drafted row pair, 8192-logit chunk) reads the chunk of the target and
 // draft rows once and writes max-shifted exponential sums of p and q and the
 // KL accumulator (Sec. 3.1.2), and captures the two logits at the drafted
-// token.  It carries almost all HBM bytes of the step.  A one-workgroup
-// set-up kernel before it validates the packed layout (Sec. 3.2) and writes
-// the work list (target row and scale of every drafted pair, in sequence
-// order).
+// token.  It carries almost all HBM bytes of the step.  In large batches a
+// one-workgroup set-up kernel before it validates the packed layout (Sec. 3.2)
+// and writes the work list (target row and scale of every drafted pair, in
+// sequence order); in small ones the workgroups find their pair themselves
+// (stats_lookup) and the kernel behind the pass validates the layout.
 #include <hip/hip_ext.h>
 #include <math.h>
 
@@ -18,6 +19,14 @@ namespace {
 // ---------------------------------------------------------------------------
 // set-up
 // ---------------------------------------------------------------------------
+
+// The scale of one sequence's logits, by the same expression as every later
+// kernel's; a temperature outside the admissible range is flagged by the
+// acceptance kernel.  T = 0 selects greedy verification: statistics at T = 1,
+// and the sign bit asks for the chunk argmax of the target row.
+__device__ __forceinline__ uint32_t scale_bits(float T) {
+  return T == 0.0f ? (__float_as_uint(kLog2e) | kGreedyBit) : __float_as_uint(kLog2e / T);
+}
 
 __global__ __launch_bounds__(1024) void setup_kernel(int32_t B, int64_t N, int32_t k_max,
                                                      const int32_t *__restrict__ sl,
@@ -52,13 +61,9 @@ __global__ __launch_bounds__(1024) void setup_kernel(int32_t B, int64_t N, int32
     for (int64_t k = t; k < N; k += blockDim.x) work[k] = WorkItem{int32_t(k), -1, 0u, -1};
     return;
   }
-  // the same expression as every later kernel's scale; a temperature outside
-  // the admissible range is flagged by the acceptance kernel.  T = 0 selects
-  // greedy verification: statistics at T = 1, and the sign bit asks the
-  // statistics kernel for the chunk argmax of the target row.
   auto list = [&](int32_t b, int32_t first, int32_t s, float T) {
     seq_err[b] = 0u;
-    const uint32_t cbits = T == 0.0f ? (__float_as_uint(kLog2e) | kGreedyBit) : __float_as_uint(kLog2e / T);
+    const uint32_t cbits = scale_bits(T);
     for (int32_t j = 0; j < s; ++j) work[first + j] = WorkItem{first + j, first + b + j, cbits, b * k_max + j};
   };
   if (one) {
@@ -71,6 +76,42 @@ __global__ __launch_bounds__(1024) void setup_kernel(int32_t B, int64_t N, int32
 // ---------------------------------------------------------------------------
 // row statistics of every drafted pair
 // ---------------------------------------------------------------------------
+
+// The pair and chunk of one workgroup.  From the set-up's work list: workgroup
+// x takes chunk x % nc of entry x / nc.  LOOKUP: workgroup (x, y, z) takes
+// chunk x of position (y + z) mod k_max of sequence z; it checks only what
+// keeps its own reads in bounds (the whole layout is checked by the kernel
+// behind).  Workgroups go to the XCDs and shader engines in turn, so without
+// the rotation by z each engine would hold the same few positions of every
+// sequence, the early ones always busy and the late ones mostly empty (1.45
+// times the time at 256 sequences of 1 to 8 positions and 4 chunks).
+struct BatchLayout {
+  const int32_t *sl, *cu_sl;
+  const float *temperature;
+  int64_t N;
+  int32_t k_max;
+  uint32_t k_rcp;  // ceil(2^32 / k_max): n / k_max = high word of n * k_rcp for n < 2^16
+};
+template <bool LOOKUP>
+__device__ __forceinline__ bool find_item(const WorkItem *__restrict__ work, const BatchLayout &L, int32_t nc,
+                                          WorkItem *w, int64_t *chunk) {
+  if constexpr (LOOKUP) {
+    const int32_t b = blockIdx.z;
+    const uint32_t n = blockIdx.y + blockIdx.z;
+    const int32_t j = int32_t(L.k_max > 1 ? n - __umulhi(n, L.k_rcp) * uint32_t(L.k_max) : 0u);
+    const int32_t s = L.sl[b], first = L.cu_sl[b];
+    const float T = L.temperature[b];
+    *chunk = blockIdx.x;
+    if (j >= s || s > L.k_max || first < 0 || int64_t(first) + s > L.N) return false;
+    *w = WorkItem{first + j, first + b + j, scale_bits(T), b * L.k_max + j};
+    return true;
+  } else {
+    const int64_t unit = blockIdx.x, k = unit / nc;
+    *chunk = unit - k * nc;
+    *w = work[k];
+    return w->target_row >= 0;
+  }
+}
 
 // Greedy pairs: each wavefront's smallest token id holding the chunk maximum
 // M of the target row, into red[wave] (0xffffffff if none).  Only a thread
@@ -164,10 +205,11 @@ __device__ __forceinline__ void write_pair_chunk(float rt, float rd, const PairA
 // VALU instructions per logit pair).  Two kernels rather than a branch in
 // one: with both forms in one body the compiler hoists their common
 // arithmetic above the branch and nearly doubles the register footprint.
-template <bool ENT>
+template <bool ENT, bool LOOKUP>
 __global__ __launch_bounds__(kThreads) void stats_kernel_bf16(const void *__restrict__ target,
                                                              const void *__restrict__ draft, int64_t V, int32_t nc,
                                                              const WorkItem *__restrict__ work,
+                                                             const BatchLayout layout,
                                                              const int32_t *__restrict__ draft_tokens,
                                                              int64_t token_base, PairChunk *__restrict__ out,
                                                              Gathered *__restrict__ gathered,
@@ -175,11 +217,9 @@ __global__ __launch_bounds__(kThreads) void stats_kernel_bf16(const void *__rest
   __shared__ float red[2][kWaves];
   __shared__ double red_sum[4][kWaves];
   __shared__ uint32_t red_arg[kWaves];
-  const int64_t unit = blockIdx.x;
-  const int64_t k = unit / nc;
-  const int64_t chunk = unit - k * nc;
-  const WorkItem w = work[k];
-  if (w.target_row < 0) return;
+  int64_t chunk;
+  WorkItem w;
+  if (!find_item<LOOKUP>(work, layout, nc, &w, &chunk)) return;
   const int t = threadIdx.x;
   const bool greedy = (w.scale_bits & kGreedyBit) != 0;
   const float c = __uint_as_float(w.scale_bits & ~kGreedyBit);
@@ -226,10 +266,11 @@ __global__ __launch_bounds__(kThreads) void stats_kernel_bf16(const void *__rest
 }
 
 // fp32 rows, or rows without 16-byte alignment.
-template <int DT, bool VEC>
+template <int DT, bool VEC, bool LOOKUP>
 __global__ __launch_bounds__(kThreads) void stats_kernel_generic(const void *__restrict__ target,
                                                                 const void *__restrict__ draft, int64_t V,
                                                                 int32_t nc, const WorkItem *__restrict__ work,
+                                                                const BatchLayout layout,
                                                                 const int32_t *__restrict__ draft_tokens,
                                                                 int64_t token_base, PairChunk *__restrict__ out,
                                                                 Gathered *__restrict__ gathered,
@@ -237,11 +278,9 @@ __global__ __launch_bounds__(kThreads) void stats_kernel_generic(const void *__r
   __shared__ float red[2][kWaves];
   __shared__ double red_sum[4][kWaves];
   __shared__ uint32_t red_arg[kWaves];
-  const int64_t unit = blockIdx.x;
-  const int64_t k = unit / nc;
-  const int64_t chunk = unit - k * nc;
-  const WorkItem w = work[k];
-  if (w.target_row < 0) return;
+  int64_t chunk;
+  WorkItem w;
+  if (!find_item<LOOKUP>(work, layout, nc, &w, &chunk)) return;
   const int t = threadIdx.x;
   const bool greedy = (w.scale_bits & kGreedyBit) != 0;
   const float c = __uint_as_float(w.scale_bits & ~kGreedyBit);
@@ -310,36 +349,63 @@ bool rows_vectorizable(const VerifyArgs &a) {
          (a.dtype == DSDE_BF16 ? a.V % 8 == 0 : a.V % 4 == 0);
 }
 
-void launch_stats_pass(const VerifyArgs &a, WorkItem *work, PairChunk *part, Gathered *gath, ChunkArg *chunk_arg,
-                       bool entropy) {
+// Whether the statistics pass runs without the set-up kernel, on a grid over
+// (chunk, position < k_max, sequence) whose workgroups past SL_b exit at once.
+// That saves a dependent launch (2.2 us on the device after an idle gap, 4.8 us
+// behind other kernels, and its enqueueing on the host) and costs, with the
+// engines' uneven shares of the empty ones, 0.4-0.5 ns for each empty
+// workgroup: 256 sequences of 1-8 positions at 4 chunks (3,600 empty) 26.8 ->
+// 28.2 us; at 16 chunks (15,000 empty) 90.7 -> 97.6 us, more than the launch.
+// 1,024 sequences of 2-3 positions at 16 chunks (8,200 empty) came out equal.
+// With profiling events the set-up kernel's completion is the start mark, so it
+// has to run.
+constexpr int64_t kMaxEmptyWorkgroups = 4096;
+constexpr int32_t kLookupSeqs = 1024;  // one workgroup per sequence of the kernel behind reads the whole layout
+bool stats_lookup(const VerifyArgs &a) {
+  if (a.prof_start && a.prof_stop) return false;
+  return a.B <= kLookupSeqs && (int64_t(a.B) * a.k_max - a.N) * num_chunks(a.V) <= kMaxEmptyWorkgroups;
+}
+
+template <bool LOOKUP>
+static void launch_rows(const VerifyArgs &a, const WorkItem *w, PairChunk *part, Gathered *gath, ChunkArg *chunk_arg,
+                        bool entropy, hipEvent_t done) {
   const int32_t nc = int32_t(num_chunks(a.V));
-  const bool prof = a.prof_start && a.prof_stop && a.N > 0;
-  launch_timed(setup_kernel, dim3(1), dim3(1024), a.stream, prof ? a.prof_start : nullptr, a.B, a.N, a.k_max,
-               a.sl, a.cu_sl, a.temperature, a.seq_err, work);
-  if (a.N == 0) return;
   const bool vec = rows_vectorizable(a);
-  const dim3 grid(unsigned(a.N * nc)), block(kThreads);
-  hipEvent_t done = prof ? a.prof_stop : nullptr;
+  const dim3 grid = LOOKUP ? dim3(unsigned(nc), unsigned(a.k_max), unsigned(a.B)) : dim3(unsigned(a.N * nc));
+  const dim3 block(kThreads);
   const void *T = a.target, *D = a.draft;
   const int64_t V = a.V;
   const int32_t *tokens = a.draft_tokens;
   const int64_t base = a.token_base;
-  const WorkItem *w = work;
+  const uint32_t k_rcp = a.k_max > 1 ? uint32_t(((uint64_t(1) << 32) + a.k_max - 1) / a.k_max) : 0u;
+  const BatchLayout L{a.sl, a.cu_sl, a.temperature, a.N, a.k_max, k_rcp};
   if (a.dtype == DSDE_BF16 && vec && entropy)
-    launch_timed(stats_kernel_bf16<true>, grid, block, a.stream, done, T, D, V, nc, w, tokens, base, part, gath,
-                 chunk_arg);
+    launch_timed(stats_kernel_bf16<true, LOOKUP>, grid, block, a.stream, done, T, D, V, nc, w, L, tokens, base, part,
+                 gath, chunk_arg);
   else if (a.dtype == DSDE_BF16 && vec)
-    launch_timed(stats_kernel_bf16<false>, grid, block, a.stream, done, T, D, V, nc, w, tokens, base, part, gath,
-                 chunk_arg);
+    launch_timed(stats_kernel_bf16<false, LOOKUP>, grid, block, a.stream, done, T, D, V, nc, w, L, tokens, base, part,
+                 gath, chunk_arg);
   else if (a.dtype == DSDE_BF16)
-    launch_timed(stats_kernel_generic<DSDE_BF16, false>, grid, block, a.stream, done, T, D, V, nc, w, tokens, base,
-                 part, gath, chunk_arg);
+    launch_timed(stats_kernel_generic<DSDE_BF16, false, LOOKUP>, grid, block, a.stream, done, T, D, V, nc, w, L,
+                 tokens, base, part, gath, chunk_arg);
   else if (vec)
-    launch_timed(stats_kernel_generic<DSDE_FP32, true>, grid, block, a.stream, done, T, D, V, nc, w, tokens, base,
-                 part, gath, chunk_arg);
+    launch_timed(stats_kernel_generic<DSDE_FP32, true, LOOKUP>, grid, block, a.stream, done, T, D, V, nc, w, L, tokens,
+                 base, part, gath, chunk_arg);
   else
-    launch_timed(stats_kernel_generic<DSDE_FP32, false>, grid, block, a.stream, done, T, D, V, nc, w, tokens, base,
-                 part, gath, chunk_arg);
+    launch_timed(stats_kernel_generic<DSDE_FP32, false, LOOKUP>, grid, block, a.stream, done, T, D, V, nc, w, L,
+                 tokens, base, part, gath, chunk_arg);
+}
+
+void launch_stats_pass(const VerifyArgs &a, bool lookup, WorkItem *work, PairChunk *part, Gathered *gath,
+                       ChunkArg *chunk_arg, bool entropy) {
+  const bool prof = a.prof_start && a.prof_stop && a.N > 0;
+  if (lookup) {
+    if (a.N > 0) launch_rows<true>(a, nullptr, part, gath, chunk_arg, entropy, nullptr);
+    return;
+  }
+  launch_timed(setup_kernel, dim3(1), dim3(1024), a.stream, prof ? a.prof_start : nullptr, a.B, a.N, a.k_max,
+               a.sl, a.cu_sl, a.temperature, a.seq_err, work);
+  if (a.N > 0) launch_rows<false>(a, work, part, gath, chunk_arg, entropy, prof ? a.prof_stop : nullptr);
 }
 
 }  // namespace dsde

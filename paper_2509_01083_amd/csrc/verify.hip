@@ -4,18 +4,23 @@
 //
 // Kernels, in launch order on the caller's stream:
 //   setup_kernel, stats_kernel   (stats.hip) layout check, work list, and the
-//                      row statistics of every drafted pair, chunk by chunk.
-//   seq_kernel         one workgroup per sequence: combines the chunk partials
-//                      of its drafted pairs (fp64), KLD, acceptance u < p(x)/q(x)
-//                      (fp64) up to the first rejection, then the draw: the
-//                      residual max(0, p - q) of the rejected pair (or the bonus
-//                      row) streamed one wavefront per chunk with the chunk
-//                      and sub-block totals in LDS, then one wavefront: a
-//                      fixed-order fp64 prefix to the chunk holding u' * Z, the
-//                      same over its 16 sub-blocks, and an ordered scan of the
-//                      512 logits of the sub-block found.
-//                      Fused step: one wavefront also runs the signal update.
-//   next_sl_kernel     (signal.hip, fused step only) batch cap and next lengths.
+//                      row statistics of every drafted pair, chunk by chunk
+//                      (small batches: no set-up kernel, seq_kernel checks the
+//                      layout).
+//   seq_kernel         several workgroups per sequence.  Each combines the chunk
+//                      partials of the sequence's drafted pairs (fp64) and finds
+//                      the acceptance u < p(x)/q(x) (fp64) up to the first
+//                      rejection.  One of them writes the outputs (accepted
+//                      drafts, KLD, and in the fused step the signal update);
+//                      the others stream the draw's row(s), the residual
+//                      max(0, p - q) of the rejected pair or the bonus row, and
+//                      leave weight totals per unit of 2048 logits.
+//   pick_kernel        one workgroup per sequence: the token, by a fixed-order
+//                      fp64 prefix over the units to the one holding u' * Z, the
+//                      same over its four sub-blocks, and an ordered scan of the
+//                      512 logits of the sub-block found.  Fused step: one more
+//                      workgroup runs the batch cap and the next lengths, which
+//                      need nothing from the draw.
 //
 // Every reduction runs in a fixed order, so results are bitwise reproducible.
 #include <math.h>
@@ -28,20 +33,17 @@
 namespace dsde {
 namespace {
 
-// ---------------------------------------------------------------------------
-// per-sequence kernel: acceptance, draw weights and draw
-// ---------------------------------------------------------------------------
-
-// Threads per sequence: 512 (8 wavefronts) when every sequence has a CU of its
-// own, 256 when sequences outnumber the CUs (then three workgroups share a CU
-// and each one's latency-bound phases overlap the others' row streams).
-constexpr int kSeqThreadsWide = 512;
-constexpr int kSeqThreadsNarrow = 256;
+constexpr int kSeqThreads = 256;
+constexpr int kSeqWaves = kSeqThreads / 64;
+constexpr int kSignalWave = kSeqWaves - 1;  // wavefront of the KLD outputs and the fused signal update
 
 struct StepParams {
   const void *target, *draft;
   int64_t V;
-  int32_t B, k_max, nc, pad_id;
+  int32_t B, k_max, nc, nu, pad_id;
+  bool lookup;        // no set-up kernel ran: this kernel checks the layout and writes seq_err
+  int64_t N;
+  int32_t first_seq;  // first sequence of this pass (the cells and jobs are indexed from it)
   const int32_t *sl, *cu_sl, *draft_tokens;
   const float *temperature, *u_acc, *u_res;
   int32_t *accepted, *tokens;
@@ -52,37 +54,36 @@ struct StepParams {
   const PairChunk *part;
   const Gathered *gathered;
   const ChunkArg *chunk_arg;  // greedy pairs: the target row's maximum and argmax per chunk
+  DrawJob *jobs;
+  float *sub;
+  UnitRef *ref;
 };
 
-// One workgroup per sequence.
-//   1. all wavefronts: combine the chunk partials of the drafted pairs (fp64);
-//      wavefront 0: input checks, acceptance u < p(x)/q(x) (fp64), the
-//      accepted tokens and the draw job.  The last wavefront then writes the
-//      KLD (and entropy, log-normalisers) of every position and, fused, runs
-//      the signal update of the sequence.
-//   2. wavefront w: the draw-weight totals of chunks w, w + 8, ... (residual
-//      max(0, p - q) of the first rejected pair, or the bonus row), into LDS.
-//   3. wavefront 0: fixed-order fp64 prefix over the chunk totals to the chunk
-//      holding u' * Z, the same over that chunk's sub-block totals, then the
-//      ordered scan of the sub-block (the other wavefronts are done).
-template <int DT, bool VEC, bool FUSED, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == kSeqThreadsNarrow ? 3 : 1))) void seq_kernel(
-    const StepParams P, const SignalArgs S) {
-  constexpr int kSeqWaves = NT / 64;
-  constexpr int kSignalWave = kSeqWaves - 1;  // wavefront of the KLD outputs and the fused signal update
+// ---------------------------------------------------------------------------
+// acceptance, outputs and draw weights
+// ---------------------------------------------------------------------------
+
+// Workgroup (x, y) works on sequence x of the pass; y = 0 writes the outputs,
+// y = 1 .. gridDim.y - 1 take a share of the draw's units each.  All of them
+// repeat the acceptance: it takes about 3 us of latency and few instructions,
+// where handing its result to other workgroups would take a kernel boundary.
+// A row dealt to one workgroup per sequence is bound by that CU's VALU (two
+// exponentials per logit pair), 20 us for two bf16 rows of 128,256 logits, and
+// leaves the other CUs idle in small batches.  Measured against the kernel that
+// streamed and drew in one workgroup per sequence: 21.7 -> 6.6 us for one
+// sequence (V = 128,256 bf16), 65.4 -> 14.6 us for 64 in fp32,
+// 29.8 -> 25.8 us for 256 in bf16 (18 us of bytes).
+template <int DT, bool VEC, bool FUSED>
+__global__ __launch_bounds__(kSeqThreads) void seq_kernel(const StepParams P, const SignalArgs S) {
   __shared__ float st_mt[DSDE_MAX_K + 1], st_md[DSDE_MAX_K + 1];
   __shared__ double st_sp[DSDE_MAX_K + 1], st_sq[DSDE_MAX_K + 1], st_a[DSDE_MAX_K + 1], st_h[DSDE_MAX_K + 1];
   __shared__ int st_bad[DSDE_MAX_K + 1], st_arg[DSDE_MAX_K + 1];
   __shared__ uint32_t s_err_in, s_err;  // error bits before and after the row checks
-  __shared__ double ch_w[kMaxChunks], ch_p[kMaxChunks];
-  __shared__ float ch_ref[kMaxChunks];
-  __shared__ int ch_bad[kMaxChunks];
-  __shared__ int32_t ch_arg[kMaxChunks];
-  extern __shared__ float s_sub[];  // 64 row partials of the 16 sub-block totals, per chunk
   __shared__ DrawJob s_job;
   const int t = threadIdx.x, lane = t & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);  // uniform: chunk indices and addresses stay scalar
-  const int32_t b = blockIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);  // uniform: unit indices and addresses stay scalar
+  const int32_t lb = blockIdx.x, b = P.first_seq + lb;
+  const bool outputs = blockIdx.y == 0;
   const int32_t width = P.k_max + 1;
   int32_t *tok = P.tokens + int64_t(b) * width;
   // first round trip: everything whose address depends on the sequence index
@@ -98,9 +99,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == kSeqTh
   if (j0 < P.k_max && g0 < P.nc) arg0 = P.chunk_arg[(slot0 + j0) * P.nc + g0];
   Gathered gz{0.f, 0.f};
   if (wave == 0 && lane < P.k_max) gz = P.gathered[slot0 + lane];
-  uint32_t err = P.seq_err[b];  // the set-up's layout verdict
   const int32_t s = P.sl[b], first = P.cu_sl[b];
   const float T = P.temperature[b], ur = P.u_res[b];
+  // without a set-up kernel the outputs workgroup checks the whole layout, here
+  // beside the first round trip; the streaming ones look only at what keeps
+  // their own reads in bounds (their cells go unused when the layout is invalid)
+  const int fault = P.lookup && outputs ? layout_fault(P.B, P.N, P.k_max, P.sl, P.cu_sl) : 0;
   // one wait for the whole first round trip: every load above is issued
   // before any of the pins below asks for its value
   asm volatile("" ::: "memory");
@@ -113,10 +117,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == kSeqTh
   pin(gz.zd);
   pin(arg0.zmax);
   pin(arg0.idx);
-  if (err & DSDE_ERR_LAYOUT) {
+  const bool own_bad = P.lookup ? s < 0 || s > P.k_max || first < 0 || int64_t(first) + s > P.N
+                                : (P.seq_err[b] & DSDE_ERR_LAYOUT) != 0;
+  if (!outputs && own_bad) return;
+  if (outputs && (P.lookup ? __syncthreads_or(fault) != 0 : own_bad)) {
     if (t < width) tok[t] = P.pad_id;
     if (t == 0) {
+      if (P.lookup) P.seq_err[b] = DSDE_ERR_LAYOUT;
       P.accepted[b] = 0;
+      DrawJob j{};
+      j.kind = -1;
+      P.jobs[lb] = j;
       if constexpr (FUSED) S.mu_last[b] = S.var_short[b] = S.var_long[b] = S.wvir[b] = S.sf[b] = NAN;
     }
     return;
@@ -132,7 +143,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == kSeqTh
     u = P.u_acc[first + lane];
   }
 
-  // ---- 1. acceptance
+  // ---- acceptance
   // row statistics of every drafted pair (read even for a flagged sequence:
   // the layout is valid, so every access stays in bounds)
   if (s > 0) {
@@ -148,6 +159,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == kSeqTh
   }
   __syncthreads();
   if (wave == 0) {
+    uint32_t err = 0;
     {  // per-sequence input checks
       uint32_t e = 0;
       if (lane < s) {
@@ -189,382 +201,208 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == kSeqTh
     if (a > s) a = s;
     if (err) a = 0;
     if (lane == 0) s_err = err;
-    if (lane < width) tok[lane] = lane < a ? x : P.pad_id;
     // the first rejected position's row values, from its lane
     const float a_mt = lanes::readlane(my_mt, a), a_md = lanes::readlane(my_md, a);
     const float a_isp = lanes::readlane(my_isp, a), a_isq = lanes::readlane(my_isq, a);
     const int32_t a_arg = lanes::readlane(my_arg, a);
-    if (lane == 0) {
-      P.accepted[b] = a;
-      DrawJob j{};
-      j.kind = -1;
-      if (!err && greedy) {
-        j.accepted = a;
-        j.target_row = first + b + a;
-        j.draft_row = -1;
-        if (a < s) {  // the argmax of the first rejected row is known already
-          j.kind = 2;
-          j.token = a_arg;
-          tok[a] = a_arg;
-        } else {      // the argmax of the bonus row
-          j.kind = 3;
-        }
-      } else if (!err) {
-        j.accepted = a;
-        j.scale = c;
-        j.u = ur;
-        if (a < s) {
-          j.kind = 0;
-          j.target_row = first + b + a;
-          j.draft_row = first + a;
-          j.mt = a_mt;
-          j.md = a_md;
-          j.inv_sp = a_isp;
-          j.inv_sq = a_isq;
-        } else {
-          j.kind = 1;
-          j.target_row = first + b + s;
-          j.draft_row = -1;
-        }
+    DrawJob j{};
+    j.kind = -1;
+    if (!err && greedy) {
+      j.accepted = a;
+      j.target_row = first + b + a;
+      j.draft_row = -1;
+      if (a < s) {  // the argmax of the first rejected row is known already
+        j.kind = 2;
+        j.token = a_arg;
+      } else {      // the argmax of the bonus row
+        j.kind = 3;
       }
+    } else if (!err) {
+      j.accepted = a;
+      j.scale = c;
+      j.u = ur;
+      if (a < s) {
+        j.kind = 0;
+        j.target_row = first + b + a;
+        j.draft_row = first + a;
+        j.mt = a_mt;
+        j.md = a_md;
+        j.inv_sp = a_isp;
+        j.inv_sq = a_isq;
+      } else {
+        j.kind = 1;
+        j.target_row = first + b + s;
+        j.draft_row = -1;
+      }
+    }
+    if (outputs) {
+      if (lane < width) tok[lane] = lane < a ? x : j.kind == 2 && lane == a ? j.token : P.pad_id;
+      if (lane == 0) {
+        P.accepted[b] = a;
+        P.jobs[lb] = j;
+        if (P.lookup)
+          P.seq_err[b] = err;  // ahead of the barrier below, behind which the signal's bits are OR-ed in
+        else if (err)
+          atomicOr(&P.seq_err[b], err);
+      }
+    } else if (lane == 0) {
       s_job = j;
     }
   }
   __syncthreads();
-  const DrawJob job = uniform_job(s_job);
 
-  // ---- 2. draw-weight totals of every chunk
-  const size_t esz = DT == DSDE_BF16 ? 2 : 4;
-  const int32_t nc = P.nc;
-  if (job.kind == 3) {
-    const char *trow = (const char *)P.target + size_t(job.target_row) * size_t(P.V) * esz;
-    for (int32_t ch = wave; ch < nc; ch += kSeqWaves) {
-      float zmax;
-      int32_t idx;
-      int bad;
-      bonus_argmax_chunk<DT, VEC>(trow, P.V, ch, &zmax, &idx, &bad);
-      if (lane == 0) {
-        ch_ref[ch] = zmax;
-        ch_arg[ch] = idx;
-        ch_bad[ch] = bad;
-      }
-    }
-    __syncthreads();
-  } else if (job.kind == 0 || job.kind == 1) {
-    const char *trow = (const char *)P.target + size_t(job.target_row) * size_t(P.V) * esz;
-    if (job.kind == 0) {
-      const char *drow = (const char *)P.draft + size_t(job.draft_row) * size_t(P.V) * esz;
-      for (int32_t ch = wave; ch < nc; ch += kSeqWaves) {
-        const double w = residual_chunk<DT, VEC>(trow, drow, P.V, ch, job, s_sub + int64_t(ch) * 64);
-        if (lane == 0) ch_w[ch] = w;
-      }
-    } else {
-      for (int32_t ch = wave; ch < nc; ch += kSeqWaves) {
-        double w;
-        float ref;
-        int bad;
-        bonus_chunk<DT, VEC>(trow, P.V, ch, job.scale, &w, &ref, &bad, s_sub + int64_t(ch) * 64);
-        if (lane == 0) {
-          ch_w[ch] = w;
-          ch_ref[ch] = ref;
-          ch_bad[ch] = bad;
-        }
-      }
-    }
-    __syncthreads();
-    if (job.kind == 0) {
-      // the residual's total mass, evaluated identically by every wavefront;
-      // without mass the draw falls back to p, whose chunk totals come next
-      double part = 0.0;
-      for (int32_t ch = lane; ch < nc; ch += 64) part += ch_w[ch];
-      if (!(wave_sum_f64(part) > 0.0)) {
-        for (int32_t ch = wave; ch < nc; ch += kSeqWaves) {
-          const double p = target_p_chunk<DT, VEC>(trow, P.V, ch, job, s_sub + int64_t(ch) * 64);
-          if (lane == 0) ch_p[ch] = p;
-        }
-        __syncthreads();
-      }
-    }
-  }
-
-  if (wave == kSignalWave) {
-    // the KLD of every drafted position (lane j: position j), its draft
-    // entropy and row log-normalisers, and in the fused step the signal update
-    // of Sec. 3.1.2 on those KLD values: on the last wavefront after the last
-    // barrier, beside wavefront 0's chunk search and final scan, so that none
-    // of it delays the draw (the draw stream is VALU-bound: work added to any
-    // wavefront before the barrier lengthens it)
-    // the ring state, fetched here: its round trip overlaps the KLD arithmetic
-    RingPrefetch rp{};
-    if constexpr (FUSED) rp = wave_ring_prefetch(S.hist + int64_t(b) * S.W, S.head + b, S.count + b, S.W);
-    const uint32_t e_in = s_err_in, e_all = s_err;
-    float my_kld = NAN, my_h = NAN;
-    if (lane < s && !e_in) {
-      const double sp = st_sp[lane], sq = st_sq[lane];
-      const double l2sp = log2_rowsum(sp), l2sq = log2_rowsum(sq);
-      // KL in log2 units: E_p[(z_t c - mt) - (z_d c - md)] - log2 S_p + log2 S_q
-      const double kl = (st_a[lane] * rcp_newton(sp) - l2sp + l2sq) * kLn2;
-      // draft entropy in log2 units: log2 S_q - E_q[z_d c - md]
-      const double h = (l2sq - st_h[lane] * rcp_newton(sq)) * kLn2;
-      if (!e_all) {
-        my_kld = kl > 0.0 ? float(kl) : 0.0f;
-        my_h = float(h);
-      }
-      if (!st_bad[lane] && P.row_lse) {
-        P.row_lse[2 * (first + lane)] = (double(st_mt[lane]) + l2sp) * kLn2;
-        P.row_lse[2 * (first + lane) + 1] = (double(st_md[lane]) + l2sq) * kLn2;
-      }
-    }
-    if (lane < s) P.kld[first + lane] = my_kld;
-    if (lane < s && P.entropy) P.entropy[first + lane] = my_h;
-    if constexpr (FUSED) {
-      const uint32_t e = wave_signal_update(s, first, nullptr, my_kld, rp, S.hist + int64_t(b) * S.W, S.head + b,
-                                            S.count + b, S.W, S.n_short, S.n_long, S.delta, S.eps, S.mu_last + b,
-                                            S.var_short + b, S.var_long + b, S.wvir + b, S.sf + b);
-      if (e && lane == 0) atomicOr(&P.seq_err[b], e);
-    }
-  }
-
-  if (job.kind < 0 || job.kind == 2) {  // flagged, or a greedy token already emitted
-    if (err && wave == 0 && lane == 0) atomicOr(&P.seq_err[b], err);
+  if (!outputs) {
+    // ---- this workgroup's share of the draw's units
+    const DrawJob job = uniform_job(s_job);
+    const UnitCells cells{P.sub + int64_t(lb) * P.nu * kSubs, P.ref + int64_t(lb) * P.nu};
+    const int32_t gw = (int32_t(blockIdx.y) - 1) * kSeqWaves + wave;
+    draw_units<DT, VEC>(job, (const char *)P.target, (const char *)P.draft, P.V, P.nu, gw,
+                        (int32_t(gridDim.y) - 1) * kSeqWaves, cells);
     return;
   }
-  if (job.kind == 3) {
-    // greedy bonus: the chunk holding the row maximum (the earliest on ties)
-    if (wave == 0) {
-      float best = -INFINITY;
-      int32_t bch = 0x7fffffff;
-      int bad = 0;
-      for (int32_t ch = lane; ch < nc; ch += 64) {
-        bad |= ch_bad[ch];
-        if (bch == 0x7fffffff || ch_ref[ch] > best) {
-          best = ch_ref[ch];
-          bch = ch;
-        }
-      }
-      bad = lanes::wave_or(bad);
-      const float M = wave_max(best);
-      int32_t cand = bch != 0x7fffffff && best == M ? bch : 0x7fffffff;
-      cand = lanes::wave_min(cand);
-      if (bad) {
-        // a NaN or infinite logit in the bonus row: no token is emitted
-        if (lane < width) tok[lane] = P.pad_id;
-        if (lane == 0) {
-          P.accepted[b] = 0;
-          atomicOr(&P.seq_err[b], DSDE_ERR_LOGIT);
-        }
-      } else if (lane == 0) {
-        tok[job.accepted] = ch_arg[cand];
-      }
+  if (wave != kSignalWave) return;
+  // ---- the KLD of every drafted position (lane j: position j), its draft
+  // entropy and row log-normalisers, and in the fused step the signal update
+  // of Sec. 3.1.2 on those KLD values
+  // the ring state, fetched here: its round trip overlaps the KLD arithmetic
+  RingPrefetch rp{};
+  if constexpr (FUSED) rp = wave_ring_prefetch(S.hist + int64_t(b) * S.W, S.head + b, S.count + b, S.W);
+  const uint32_t e_in = s_err_in, e_all = s_err;
+  float my_kld = NAN, my_h = NAN;
+  if (lane < s && !e_in) {
+    const double sp = st_sp[lane], sq = st_sq[lane];
+    const double l2sp = log2_rowsum(sp), l2sq = log2_rowsum(sq);
+    // KL in log2 units: E_p[(z_t c - mt) - (z_d c - md)] - log2 S_p + log2 S_q
+    const double kl = (st_a[lane] * rcp_newton(sp) - l2sp + l2sq) * kLn2;
+    // draft entropy in log2 units: log2 S_q - E_q[z_d c - md]
+    const double h = (l2sq - st_h[lane] * rcp_newton(sq)) * kLn2;
+    if (!e_all) {
+      my_kld = kl > 0.0 ? float(kl) : 0.0f;
+      my_h = float(h);
     }
+    if (!st_bad[lane] && P.row_lse) {
+      P.row_lse[2 * (first + lane)] = (double(st_mt[lane]) + l2sp) * kLn2;
+      P.row_lse[2 * (first + lane) + 1] = (double(st_md[lane]) + l2sq) * kLn2;
+    }
+  }
+  if (lane < s) P.kld[first + lane] = my_kld;
+  if (lane < s && P.entropy) P.entropy[first + lane] = my_h;
+  if constexpr (FUSED) {
+    const uint32_t e = wave_signal_update(s, first, nullptr, my_kld, rp, S.hist + int64_t(b) * S.W, S.head + b,
+                                          S.count + b, S.W, S.n_short, S.n_long, S.delta, S.eps, S.mu_last + b,
+                                          S.var_short + b, S.var_long + b, S.wvir + b, S.sf + b);
+    if (e && lane == 0) atomicOr(&P.seq_err[b], e);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// the drawn token
+// ---------------------------------------------------------------------------
+
+// One workgroup per sequence of the pass; with `rule` set, workgroup gridDim.x
+// - 1 is the SL rule's (the same workgroup size as next_sl_kernel, so the same
+// order of its sums).  A sequence's draw needs one wavefront; the others are
+// there for a residual without mass, whose fallback to p has to read the
+// target row again.
+template <int DT, bool VEC>
+__global__ __launch_bounds__(kCapThreads) void pick_kernel(const StepParams P, const SignalArgs S, bool rule) {
+  if (rule && blockIdx.x == gridDim.x - 1) {
+    __shared__ double red_s[kCapThreads / 64];
+    __shared__ int red_n[kCapThreads / 64];
+    block_next_sl(P.B, S.sf, S.wvir, S.sl_max, S.sl_min, S.sl_hi, S.budget, S.sl_hat, S.sl_cap, S.sl_next, P.seq_err,
+                  true, red_s, red_n);
     return;
   }
-
-  if (wave != 0) return;
-
-  // ---- 3. wavefront 0: the chunk holding u' * Z (lanes over chunks,
-  // fixed-order fp64), the sub-block inside it, and the token inside that
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int32_t lb = blockIdx.x, b = P.first_seq + lb;
+  const UnitCells cells{P.sub + int64_t(lb) * P.nu * kSubs, P.ref + int64_t(lb) * P.nu};
+  // one round trip: the job and the first 64 units' cells (whatever they hold
+  // when the job does not use them)
+  UnitCell cell0 = load_cell(cells, lane, P.nu, true);
+  const DrawJob job = uniform_job(P.jobs[lb]);
+  if (job.kind < 0 || job.kind == 2) return;  // flagged, or a greedy token already emitted
+  const int32_t width = P.k_max + 1;
+  int32_t *tok = P.tokens + int64_t(b) * width;
   int mode = job.kind == 0 ? 0 : 2;  // 0: residual weights, 1: p of the rejected pair, 2: bonus exponentials
-  float ref_max = -INFINITY;
-  if (mode == 2) {
-    int bad = 0;
-    for (int32_t ch = lane; ch < nc; ch += 64) {
-      bad |= ch_bad[ch];
-      ref_max = fmaxf(ref_max, ch_ref[ch]);
-    }
-    ref_max = wave_max(ref_max);
-    if (lanes::wave_or(bad)) {
+  float row_ref = 0.f;
+  if (job.kind != 0) {
+    bool bad;
+    row_ref = row_reference(cells, P.nu, cell0, &bad);
+    if (wave != 0) return;
+    if (bad) {
       // a NaN or infinite logit in the bonus row: no token is emitted
       if (lane < width) tok[lane] = P.pad_id;
       if (lane == 0) {
         P.accepted[b] = 0;
-        atomicOr(&P.seq_err[b], err | DSDE_ERR_LOGIT);
+        atomicOr(&P.seq_err[b], DSDE_ERR_LOGIT);
       }
       return;
     }
-  }
-  auto weight = [&](int32_t ch, int m) -> double {
-    return m == 0 ? ch_w[ch] : m == 1 ? ch_p[ch] : ch_w[ch] * exp2_taylor(double(ch_ref[ch]) - double(ref_max));
-  };
-  double part = 0.0;
-  for (int32_t ch = lane; ch < nc; ch += 64) part += weight(ch, mode);
-  double Z = wave_sum_f64(part);
-  if (mode == 0 && !(Z > 0.0)) {  // no residual mass: p of the same target row
-    mode = 1;
-    part = 0.0;
-    for (int32_t ch = lane; ch < nc; ch += 64) part += weight(ch, 1);
-    Z = wave_sum_f64(part);
-  }
-  const double target_mass = double(job.u) * Z;
-  // inclusive scan 64 chunks at a time; the chunk holding the target is the
-  // last one with positive weight whose exclusive prefix is <= the target
-  // (prefixes tile exactly: each chunk's start is the previous chunk's end),
-  // which also covers rounding past the total
-  int32_t best = -1;
-  double best_excl = 0.0, base = 0.0;
-  for (int32_t c0 = 0; c0 < nc; c0 += 64) {
-    const int32_t ch = c0 + lane;
-    const double w = ch < nc ? weight(ch, mode) : 0.0;
-    const lanes::Scan<double> sc = lanes::wave_scan(w);
-    const double incl = base + sc.incl;
-    const double excl = lane == 0 ? base : base + sc.excl;
-    const uint64_t cand = __ballot(ch < nc && w > 0.0 && excl <= target_mass);
-    if (cand) {
-      const int l = 63 - __builtin_clzll(cand);
-      best = c0 + l;
-      best_excl = lanes::readlane(excl, l);
+    if (job.kind == 3) {
+      const int32_t token = row_argmax(cells, P.nu, cell0, row_ref);
+      if (lane == 0) tok[job.accepted] = token;
+      return;
     }
-    base = lanes::readlane(incl, 63);
   }
-  const int32_t chunk = best >= 0 ? best : 0;
-  double rem = target_mass - best_excl;
-  if (rem < 0.0) rem = 0.0;
-  const float ref = mode == 2 ? ch_ref[chunk] : 0.f;
-  if (mode == 2) rem *= exp2_taylor(double(ref_max) - double(ref));  // into the chunk's own scale
-
-  // the sub-block: the same rule over the chunk's 16 sub-block totals
-  double sbw = 0.0;
-  if (lane < kSubs) {
-    const float *r = s_sub + int64_t(chunk) * 64;
-    sbw = double(((r[lane] + r[16 + lane]) + r[32 + lane]) + r[48 + lane]);
-  }
-  const lanes::Scan<double> ss = lanes::wave_scan(sbw);
-  const uint64_t scand = __ballot(lane < kSubs && sbw > 0.0 && ss.excl <= rem);
-  const int sb = scand ? 63 - __builtin_clzll(scand) : 0;
-  double rem2 = rem - lanes::readlane(ss.excl, sb);
-  if (rem2 < 0.0) rem2 = 0.0;
-
-  // ---- 4. the 512 logits of that sub-block, 8 consecutive per lane, with the
-  // weights evaluated by the routines of the totals; the lane holding the
-  // target walks its own eight
-  const int64_t run0 = int64_t(chunk) * kChunk + int64_t(sb) * kSubLen + 8 * lane;
+  const size_t esz = DT == DSDE_BF16 ? 2 : 4;
   const char *trow = (const char *)P.target + size_t(job.target_row) * size_t(P.V) * esz;
-  float w[8];
-  {
-    float zt[8];
-    load_run<DT, VEC, 8>(trow, P.V, run0, zt);
-    if (mode == 0) {
-      float zd[8];
-      const char *drow = (const char *)P.draft + size_t(job.draft_row) * size_t(P.V) * esz;
-      load_run<DT, VEC, 8>(drow, P.V, run0, zd);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) w[i] = residual_weight(zt[i], zd[i], job);
-    } else if (mode == 1) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) w[i] = target_p_weight(zt[i], job);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) w[i] = bonus_weight(zt[i], job.scale, ref);
-    }
+  const char *drow =
+      job.kind == 0 ? (const char *)P.draft + size_t(job.draft_row) * size_t(P.V) * esz : nullptr;
+  double Z = row_total(cells, P.nu, cell0, mode, row_ref);
+  if (mode == 0 && !(Z > 0.0)) {  // no residual mass (the same in every wavefront): p of the same target row
+    mode = 1;
+    __syncthreads();  // every wavefront has read the residual's cells, which p's now replace
+    for (int32_t u = wave; u < P.nu; u += kCapThreads / 64) target_p_unit<DT, VEC>(trow, P.V, u, job, cells);
+    __syncthreads();
+    cell0 = load_cell(cells, lane, P.nu, false);
+    Z = row_total(cells, P.nu, cell0, mode, row_ref);
   }
-  double run_total = 0.0;
-  int last = -1;  // this lane's last positive weight
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    run_total += double(w[i]);
-    if (w[i] > 0.0f) last = i;
-  }
-  const lanes::Scan<double> sr = lanes::wave_scan(run_total);
-  // the last lane with positive weight whose exclusive prefix is <= the target
-  // (rounding past the sub-block's total lands on its last positive weight)
-  const uint64_t cand = __ballot(last >= 0 && sr.excl <= rem2);
-  const int winner = cand ? 63 - __builtin_clzll(cand) : 0;
-  if (lane == winner) {
-    int pick = last >= 0 ? last : 0;
-    double acc = sr.excl;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      acc += double(w[i]);
-      if (acc > rem2) {
-        pick = i;
-        break;
-      }
-    }
-    tok[job.accepted] = int32_t(run0 + pick);
-    if (err) atomicOr(&P.seq_err[b], err);
-  }
+  if (wave != 0) return;
+  const int32_t token =
+      draw_in_row<DT, VEC>(cells, P.nu, cell0, row_ref, double(job.u) * Z, trow, drow, P.V, mode, job);
+  if (lane == 0) tok[job.accepted] = token;
 }
 
 }  // namespace
 
-// Largest dynamic LDS a launch of `kernel` may ask for: the CU's LDS less the
-// kernel's static LDS (0 when the runtime does not tell).  Set up once per
-// kernel.
-template <typename K>
-static size_t dynamic_lds_limit(K kernel) {
-  int dev = 0, lds = 0;
-  hipFuncAttributes attr{};
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) != hipSuccess ||
-      hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(kernel)) != hipSuccess || lds <= 0 ||
-      size_t(lds) <= attr.sharedSizeBytes) {
-    (void)hipGetLastError();
-    return 0;
-  }
-  const size_t bytes = size_t(lds) - attr.sharedSizeBytes;
-  if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                          int(bytes)) != hipSuccess) {
-    (void)hipGetLastError();
-    return 0;
-  }
-  return bytes;
-}
-
-template <typename K>
-static int launch_one_seq(K kernel, size_t limit, size_t need, size_t spread, int B, int threads,
-                          const StepParams &P, const SignalArgs &S, hipStream_t stream) {
-  if (need > limit) return DSDE_DEVICE_ERROR;  // cannot happen within the vocabulary limit
-  const size_t dyn = spread > need && spread <= limit ? spread : need;
-  kernel<<<dim3(unsigned(B)), dim3(unsigned(threads)), dyn, stream>>>(P, S);
-  return DSDE_OK;
+// Streaming workgroups per sequence: about kStreamWorkgroups in all (four of
+// these workgroups fill a CU's registers), but no wavefront without a unit.
+constexpr int32_t kStreamWorkgroups = 1024;
+static int32_t stream_parts(int32_t seqs, int32_t nu) {
+  const int32_t most = (nu + kSeqWaves - 1) / kSeqWaves;
+  const int32_t want = (kStreamWorkgroups + seqs - 1) / seqs;
+  return want < most ? want : most;
 }
 
 template <int DT, bool VEC>
-static int launch_seq(const VerifyArgs &a, const StepParams &P, const SignalArgs &S) {
-  // Dynamic LDS: the sub-block partials, 256 bytes per chunk.  With no more
-  // sequences than CUs: 512 threads per sequence, one sequence per CU.  Two
-  // such workgroups would fit on one CU, and the dispatcher could pair them
-  // up on half of the CUs, each pair then sharing one CU's load bandwidth;
-  // asking for more than half of the CU's LDS per workgroup places one
-  // sequence per CU.  With more sequences: 256 threads per sequence and only
-  // the LDS needed, so that several share a CU.
-  static const size_t lim_wide_fused = dynamic_lds_limit(seq_kernel<DT, VEC, true, kSeqThreadsWide>);
-  static const size_t lim_wide_plain = dynamic_lds_limit(seq_kernel<DT, VEC, false, kSeqThreadsWide>);
-  static const size_t lim_narrow_fused = dynamic_lds_limit(seq_kernel<DT, VEC, true, kSeqThreadsNarrow>);
-  static const size_t lim_narrow_plain = dynamic_lds_limit(seq_kernel<DT, VEC, false, kSeqThreadsNarrow>);
-  int dev = 0, ncu = 0, lds = 0;
-  const bool known = hipGetDevice(&dev) == hipSuccess &&
-                     hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-                     hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) ==
-                         hipSuccess;
-  (void)hipGetLastError();
-  const bool few = known && a.B <= ncu;
-  const size_t need = size_t(P.nc) * 64 * sizeof(float);
-  const size_t spread = known ? size_t(lds) / 2 + 1 : 0;
-  if (few) {
+static void launch_draw(const VerifyArgs &a, StepParams P, const SignalArgs &S) {
+  const int32_t per_pass = draw_seqs_per_pass(a.B, a.V);
+  for (int32_t b0 = 0; b0 < a.B; b0 += per_pass) {
+    const int32_t seqs = a.B - b0 < per_pass ? a.B - b0 : per_pass;
+    const bool last = b0 + seqs == a.B;
+    P.first_seq = b0;
+    const dim3 grid(unsigned(seqs), unsigned(1 + stream_parts(seqs, P.nu)));
     if (a.signal)
-      return launch_one_seq(seq_kernel<DT, VEC, true, kSeqThreadsWide>, lim_wide_fused, need, spread, a.B,
-                            kSeqThreadsWide, P, S, a.stream);
-    return launch_one_seq(seq_kernel<DT, VEC, false, kSeqThreadsWide>, lim_wide_plain, need, spread, a.B,
-                          kSeqThreadsWide, P, S, a.stream);
+      seq_kernel<DT, VEC, true><<<grid, dim3(kSeqThreads), 0, a.stream>>>(P, S);
+    else
+      seq_kernel<DT, VEC, false><<<grid, dim3(kSeqThreads), 0, a.stream>>>(P, S);
+    // the SL rule needs every sequence's signal: behind the last pass
+    const bool rule = a.signal && last;
+    pick_kernel<DT, VEC><<<dim3(unsigned(seqs + rule)), dim3(kCapThreads), 0, a.stream>>>(P, S, rule);
   }
-  if (a.signal)
-    return launch_one_seq(seq_kernel<DT, VEC, true, kSeqThreadsNarrow>, lim_narrow_fused, need, 0, a.B,
-                          kSeqThreadsNarrow, P, S, a.stream);
-  return launch_one_seq(seq_kernel<DT, VEC, false, kSeqThreadsNarrow>, lim_narrow_plain, need, 0, a.B,
-                        kSeqThreadsNarrow, P, S, a.stream);
 }
 
 int launch_verify(const VerifyArgs &a) {
   const WorkspaceLayout L = workspace_layout(a.B, a.N, a.V, a.k_max);
-  const int32_t nc = int32_t(num_chunks(a.V));
   char *ws = (char *)a.workspace;
   WorkItem *work = (WorkItem *)(ws + L.work);
   PairChunk *part = (PairChunk *)(ws + L.pair_chunk);
   Gathered *gath = (Gathered *)(ws + L.gathered);
   (void)hipGetLastError();
   ChunkArg *cargs = (ChunkArg *)(ws + L.chunk_arg);
-  launch_stats_pass(a, work, part, gath, cargs, a.draft_entropy != nullptr);
+  const bool lookup = stats_lookup(a);
+  launch_stats_pass(a, lookup, work, part, gath, cargs, a.draft_entropy != nullptr);
   const bool vec = rows_vectorizable(a);
   StepParams P;
   P.target = a.target;
@@ -572,8 +410,12 @@ int launch_verify(const VerifyArgs &a) {
   P.V = a.V;
   P.B = a.B;
   P.k_max = a.k_max;
-  P.nc = nc;
+  P.nc = int32_t(num_chunks(a.V));
+  P.nu = int32_t(num_units(a.V));
   P.pad_id = a.pad_id;
+  P.lookup = lookup;
+  P.N = a.N;
+  P.first_seq = 0;
   P.sl = a.sl;
   P.cu_sl = a.cu_sl;
   P.draft_tokens = a.draft_tokens;
@@ -589,17 +431,15 @@ int launch_verify(const VerifyArgs &a) {
   P.part = part;
   P.gathered = gath;
   P.chunk_arg = cargs;
+  P.jobs = (DrawJob *)(ws + L.jobs);
+  P.sub = (float *)(ws + L.sub);
+  P.ref = (UnitRef *)(ws + L.ref);
   const SignalArgs S = a.signal ? *a.signal : SignalArgs{};
-  int st;
   if (a.dtype == DSDE_BF16)
-    st = vec ? launch_seq<DSDE_BF16, true>(a, P, S) : launch_seq<DSDE_BF16, false>(a, P, S);
+    vec ? launch_draw<DSDE_BF16, true>(a, P, S) : launch_draw<DSDE_BF16, false>(a, P, S);
   else
-    st = vec ? launch_seq<DSDE_FP32, true>(a, P, S) : launch_seq<DSDE_FP32, false>(a, P, S);
-  if (st != DSDE_OK || hipGetLastError() != hipSuccess) return DSDE_DEVICE_ERROR;
-  if (a.signal)
-    return launch_next_sl(a.B, S.sf, S.wvir, S.sl_max, S.sl_min, S.sl_hi, S.budget, S.sl_hat, S.sl_cap, S.sl_next,
-                          a.seq_err, true, a.stream);
-  return DSDE_OK;
+    vec ? launch_draw<DSDE_FP32, true>(a, P, S) : launch_draw<DSDE_FP32, false>(a, P, S);
+  return hipGetLastError() == hipSuccess ? DSDE_OK : DSDE_DEVICE_ERROR;
 }
 
 }  // namespace dsde

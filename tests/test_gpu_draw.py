@@ -1,0 +1,73 @@
+"""GPU parity of the draw where its division of the work changes: rows that end
+at, before and after a unit of 2048 logits and a sub-block of 512, one logit
+row per workgroup and several, more than 64 units (two rounds of the unit
+search), and batches drawn in more than one pass over the workspace's cells.
+The oracle and the tie rules are those of the other parity tests."""
+import numpy as np
+import pytest
+import torch
+
+from tests.test_gpu_verify import check_step, random_arrays, step_from_arrays
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("V", [504, 512, 2040, 2047, 2048, 2049, 2056, 4608, 131072, 131080, 133121])
+@pytest.mark.parametrize("B", [1, 5])
+def test_draw_unit_edges(gpu_lib, V, dtype, B):
+    rng = np.random.default_rng(V + B)
+    sls = [2, 0, 3, 1, 1][:B]
+    target, draft, tokens, u_acc, u_res = random_arrays(rng, sls, V, sigma=1.0, noise=0.5)
+    u_res = np.array([0.999999, 0.0, 0.9, 0.5, 0.05], np.float32)[:B]
+    temps = [1.0, 0.7, 0.0, 1.3, 1.0][:B]
+    step = step_from_arrays(target, draft, sls, tokens, temps, u_acc, u_res, 3, dtype)
+    check_step(gpu_lib, step, f"draw units V={V} B={B} {dtype}")
+
+
+def test_draw_in_two_passes(gpu_lib):
+    """More sequences than one pass of the draw kernels holds (32,768): the
+    second pass reuses the cells of the first."""
+    rng = np.random.default_rng(5)
+    B, V = 32768 + 77, 24
+    sls = rng.integers(0, 3, B).tolist()
+    target, draft, tokens, u_acc, u_res = random_arrays(rng, sls, V, noise=0.8)
+    temps = rng.choice([0.0, 0.7, 1.0], B).tolist()
+    step = step_from_arrays(target, draft, sls, tokens, temps, u_acc, u_res, 2)
+    _, _, rep = check_step(gpu_lib, step, f"two passes B={B} V={V}")
+    assert rep["compared"] >= 0.9 * B
+    # the fused step takes its SL rule from the last pass: same bits as the separate calls
+    dev = "cuda"
+    ring = [(torch.zeros(B, 8, device=dev), torch.zeros(B, dtype=torch.int32, device=dev),
+             torch.zeros(B, dtype=torch.int32, device=dev)) for _ in range(2)]
+    smax = torch.full((B,), 8.0, device=dev)
+    args = (step.target, step.draft, step.sl, step.cu_sl, step.draft_tokens, step.temperature, step.u_acc, step.u_res,
+            step.k_max)
+    got = gpu_lib.step(*args, *ring[0], smax)
+    ver = gpu_lib.verify(*args)
+    sig = gpu_lib.kld_signal(step.sl, step.cu_sl, ver["kld"], *ring[1])
+    rule = gpu_lib.next_sl(sig["sf"], sig["wvir"], smax, 2.0, step.k_max)
+    for k in ("accepted", "tokens"):
+        assert torch.equal(got[k], ver[k]), k
+    for k in ("sl_hat", "sl_cap"):
+        assert torch.equal(got[k].view(torch.int32), rule[k].view(torch.int32)), k
+    assert torch.equal(got["sl_next"], rule["sl_next"])
+
+
+@pytest.mark.parametrize("B,k_max,V", [(64, 8, 8192), (1024, 4, 9000), (1024, 5, 8192), (1025, 1, 512)])
+def test_statistics_with_and_without_the_setup_kernel(gpu_lib, B, k_max, V):
+    """Batches on both sides of the rule that drops the set-up kernel (at most
+    4,096 workgroups past the sequences' ends, at most 1,024 sequences), and a
+    broken layout on each, which flags every sequence."""
+    rng = np.random.default_rng(B + k_max)
+    sls = rng.integers(0, k_max + 1, B).tolist()
+    target, draft, tokens, u_acc, u_res = random_arrays(rng, sls, V, sigma=1.0, noise=0.5)
+    temps = rng.choice([0.0, 0.7, 1.0], B).tolist()
+    step = step_from_arrays(target, draft, sls, tokens, temps, u_acc, u_res, k_max)
+    _, _, rep = check_step(gpu_lib, step, f"set-up rule B={B} k_max={k_max} V={V}")
+    assert rep["compared"] >= 0.9 * B
+    step.cu_sl[B // 2] += 1
+    got = gpu_lib.verify(step.target, step.draft, step.sl, step.cu_sl, step.draft_tokens, step.temperature,
+                         step.u_acc, step.u_res, k_max)
+    torch.cuda.synchronize()
+    assert (got["seq_err"] == 1).all() and (got["accepted"] == 0).all() and (got["tokens"] == -1).all()
