@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "dsde.h"
 
 namespace dsde {
@@ -197,8 +199,32 @@ __device__ __forceinline__ int layout_fault(int32_t B, int64_t N, int32_t k_max,
   return bad;
 }
 
-// Rows are 16-byte aligned and V a multiple of the vector width.
-bool rows_vectorizable(const VerifyArgs &a);
+
+// How the kernels read a call's rows (row_io.hpp): 2 when both arrays are
+// 16-byte aligned and V a whole number of 16-byte loads, 1 when V holds at
+// least one such load, else 0.
+inline int rows_form(const void *target, const void *draft, int32_t dtype, int64_t V, int64_t N) {
+  const int64_t per_load = dtype == DSDE_BF16 ? 8 : 4;
+  const uintptr_t low = reinterpret_cast<uintptr_t>(target) | (N > 0 ? reinterpret_cast<uintptr_t>(draft) : 0);
+  if ((low & 15u) == 0 && V % per_load == 0) return 2;
+  return V >= per_load ? 1 : 0;
+}
+// Calls f with the logit type and the row form as integral constants.
+template <typename F>
+void by_rows(int32_t dtype, int form, F f) {
+  auto with = [&](auto dt) {
+    if (form == 2)
+      f(dt, std::integral_constant<int, 2>{});
+    else if (form == 1)
+      f(dt, std::integral_constant<int, 1>{});
+    else
+      f(dt, std::integral_constant<int, 0>{});
+  };
+  if (dtype == DSDE_BF16)
+    with(std::integral_constant<int, DSDE_BF16>{});
+  else
+    with(std::integral_constant<int, DSDE_FP32>{});
+}
 int launch_kld_signal(int32_t B, int64_t N, const int32_t *sl, const int32_t *cu_sl, const float *kld,
                       float *hist, int32_t *head, int32_t *count, int32_t W, int32_t n_short, int32_t n_long,
                       float delta, float eps, float *mu_last, float *var_short, float *var_long, float *wvir,

@@ -198,77 +198,67 @@ __device__ inline void combine_pairs(const PairChunk *__restrict__ part, int64_t
 // layout need a barrier or four times the logits per wavefront), so the units
 // of one row can be dealt to any number of workgroups.  Lane l owns slots
 // i = 0..31 of its unit:
-//   bf16, 16-byte rows : logit 2048 u + 512 (i / 8) + 8 l + i % 8   (4 x uint4)
-//   fp32, 16-byte rows : logit 2048 u + 256 (i / 4) + 4 l + i % 4   (8 x float4)
-//   any other row      : as bf16, 32 scalar loads
+//   bf16 rows        : logit 2048 u + 512 (i / 8) + 8 l + i % 8   (4 loads of 16 bytes)
+//   fp32 rows        : logit 2048 u + 256 (i / 4) + 4 l + i % 4   (8 loads of 16 bytes)
+//   rows below 16 B  : as bf16, 32 scalar loads
 // Every wavefront load is contiguous, and slots 8 g .. 8 g + 7 lie in
 // sub-block g in every layout.
 constexpr int kUnitElts = kUnit / 64;
 constexpr int kSubs = 4;
 constexpr int kSubLen = kUnit / kSubs;
 
-template <int DT, bool VEC>
+template <int DT, int ROW>
 __device__ __forceinline__ int64_t unit_token(int64_t unit, int i, int lane) {
-  if constexpr (VEC && DT == DSDE_FP32) return unit * kUnit + (i / 4) * 256 + 4 * lane + (i % 4);
+  if constexpr (ROW != kScalarRows && DT == DSDE_FP32) return unit * kUnit + (i / 4) * 256 + 4 * lane + (i % 4);
   return unit * kUnit + (i / 8) * 512 + 8 * lane + (i % 8);
 }
 
-// One row's logits of a unit.  issue() loads them (indices clamped into the
-// row, so no load branches), pad() replaces what lies past V; callers that
-// read two rows issue both before they pad either.
-template <int DT, bool VEC>
+// One row's logits of a unit.  issue() loads them from inside the row, so no
+// load branches; place() puts the last load's logits in their places and pads
+// past V.  Callers that read two rows issue both before they place either.
+template <int DT, int ROW>
 struct UnitRow {
-  float z[kUnitElts];
-  __device__ __forceinline__ void issue(const char *row, int64_t V, int64_t unit, int lane) {
+  static constexpr bool kScalar = ROW == kScalarRows;
+  static constexpr bool kBf16 = DT == DSDE_BF16;
+  float z[kScalar ? kUnitElts : 1];
+  u32x4_t h[!kScalar && kBf16 ? 4 : 1];
+  f32x4_t f[!kScalar && !kBf16 ? 8 : 1];
+  __device__ __forceinline__ void issue(const char *row, int64_t V, int32_t unit, int lane) {
+    if constexpr (kScalar) {
 #pragma unroll
-    for (int i = 0; i < kUnitElts; ++i) {
-      const int64_t v = unit_token<DT, VEC>(unit, i, lane);
-      z[i] = load_logit(row, DT, v < V ? v : V - 1);
+      for (int i = 0; i < kUnitElts; ++i) {
+        const int64_t v = unit_token<DT, ROW>(unit, i, lane);
+        z[i] = load_logit(row, DT, v < V ? v : V - 1);
+      }
+    } else if constexpr (kBf16) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) h[g] = load_words<ROW>(row, uint32_t(V), uint32_t(unit) * 256u + 64u * g + lane);
+    } else {
+#pragma unroll
+      for (int g = 0; g < 8; ++g) f[g] = load_quad<ROW>(row, uint32_t(V), uint32_t(unit) * 512u + 64u * g + lane);
     }
   }
-  __device__ __forceinline__ void pad(int64_t V, int64_t unit, int lane) {
+  __device__ __forceinline__ void place(int64_t V, int32_t unit, int lane) {
+    if constexpr (kScalar) {
 #pragma unroll
-    for (int i = 0; i < kUnitElts; ++i)
-      if (unit_token<DT, VEC>(unit, i, lane) >= V) z[i] = kPadF32;
-  }
-  __device__ __forceinline__ float at(int i) const { return z[i]; }
-};
-template <>
-struct UnitRow<DSDE_BF16, true> {
-  u32x4_t v[4];
-  __device__ __forceinline__ void issue(const char *row, int64_t V, int64_t unit, int lane) {
-    const u32x4_t *p = (const u32x4_t *)row;
-    const uint32_t last = uint32_t(V / 8 - 1), i0 = uint32_t(unit) * 256u + uint32_t(lane);
+      for (int i = 0; i < kUnitElts; ++i)
+        if (unit_token<DT, ROW>(unit, i, lane) >= V) z[i] = kPadF32;
+    } else if constexpr (kBf16) {
 #pragma unroll
-    for (int g = 0; g < 4; ++g) v[g] = __builtin_nontemporal_load(p + min(i0 + 64u * g, last));
-  }
-  __device__ __forceinline__ void pad(int64_t V, int64_t unit, int lane) {
-    const uint32_t last = uint32_t(V / 8 - 1), i0 = uint32_t(unit) * 256u + uint32_t(lane);
+      for (int g = 0; g < 4; ++g) place_words<ROW>(h[g], uint32_t(V), uint32_t(unit) * 256u + 64u * g + lane);
+    } else {
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
-      if (i0 + 64u * g > last) v[g] = u32x4_t{kPadBf16x2, kPadBf16x2, kPadBf16x2, kPadBf16x2};
+      for (int g = 0; g < 8; ++g) place_quad<ROW>(f[g], uint32_t(V), uint32_t(unit) * 512u + 64u * g + lane);
+    }
   }
   __device__ __forceinline__ float at(int i) const {
-    const uint32_t x = v[i >> 3][(i >> 1) & 3];
-    return (i & 1) ? bf_hi(x) : bf_lo(x);
+    if constexpr (kScalar) return z[i];
+    if constexpr (kBf16) {
+      const uint32_t x = h[i >> 3][(i >> 1) & 3];
+      return (i & 1) ? bf_hi(x) : bf_lo(x);
+    }
+    return f[i >> 2][i & 3];
   }
-};
-template <>
-struct UnitRow<DSDE_FP32, true> {
-  f32x4_t v[8];
-  __device__ __forceinline__ void issue(const char *row, int64_t V, int64_t unit, int lane) {
-    const f32x4_t *p = (const f32x4_t *)row;
-    const uint32_t last = uint32_t(V / 4 - 1), i0 = uint32_t(unit) * 512u + uint32_t(lane);
-#pragma unroll
-    for (int g = 0; g < 8; ++g) v[g] = __builtin_nontemporal_load(p + min(i0 + 64u * g, last));
-  }
-  __device__ __forceinline__ void pad(int64_t V, int64_t unit, int lane) {
-    const uint32_t last = uint32_t(V / 4 - 1), i0 = uint32_t(unit) * 512u + uint32_t(lane);
-#pragma unroll
-    for (int g = 0; g < 8; ++g)
-      if (i0 + 64u * g > last) v[g] = f32x4_t{kPadF32, kPadF32, kPadF32, kPadF32};
-  }
-  __device__ __forceinline__ float at(int i) const { return v[i >> 2][i & 3]; }
 };
 
 // What a unit's pass leaves behind, in two arrays per sequence: sub[4 u + g],
@@ -319,40 +309,40 @@ __device__ __forceinline__ void store_totals(float total, float *sub, int32_t un
 }
 
 // Residual weights max(0, p - q) of one unit of the rejected pair.
-template <int DT, bool VEC>
+template <int DT, int ROW>
 __device__ __forceinline__ void residual_unit(const char *trow, const char *drow, int64_t V, int32_t unit,
                                               const DrawJob &job, const UnitCells &c) {
   const int lane = threadIdx.x & 63;
-  UnitRow<DT, VEC> t, d;
+  UnitRow<DT, ROW> t, d;
   t.issue(trow, V, unit, lane);
   d.issue(drow, V, unit, lane);
-  t.pad(V, unit, lane);
-  d.pad(V, unit, lane);
+  t.place(V, unit, lane);
+  d.place(V, unit, lane);
   store_totals(unit_totals([&](int i) { return residual_weight(t.at(i), d.at(i), job); }), c.sub, unit);
 }
 
 // p of one unit of the rejected pair's target row (the draw's fallback when
 // the residual has no mass).
-template <int DT, bool VEC>
+template <int DT, int ROW>
 __device__ __forceinline__ void target_p_unit(const char *trow, int64_t V, int32_t unit, const DrawJob &job,
                                               const UnitCells &c) {
   const int lane = threadIdx.x & 63;
-  UnitRow<DT, VEC> t;
+  UnitRow<DT, ROW> t;
   t.issue(trow, V, unit, lane);
-  t.pad(V, unit, lane);
+  t.place(V, unit, lane);
   store_totals(unit_totals([&](int i) { return target_p_weight(t.at(i), job); }), c.sub, unit);
 }
 
 // Bonus row, one unit: the exponentials 2^(z c - ref) against the unit's own
 // reference.  +inf shows in the maximum, -inf in the minimum, NaN in the
 // totals; padding is finite.
-template <int DT, bool VEC>
+template <int DT, int ROW>
 __device__ __forceinline__ void bonus_unit(const char *trow, int64_t V, int32_t unit, float scale,
                                            const UnitCells &c) {
   const int lane = threadIdx.x & 63;
-  UnitRow<DT, VEC> t;
+  UnitRow<DT, ROW> t;
   t.issue(trow, V, unit, lane);
-  t.pad(V, unit, lane);
+  t.place(V, unit, lane);
   float m = -INFINITY, lo = INFINITY;
 #pragma unroll
   for (int i = 0; i < kUnitElts; ++i) {
@@ -369,12 +359,12 @@ __device__ __forceinline__ void bonus_unit(const char *trow, int64_t V, int32_t 
 
 // Greedy bonus row, one unit: the largest raw logit and the smallest token
 // holding it.  A NaN shows in the sum (|z| <= 2^64 keeps finite sums finite).
-template <int DT, bool VEC>
+template <int DT, int ROW>
 __device__ __forceinline__ void bonus_argmax_unit(const char *trow, int64_t V, int32_t unit, const UnitCells &c) {
   const int lane = threadIdx.x & 63;
-  UnitRow<DT, VEC> t;
+  UnitRow<DT, ROW> t;
   t.issue(trow, V, unit, lane);
-  t.pad(V, unit, lane);
+  t.place(V, unit, lane);
   float m = -INFINITY, lo = INFINITY, sum = 0.f;
 #pragma unroll
   for (int i = 0; i < kUnitElts; ++i) {
@@ -388,7 +378,7 @@ __device__ __forceinline__ void bonus_argmax_unit(const char *trow, int64_t V, i
   if (m == M) {  // a lane's slots ascend in token order: its first equal slot is its smallest token
 #pragma unroll
     for (int i = kUnitElts - 1; i >= 0; --i)
-      if (t.at(i) == M) best = uint32_t(unit_token<DT, VEC>(unit, i, lane));
+      if (t.at(i) == M) best = uint32_t(unit_token<DT, ROW>(unit, i, lane));
   }
   best = lanes::wave_min(best);
   const bool bad = __ballot(m == INFINITY || lo == -INFINITY || sum != sum) != 0;
@@ -396,18 +386,18 @@ __device__ __forceinline__ void bonus_argmax_unit(const char *trow, int64_t V, i
 }
 
 // Every unit of a row that this wavefront takes: units first, first + step, ...
-template <int DT, bool VEC>
+template <int DT, int ROW>
 __device__ __forceinline__ void draw_units(const DrawJob &job, const char *target, const char *draft, int64_t V,
                                            int32_t nu, int32_t first, int32_t step, const UnitCells &c) {
   const size_t esz = DT == DSDE_BF16 ? 2 : 4;
   const char *trow = target + size_t(job.target_row) * size_t(V) * esz;
   if (job.kind == 0) {
     const char *drow = draft + size_t(job.draft_row) * size_t(V) * esz;
-    for (int32_t u = first; u < nu; u += step) residual_unit<DT, VEC>(trow, drow, V, u, job, c);
+    for (int32_t u = first; u < nu; u += step) residual_unit<DT, ROW>(trow, drow, V, u, job, c);
   } else if (job.kind == 1) {
-    for (int32_t u = first; u < nu; u += step) bonus_unit<DT, VEC>(trow, V, u, job.scale, c);
+    for (int32_t u = first; u < nu; u += step) bonus_unit<DT, ROW>(trow, V, u, job.scale, c);
   } else if (job.kind == 3) {
-    for (int32_t u = first; u < nu; u += step) bonus_argmax_unit<DT, VEC>(trow, V, u, c);
+    for (int32_t u = first; u < nu; u += step) bonus_argmax_unit<DT, ROW>(trow, V, u, c);
   }
 }
 
@@ -485,7 +475,7 @@ __device__ __forceinline__ int32_t row_argmax(const UnitCells &c, int32_t nu, co
 // (prefixes tile exactly: each position's start is the previous one's end),
 // which also covers rounding past the total.  Returns the row-local token id
 // in every lane.
-template <int DT, bool VEC>
+template <int DT, int ROW>
 __device__ __forceinline__ int32_t draw_in_row(const UnitCells &c, int32_t nu, const UnitCell &cell0, float row_ref,
                                                double target, const char *trow, const char *drow, int64_t V, int mode,
                                                const DrawJob &job) {
@@ -532,10 +522,10 @@ __device__ __forceinline__ int32_t draw_in_row(const UnitCells &c, int32_t nu, c
   float w[8];
   {
     float zt[8];
-    load_run<DT, VEC, 8>(trow, V, run0, zt);
+    load_run8<DT, ROW>(trow, V, run0, zt);
     if (mode == 0) {
       float zd[8];
-      load_run<DT, VEC, 8>(drow, V, run0, zd);
+      load_run8<DT, ROW>(drow, V, run0, zd);
 #pragma unroll
       for (int i = 0; i < 8; ++i) w[i] = residual_weight(zt[i], zd[i], job);
     } else if (mode == 1) {

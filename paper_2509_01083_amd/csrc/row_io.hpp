@@ -70,9 +70,9 @@ __device__ __forceinline__ float block_max(float v, float *lds) {
 //
 // The 8192 logits of chunk k of a row are spread over the 256 threads so that
 // each wavefront load is contiguous.  Thread t owns slots i = 0..31:
-//   bf16, 16-byte rows : logit 8 * (1024 k + 256 (i / 8) + t) + i % 8  (4 x uint4)
-//   fp32, 16-byte rows : logit 4 * (2048 k + 256 (i / 4) + t) + i % 4  (8 x float4)
-//   any other row      : logit 8192 k + 256 i + t                       (32 scalars)
+//   bf16 rows        : logit 8 * (1024 k + 256 (i / 8) + t) + i % 8  (4 x uint4)
+//   fp32 rows        : logit 4 * (2048 k + 256 (i / 4) + t) + i % 4  (8 x float4)
+//   rows below 16 B  : logit 8192 k + 256 i + t                       (32 scalars)
 // Every load uses an in-bounds (clamped) index and the value is replaced by
 // padding past V, so the loads never branch.
 
@@ -112,30 +112,84 @@ struct RawBf16 {
   uint4 v0, v1, v2, v3;
 };
 
-// The same loads without the padding (indices clamped into the row), and the
-// padding applied afterwards: callers that issue many loads up front pad only
-// where the values are used, so that no load waits for another.
-__device__ __forceinline__ RawBf16 issue_raw_bf16(const void *row, int64_t V, int64_t chunk, int t) {
-  const uint4 *p = (const uint4 *)row;
-  const int64_t last = V / 8 - 1;
-  const int64_t i0 = chunk * 1024 + t;
+// How a row is read.  Sixteen-byte loads need no alignment on gfx950 beyond
+// the element's, so rows of any width from one load up take them: a load that
+// would pass the row's end starts at its last full 16 bytes instead, and the
+// logits are moved down into their places afterwards.  Only rows narrower than
+// one load (8 bf16 or 4 fp32 logits) are read one logit at a time.  Aligned
+// rows (16-byte base, a whole number of loads) keep a form of their own, whose
+// last load needs no moving: the moving is a branch that only the wavefront at
+// the row's end takes, but it keeps the compiler from mixing the loads with
+// the arithmetic of the hot kernel.
+enum : int { kScalarRows = 0, kUnalignedRows = 1, kAlignedRows = 2 };
+
+typedef u32x4_t __attribute__((aligned(2))) u32x4_a2_t;
+typedef f32x4_t __attribute__((aligned(4))) f32x4_a4_t;
+
+// Logits 8 w .. 8 w + 7 of a bf16 row (V >= 8), from inside the row.
+template <int ROW>
+__device__ __forceinline__ u32x4_t load_words(const char *row, uint32_t V, uint32_t w) {
+  if constexpr (ROW == kAlignedRows) return __builtin_nontemporal_load((const u32x4_t *)row + min(w, V / 8 - 1));
+  return __builtin_nontemporal_load((const u32x4_a2_t *)(row + 2 * size_t(min(8 * w, V - 8))));
+}
+// What load_words returned, in place and padded past V.
+template <int ROW>
+__device__ __forceinline__ void place_words(u32x4_t &v, uint32_t V, uint32_t w) {
+  constexpr uint32_t P = kPadBf16x2;
+  if constexpr (ROW == kAlignedRows) {
+    if (w > V / 8 - 1) v = u32x4_t{P, P, P, P};
+  } else if (8 * w > V - 8) {
+    const uint32_t n = min(8 * w - (V - 8), 8u);  // logits to move down by (8: none of them is wanted)
+    if (n & 8) v = u32x4_t{P, P, P, P};
+    if (n & 4) v = u32x4_t{v.z, v.w, P, P};
+    if (n & 2) v = u32x4_t{v.y, v.z, v.w, P};
+    if (n & 1)
+      v = u32x4_t{(v.x >> 16) | (v.y << 16), (v.y >> 16) | (v.z << 16), (v.z >> 16) | (v.w << 16),
+                  (v.w >> 16) | (P << 16)};
+  }
+}
+// Logits 4 w .. 4 w + 3 of an fp32 row (V >= 4), likewise.
+template <int ROW>
+__device__ __forceinline__ f32x4_t load_quad(const char *row, uint32_t V, uint32_t w) {
+  if constexpr (ROW == kAlignedRows) return __builtin_nontemporal_load((const f32x4_t *)row + min(w, V / 4 - 1));
+  return __builtin_nontemporal_load((const f32x4_a4_t *)(row + 4 * size_t(min(4 * w, V - 4))));
+}
+template <int ROW>
+__device__ __forceinline__ void place_quad(f32x4_t &v, uint32_t V, uint32_t w) {
+  constexpr float P = kPadF32;
+  if constexpr (ROW == kAlignedRows) {
+    if (w > V / 4 - 1) v = f32x4_t{P, P, P, P};
+  } else if (4 * w > V - 4) {
+    const uint32_t n = min(4 * w - (V - 4), 4u);
+    if (n & 4) v = f32x4_t{P, P, P, P};
+    if (n & 2) v = f32x4_t{v.z, v.w, P, P};
+    if (n & 1) v = f32x4_t{v.y, v.z, v.w, P};
+  }
+}
+
+// The unaligned form of load_raw_bf16 in its two halves, so that both rows'
+// loads are issued before the first branch.
+__device__ __forceinline__ uint4 as_uint4(u32x4_t v) { return make_uint4(v.x, v.y, v.z, v.w); }
+__device__ __forceinline__ RawBf16 issue_raw_unaligned(const char *row, int64_t V, int64_t chunk, int t) {
+  const uint32_t i0 = uint32_t(chunk) * 1024u + uint32_t(t), n = uint32_t(V);
   RawBf16 r;
-  r.v0 = stream_load(p + min(i0, last));
-  r.v1 = stream_load(p + min(i0 + 256, last));
-  r.v2 = stream_load(p + min(i0 + 512, last));
-  r.v3 = stream_load(p + min(i0 + 768, last));
+  r.v0 = as_uint4(load_words<kUnalignedRows>(row, n, i0));
+  r.v1 = as_uint4(load_words<kUnalignedRows>(row, n, i0 + 256u));
+  r.v2 = as_uint4(load_words<kUnalignedRows>(row, n, i0 + 512u));
+  r.v3 = as_uint4(load_words<kUnalignedRows>(row, n, i0 + 768u));
   return r;
 }
-__device__ __forceinline__ RawBf16 pad_raw_bf16(const RawBf16 &a, int64_t V, int64_t chunk, int t) {
-  const int64_t last = V / 8 - 1;
-  const int64_t i0 = chunk * 1024 + t;
-  const uint4 pad = make_uint4(kPadBf16x2, kPadBf16x2, kPadBf16x2, kPadBf16x2);
-  RawBf16 r;
-  r.v0 = i0 <= last ? a.v0 : pad;
-  r.v1 = i0 + 256 <= last ? a.v1 : pad;
-  r.v2 = i0 + 512 <= last ? a.v2 : pad;
-  r.v3 = i0 + 768 <= last ? a.v3 : pad;
-  return r;
+__device__ __forceinline__ void place_uint4(uint4 &a, uint32_t V, uint32_t w) {
+  u32x4_t v{a.x, a.y, a.z, a.w};
+  place_words<kUnalignedRows>(v, V, w);
+  a = as_uint4(v);
+}
+__device__ __forceinline__ void place_raw_unaligned(RawBf16 &r, int64_t V, int64_t chunk, int t) {
+  const uint32_t i0 = uint32_t(chunk) * 1024u + uint32_t(t), n = uint32_t(V);
+  place_uint4(r.v0, n, i0);
+  place_uint4(r.v1, n, i0 + 256u);
+  place_uint4(r.v2, n, i0 + 512u);
+  place_uint4(r.v3, n, i0 + 768u);
 }
 
 __device__ __forceinline__ RawBf16 load_raw_bf16(const void *row, int64_t V, int64_t chunk, int t) {
@@ -220,78 +274,67 @@ __device__ __forceinline__ void acc_vec(uint4 t, uint4 d, float c, float rt, flo
   acc_two<ENT>(bf_lo(t.w), bf_hi(t.w), bf_lo(d.w), bf_hi(d.w), c, rt, rd, s, 1);
 }
 
-// Generic chunk of one row as 32 floats (fp32 rows, or rows without 16-byte alignment).
-template <int DT, bool VEC>
-__device__ __forceinline__ void load_chunk_f32(const void *row, int64_t V, int64_t chunk, int t,
-                                               float (&z)[kEltsPerThread]) {
-  if constexpr (VEC && DT == DSDE_FP32) {
-    const float4 *p = (const float4 *)row;
-    const int64_t last = V / 4 - 1;
+// Generic chunk of one row as 32 floats (fp32 rows, or rows narrower than a
+// load): the loads, and the placing of what they returned.
+template <int DT, int ROW>
+__device__ __forceinline__ void issue_chunk_f32(const char *row, int64_t V, int64_t chunk, int t,
+                                                float (&z)[kEltsPerThread]) {
+  if constexpr (ROW != kScalarRows) {
+    static_assert(DT == DSDE_FP32, "bf16 rows of at least one load have their own kernel");
 #pragma unroll
     for (int g = 0; g < 8; ++g) {
-      const int64_t i = chunk * 2048 + g * 256 + t;
-      const float4 w = stream_load(p + min(i, last));
-      const bool ok = i <= last;
-      z[g * 4 + 0] = ok ? w.x : kPadF32;
-      z[g * 4 + 1] = ok ? w.y : kPadF32;
-      z[g * 4 + 2] = ok ? w.z : kPadF32;
-      z[g * 4 + 3] = ok ? w.w : kPadF32;
-    }
-  } else if constexpr (VEC && DT == DSDE_BF16) {
-    const RawBf16 r = load_raw_bf16(row, V, chunk, t);
+      const f32x4_t w = load_quad<ROW>(row, uint32_t(V), uint32_t(chunk) * 2048u + uint32_t(g * 256 + t));
 #pragma unroll
-    for (int i = 0; i < kEltsPerThread; ++i) z[i] = pick_bf16(r, i);
+      for (int e = 0; e < 4; ++e) z[g * 4 + e] = w[e];
+    }
   } else {
 #pragma unroll
     for (int i = 0; i < kEltsPerThread; ++i) {
       const int64_t v = chunk * kChunk + int64_t(i) * 256 + t;
-      const float x = load_logit(row, DT, v < V ? v : V - 1);
-      z[i] = v < V ? x : kPadF32;
+      z[i] = load_logit(row, DT, v < V ? v : V - 1);
     }
   }
 }
-
-// R consecutive logits of a row, from `start` (a multiple of R, R a multiple
-// of 8), padded past V.
-template <int DT, bool VEC, int R>
-__device__ __forceinline__ void load_run(const void *row, int64_t V, int64_t start, float (&z)[R]) {
-  if constexpr (VEC && DT == DSDE_BF16) {
-    const uint4 *p = (const uint4 *)row;
-    const int64_t last = V / 8 - 1;
+template <int DT, int ROW>
+__device__ __forceinline__ void place_chunk_f32(int64_t V, int64_t chunk, int t, float (&z)[kEltsPerThread]) {
+  if constexpr (ROW != kScalarRows) {
 #pragma unroll
-    for (int q = 0; q < R / 8; ++q) {
-      const int64_t i = start / 8 + q;
-      const uint4 a = p[min(i, last)];
-      const uint4 v = i <= last ? a : make_uint4(kPadBf16x2, kPadBf16x2, kPadBf16x2, kPadBf16x2);
-      z[8 * q + 0] = bf_lo(v.x);
-      z[8 * q + 1] = bf_hi(v.x);
-      z[8 * q + 2] = bf_lo(v.y);
-      z[8 * q + 3] = bf_hi(v.y);
-      z[8 * q + 4] = bf_lo(v.z);
-      z[8 * q + 5] = bf_hi(v.z);
-      z[8 * q + 6] = bf_lo(v.w);
-      z[8 * q + 7] = bf_hi(v.w);
-    }
-  } else if constexpr (VEC && DT == DSDE_FP32) {
-    const float4 *p = (const float4 *)row;
-    const int64_t last = V / 4 - 1;
+    for (int g = 0; g < 8; ++g) {
+      f32x4_t w{z[g * 4], z[g * 4 + 1], z[g * 4 + 2], z[g * 4 + 3]};
+      place_quad<ROW>(w, uint32_t(V), uint32_t(chunk) * 2048u + uint32_t(g * 256 + t));
 #pragma unroll
-    for (int q = 0; q < R / 4; ++q) {
-      const int64_t i = start / 4 + q;
-      const float4 a = p[min(i, last)];
-      const bool ok = i <= last;
-      z[4 * q + 0] = ok ? a.x : kPadF32;
-      z[4 * q + 1] = ok ? a.y : kPadF32;
-      z[4 * q + 2] = ok ? a.z : kPadF32;
-      z[4 * q + 3] = ok ? a.w : kPadF32;
+      for (int e = 0; e < 4; ++e) z[g * 4 + e] = w[e];
     }
   } else {
 #pragma unroll
-    for (int i = 0; i < R; ++i) {
+    for (int i = 0; i < kEltsPerThread; ++i)
+      if (chunk * kChunk + int64_t(i) * 256 + t >= V) z[i] = kPadF32;
+  }
+}
+
+// Eight consecutive logits of a row, from `start` (a multiple of 8), padded
+// past V.
+template <int DT, int ROW>
+__device__ __forceinline__ void load_run8(const char *row, int64_t V, int64_t start, float (&z)[8]) {
+  const uint32_t n = uint32_t(V), first = uint32_t(start);
+  if constexpr (ROW == kScalarRows) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
       const int64_t v = start + i;
       const float x = load_logit(row, DT, v < V ? v : V - 1);
       z[i] = v < V ? x : kPadF32;
     }
+  } else if constexpr (DT == DSDE_BF16) {
+    u32x4_t v = load_words<ROW>(row, n, first / 8);
+    place_words<ROW>(v, n, first / 8);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) z[i] = (i & 1) ? bf_hi(v[i / 2]) : bf_lo(v[i / 2]);
+  } else {
+    f32x4_t a = load_quad<ROW>(row, n, first / 4), b = load_quad<ROW>(row, n, first / 4 + 1);
+    place_quad<ROW>(a, n, first / 4);
+    place_quad<ROW>(b, n, first / 4 + 1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) z[i] = a[i], z[4 + i] = b[i];
   }
 }
 

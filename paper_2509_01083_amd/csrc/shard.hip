@@ -23,8 +23,6 @@
 #include <math.h>
 #include <stddef.h>
 
-#include <type_traits>
-
 #include "common.hpp"
 #include "draw_device.hpp"
 #include "lanes.hpp"
@@ -279,7 +277,7 @@ __global__ __launch_bounds__(64) void shard_accept_kernel(
 
 // One workgroup per sequence: the draw weight of the slice, unit by unit; the
 // cells of sequence b go to the workspace at b * nu.
-template <int DT, bool VEC>
+template <int DT, int ROW>
 __global__ __launch_bounds__(kMassThreads) void shard_mass_kernel(
     const void *__restrict__ target, const void *__restrict__ draft, int64_t V, int32_t nu, int64_t v_begin,
     const dsde_shard_partial *__restrict__ part, const DrawJob *__restrict__ jobs, dsde_shard_mass *__restrict__ mass,
@@ -300,7 +298,7 @@ __global__ __launch_bounds__(kMassThreads) void shard_mass_kernel(
     if (t == 0) mass[b] = m;
     return;
   }
-  draw_units<DT, VEC>(job, (const char *)target, (const char *)draft, V, nu, wave, kMassThreads / 64, cells);
+  draw_units<DT, ROW>(job, (const char *)target, (const char *)draft, V, nu, wave, kMassThreads / 64, cells);
   __syncthreads();
   if (wave != 0) return;
   const UnitCell cell0 = load_cell(cells, lane, nu, job.kind != 0);
@@ -330,7 +328,7 @@ __global__ __launch_bounds__(kMassThreads) void shard_mass_kernel(
 // search alike (no barrier needed); the shard whose slice holds the target
 // finishes the draw on wavefront 0 (the fallback to p first computes that
 // slice's p totals with all wavefronts).
-template <int DT, bool VEC>
+template <int DT, int ROW>
 __global__ __launch_bounds__(kShardThreads) void shard_pick_kernel(
     int32_t G, int32_t gself, const dsde_shard_mass *__restrict__ masses, int32_t B, const void *__restrict__ target,
     const void *__restrict__ draft, int64_t V, int32_t nu, int64_t v_begin, int32_t k_max,
@@ -442,12 +440,12 @@ __global__ __launch_bounds__(kShardThreads) void shard_pick_kernel(
   const char *drow = job.draft_row >= 0 ? (const char *)draft + size_t(job.draft_row) * size_t(V) * esz : nullptr;
   const UnitCells cells{sub + int64_t(b) * nu * kSubs, ref + int64_t(b) * nu};
   if (mode == 1) {  // the slice's p totals, which call 3 did not keep
-    for (int32_t u = wave; u < nu; u += kShardWaves) target_p_unit<DT, VEC>(trow, V, u, job, cells);
+    for (int32_t u = wave; u < nu; u += kShardWaves) target_p_unit<DT, ROW>(trow, V, u, job, cells);
     __syncthreads();
   }
   if (wave != 0) return;
   const UnitCell cell0 = load_cell(cells, lane, nu, mode == 2);
-  const int32_t local = draw_in_row<DT, VEC>(cells, nu, cell0, row_ref, rem, trow, drow, V, mode, job);
+  const int32_t local = draw_in_row<DT, ROW>(cells, nu, cell0, row_ref, rem, trow, drow, V, mode, job);
   if (lane == 0) {
     const int32_t token = int32_t(v_begin + local);
     tok[job.accepted] = token;
@@ -455,26 +453,9 @@ __global__ __launch_bounds__(kShardThreads) void shard_pick_kernel(
   }
 }
 
-bool shard_rows_vectorizable(const ShardRows &r) {
-  const auto aligned16 = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
-  return aligned16(r.target) && (r.N == 0 || aligned16(r.draft)) &&
-         (r.dtype == DSDE_BF16 ? r.V_shard % 8 == 0 : r.V_shard % 4 == 0);
-}
-
 template <typename F>
 void by_layout(const ShardRows &r, F f) {
-  const bool vec = shard_rows_vectorizable(r);
-  if (r.dtype == DSDE_BF16) {
-    if (vec)
-      f(std::integral_constant<int, DSDE_BF16>{}, std::true_type{});
-    else
-      f(std::integral_constant<int, DSDE_BF16>{}, std::false_type{});
-  } else {
-    if (vec)
-      f(std::integral_constant<int, DSDE_FP32>{}, std::true_type{});
-    else
-      f(std::integral_constant<int, DSDE_FP32>{}, std::false_type{});
-  }
+  by_rows(r.dtype, rows_form(r.target, r.draft, r.dtype, r.V_shard, r.N), f);
 }
 
 }  // namespace
@@ -557,8 +538,8 @@ int launch_shard_draw_mass(const ShardRows &r, const dsde_shard_partial *part, c
   char *ws = (char *)r.workspace;
   const int32_t nu = int32_t(num_units(r.V_shard));
   (void)hipGetLastError();
-  by_layout(r, [&](auto dt, auto vec) {
-    shard_mass_kernel<decltype(dt)::value, decltype(vec)::value><<<dim3(unsigned(r.B)), dim3(kMassThreads), 0,
+  by_layout(r, [&](auto dt, auto row) {
+    shard_mass_kernel<decltype(dt)::value, decltype(row)::value><<<dim3(unsigned(r.B)), dim3(kMassThreads), 0,
                                                                    r.stream>>>(
         r.target, r.draft, r.V_shard, nu, r.v_begin, part, reinterpret_cast<const DrawJob *>(jobs), mass,
         (float *)(ws + L.sub), (UnitRef *)(ws + L.ref));
@@ -573,8 +554,8 @@ int launch_shard_draw_pick(const ShardRows &r, int32_t G, int32_t g, const dsde_
   char *ws = (char *)r.workspace;
   const int32_t nu = int32_t(num_units(r.V_shard));
   (void)hipGetLastError();
-  by_layout(r, [&](auto dt, auto vec) {
-    shard_pick_kernel<decltype(dt)::value, decltype(vec)::value><<<dim3(unsigned(r.B)), dim3(kShardThreads), 0,
+  by_layout(r, [&](auto dt, auto row) {
+    shard_pick_kernel<decltype(dt)::value, decltype(row)::value><<<dim3(unsigned(r.B)), dim3(kShardThreads), 0,
                                                                    r.stream>>>(
         G, g, masses, r.B, r.target, r.draft, r.V_shard, nu, r.v_begin, r.k_max,
         reinterpret_cast<const DrawJob *>(jobs), pad_id, accepted, tokens, drawn, seq_err, (float *)(ws + L.sub),

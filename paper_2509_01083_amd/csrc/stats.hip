@@ -200,12 +200,12 @@ __device__ __forceinline__ void write_pair_chunk(float rt, float rd, const PairA
   }
 }
 
-// bf16 rows with 16-byte alignment: the hot kernel.  ENT: accumulate the
+// bf16 rows of at least one 16-byte load: the hot kernel.  ENT: accumulate the
 // draft entropy, only for callers that ask for it (one FMA of about twenty
 // VALU instructions per logit pair).  Two kernels rather than a branch in
 // one: with both forms in one body the compiler hoists their common
 // arithmetic above the branch and nearly doubles the register footprint.
-template <bool ENT, bool LOOKUP>
+template <bool ENT, bool LOOKUP, int ROW>
 __global__ __launch_bounds__(kThreads) void stats_kernel_bf16(const void *__restrict__ target,
                                                              const void *__restrict__ draft, int64_t V, int32_t nc,
                                                              const WorkItem *__restrict__ work,
@@ -225,8 +225,16 @@ __global__ __launch_bounds__(kThreads) void stats_kernel_bf16(const void *__rest
   const float c = __uint_as_float(w.scale_bits & ~kGreedyBit);
   const char *trow = (const char *)target + size_t(w.target_row) * size_t(V) * 2;
   const char *drow = (const char *)draft + size_t(w.pair) * size_t(V) * 2;
-  const RawBf16 rt_ = load_raw_bf16(trow, V, chunk, t);
-  const RawBf16 rd_ = load_raw_bf16(drow, V, chunk, t);
+  RawBf16 rt_, rd_;
+  if constexpr (ROW == kAlignedRows) {
+    rt_ = load_raw_bf16(trow, V, chunk, t);
+    rd_ = load_raw_bf16(drow, V, chunk, t);
+  } else {
+    rt_ = issue_raw_unaligned(trow, V, chunk, t);
+    rd_ = issue_raw_unaligned(drow, V, chunk, t);
+    place_raw_unaligned(rt_, V, chunk, t);
+    place_raw_unaligned(rd_, V, chunk, t);
+  }
 
   // chunk maxima -> the reference shifts every exponential of the chunk uses
   const float tmt = raw_max(rt_);
@@ -265,8 +273,8 @@ __global__ __launch_bounds__(kThreads) void stats_kernel_bf16(const void *__rest
                    greedy ? chunk_arg + int64_t(w.slot) * nc + chunk : nullptr);
 }
 
-// fp32 rows, or rows without 16-byte alignment.
-template <int DT, bool VEC, bool LOOKUP>
+// fp32 rows, or bf16 rows narrower than one load.
+template <int DT, int ROW, bool LOOKUP>
 __global__ __launch_bounds__(kThreads) void stats_kernel_generic(const void *__restrict__ target,
                                                                 const void *__restrict__ draft, int64_t V,
                                                                 int32_t nc, const WorkItem *__restrict__ work,
@@ -288,8 +296,10 @@ __global__ __launch_bounds__(kThreads) void stats_kernel_generic(const void *__r
   const char *trow = (const char *)target + size_t(w.target_row) * size_t(V) * esz;
   const char *drow = (const char *)draft + size_t(w.pair) * size_t(V) * esz;
   float zt[kEltsPerThread], zd[kEltsPerThread];
-  load_chunk_f32<DT, VEC>(trow, V, chunk, t, zt);
-  load_chunk_f32<DT, VEC>(drow, V, chunk, t, zd);
+  issue_chunk_f32<DT, ROW>(trow, V, chunk, t, zt);
+  issue_chunk_f32<DT, ROW>(drow, V, chunk, t, zd);
+  place_chunk_f32<DT, ROW>(V, chunk, t, zt);
+  place_chunk_f32<DT, ROW>(V, chunk, t, zd);
   float mt = zt[0], md = zd[0];
 #pragma unroll
   for (int i = 1; i < kEltsPerThread; ++i) {
@@ -298,7 +308,7 @@ __global__ __launch_bounds__(kThreads) void stats_kernel_generic(const void *__r
   }
   const float Mt = block_max(mt, red[0]);
   const float Md = block_max(md, red[1]);
-  if (greedy) wave_chunk_argmax<DT, VEC>(Mt, mt, [&](int i) { return zt[i]; }, chunk, red_arg);
+  if (greedy) wave_chunk_argmax<DT, ROW != kScalarRows>(Mt, mt, [&](int i) { return zt[i]; }, chunk, red_arg);
   const float rt = Mt * c, rd = Md * c;
   PairAcc s;
   zero(s);
@@ -311,7 +321,7 @@ __global__ __launch_bounds__(kThreads) void stats_kernel_generic(const void *__r
   const int64_t local = int64_t(draft_tokens[w.pair]) - token_base - chunk * kChunk;
   if (local >= 0 && local < kChunk) {
     int ot, oi;
-    Layout<DT, VEC>::owner(local, &ot, &oi);
+    Layout<DT, ROW != kScalarRows>::owner(local, &ot, &oi);
     if (t == ot) {
       float a = 0.f, b = 0.f;
 #pragma unroll
@@ -329,8 +339,6 @@ __global__ __launch_bounds__(kThreads) void stats_kernel_generic(const void *__r
 
 }  // namespace
 
-static inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-
 // With profiling events set, `stop` is attached to the completion of the
 // statistics dispatch and `start` to the completion of the set-up dispatch
 // just before it, so that the interval is the statistics kernel alone (a
@@ -342,11 +350,6 @@ static void launch_timed(K kernel, dim3 grid, dim3 block, hipStream_t stream, hi
     hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, nullptr, done, 0, args...);
   else
     hipLaunchKernelGGL(kernel, grid, block, 0, stream, args...);
-}
-
-bool rows_vectorizable(const VerifyArgs &a) {
-  return aligned16(a.target) && (a.N == 0 || aligned16(a.draft)) &&
-         (a.dtype == DSDE_BF16 ? a.V % 8 == 0 : a.V % 4 == 0);
 }
 
 // Whether the statistics pass runs without the set-up kernel, on a grid over
@@ -370,7 +373,6 @@ template <bool LOOKUP>
 static void launch_rows(const VerifyArgs &a, const WorkItem *w, PairChunk *part, Gathered *gath, ChunkArg *chunk_arg,
                         bool entropy, hipEvent_t done) {
   const int32_t nc = int32_t(num_chunks(a.V));
-  const bool vec = rows_vectorizable(a);
   const dim3 grid = LOOKUP ? dim3(unsigned(nc), unsigned(a.k_max), unsigned(a.B)) : dim3(unsigned(a.N * nc));
   const dim3 block(kThreads);
   const void *T = a.target, *D = a.draft;
@@ -379,21 +381,18 @@ static void launch_rows(const VerifyArgs &a, const WorkItem *w, PairChunk *part,
   const int64_t base = a.token_base;
   const uint32_t k_rcp = a.k_max > 1 ? uint32_t(((uint64_t(1) << 32) + a.k_max - 1) / a.k_max) : 0u;
   const BatchLayout L{a.sl, a.cu_sl, a.temperature, a.N, a.k_max, k_rcp};
-  if (a.dtype == DSDE_BF16 && vec && entropy)
-    launch_timed(stats_kernel_bf16<true, LOOKUP>, grid, block, a.stream, done, T, D, V, nc, w, L, tokens, base, part,
-                 gath, chunk_arg);
-  else if (a.dtype == DSDE_BF16 && vec)
-    launch_timed(stats_kernel_bf16<false, LOOKUP>, grid, block, a.stream, done, T, D, V, nc, w, L, tokens, base, part,
-                 gath, chunk_arg);
-  else if (a.dtype == DSDE_BF16)
-    launch_timed(stats_kernel_generic<DSDE_BF16, false, LOOKUP>, grid, block, a.stream, done, T, D, V, nc, w, L,
-                 tokens, base, part, gath, chunk_arg);
-  else if (vec)
-    launch_timed(stats_kernel_generic<DSDE_FP32, true, LOOKUP>, grid, block, a.stream, done, T, D, V, nc, w, L, tokens,
-                 base, part, gath, chunk_arg);
-  else
-    launch_timed(stats_kernel_generic<DSDE_FP32, false, LOOKUP>, grid, block, a.stream, done, T, D, V, nc, w, L,
-                 tokens, base, part, gath, chunk_arg);
+  by_rows(a.dtype, rows_form(a.target, a.draft, a.dtype, a.V, a.N), [&](auto dt, auto row) {
+    constexpr int DT = decltype(dt)::value, ROW = decltype(row)::value;
+    auto run = [&](auto kernel) {
+      launch_timed(kernel, grid, block, a.stream, done, T, D, V, nc, w, L, tokens, base, part, gath, chunk_arg);
+    };
+    if constexpr (DT == DSDE_FP32 || ROW == kScalarRows)
+      run(stats_kernel_generic<DT, ROW, LOOKUP>);
+    else if (entropy)
+      run(stats_kernel_bf16<true, LOOKUP, ROW>);
+    else
+      run(stats_kernel_bf16<false, LOOKUP, ROW>);
+  });
 }
 
 void launch_stats_pass(const VerifyArgs &a, bool lookup, WorkItem *work, PairChunk *part, Gathered *gath,

@@ -73,7 +73,7 @@ struct StepParams {
 // streamed and drew in one workgroup per sequence: 21.7 -> 6.6 us for one
 // sequence (V = 128,256 bf16), 65.4 -> 14.6 us for 64 in fp32,
 // 29.8 -> 25.8 us for 256 in bf16 (18 us of bytes).
-template <int DT, bool VEC, bool FUSED>
+template <int DT, int ROW, bool FUSED>
 __global__ __launch_bounds__(kSeqThreads) void seq_kernel(const StepParams P, const SignalArgs S) {
   __shared__ float st_mt[DSDE_MAX_K + 1], st_md[DSDE_MAX_K + 1];
   __shared__ double st_sp[DSDE_MAX_K + 1], st_sq[DSDE_MAX_K + 1], st_a[DSDE_MAX_K + 1], st_h[DSDE_MAX_K + 1];
@@ -256,7 +256,7 @@ __global__ __launch_bounds__(kSeqThreads) void seq_kernel(const StepParams P, co
     const DrawJob job = uniform_job(s_job);
     const UnitCells cells{P.sub + int64_t(lb) * P.nu * kSubs, P.ref + int64_t(lb) * P.nu};
     const int32_t gw = (int32_t(blockIdx.y) - 1) * kSeqWaves + wave;
-    draw_units<DT, VEC>(job, (const char *)P.target, (const char *)P.draft, P.V, P.nu, gw,
+    draw_units<DT, ROW>(job, (const char *)P.target, (const char *)P.draft, P.V, P.nu, gw,
                         (int32_t(gridDim.y) - 1) * kSeqWaves, cells);
     return;
   }
@@ -304,7 +304,7 @@ __global__ __launch_bounds__(kSeqThreads) void seq_kernel(const StepParams P, co
 // order of its sums).  A sequence's draw needs one wavefront; the others are
 // there for a residual without mass, whose fallback to p has to read the
 // target row again.
-template <int DT, bool VEC>
+template <int DT, int ROW>
 __global__ __launch_bounds__(kCapThreads) void pick_kernel(const StepParams P, const SignalArgs S, bool rule) {
   if (rule && blockIdx.x == gridDim.x - 1) {
     __shared__ double red_s[kCapThreads / 64];
@@ -353,14 +353,14 @@ __global__ __launch_bounds__(kCapThreads) void pick_kernel(const StepParams P, c
   if (mode == 0 && !(Z > 0.0)) {  // no residual mass (the same in every wavefront): p of the same target row
     mode = 1;
     __syncthreads();  // every wavefront has read the residual's cells, which p's now replace
-    for (int32_t u = wave; u < P.nu; u += kCapThreads / 64) target_p_unit<DT, VEC>(trow, P.V, u, job, cells);
+    for (int32_t u = wave; u < P.nu; u += kCapThreads / 64) target_p_unit<DT, ROW>(trow, P.V, u, job, cells);
     __syncthreads();
     cell0 = load_cell(cells, lane, P.nu, false);
     Z = row_total(cells, P.nu, cell0, mode, row_ref);
   }
   if (wave != 0) return;
   const int32_t token =
-      draw_in_row<DT, VEC>(cells, P.nu, cell0, row_ref, double(job.u) * Z, trow, drow, P.V, mode, job);
+      draw_in_row<DT, ROW>(cells, P.nu, cell0, row_ref, double(job.u) * Z, trow, drow, P.V, mode, job);
   if (lane == 0) tok[job.accepted] = token;
 }
 
@@ -375,7 +375,7 @@ static int32_t stream_parts(int32_t seqs, int32_t nu) {
   return want < most ? want : most;
 }
 
-template <int DT, bool VEC>
+template <int DT, int ROW>
 static void launch_draw(const VerifyArgs &a, StepParams P, const SignalArgs &S) {
   const int32_t per_pass = draw_seqs_per_pass(a.B, a.V);
   for (int32_t b0 = 0; b0 < a.B; b0 += per_pass) {
@@ -384,12 +384,12 @@ static void launch_draw(const VerifyArgs &a, StepParams P, const SignalArgs &S) 
     P.first_seq = b0;
     const dim3 grid(unsigned(seqs), unsigned(1 + stream_parts(seqs, P.nu)));
     if (a.signal)
-      seq_kernel<DT, VEC, true><<<grid, dim3(kSeqThreads), 0, a.stream>>>(P, S);
+      seq_kernel<DT, ROW, true><<<grid, dim3(kSeqThreads), 0, a.stream>>>(P, S);
     else
-      seq_kernel<DT, VEC, false><<<grid, dim3(kSeqThreads), 0, a.stream>>>(P, S);
+      seq_kernel<DT, ROW, false><<<grid, dim3(kSeqThreads), 0, a.stream>>>(P, S);
     // the SL rule needs every sequence's signal: behind the last pass
     const bool rule = a.signal && last;
-    pick_kernel<DT, VEC><<<dim3(unsigned(seqs + rule)), dim3(kCapThreads), 0, a.stream>>>(P, S, rule);
+    pick_kernel<DT, ROW><<<dim3(unsigned(seqs + rule)), dim3(kCapThreads), 0, a.stream>>>(P, S, rule);
   }
 }
 
@@ -403,7 +403,6 @@ int launch_verify(const VerifyArgs &a) {
   ChunkArg *cargs = (ChunkArg *)(ws + L.chunk_arg);
   const bool lookup = stats_lookup(a);
   launch_stats_pass(a, lookup, work, part, gath, cargs, a.draft_entropy != nullptr);
-  const bool vec = rows_vectorizable(a);
   StepParams P;
   P.target = a.target;
   P.draft = a.draft;
@@ -435,10 +434,8 @@ int launch_verify(const VerifyArgs &a) {
   P.sub = (float *)(ws + L.sub);
   P.ref = (UnitRef *)(ws + L.ref);
   const SignalArgs S = a.signal ? *a.signal : SignalArgs{};
-  if (a.dtype == DSDE_BF16)
-    vec ? launch_draw<DSDE_BF16, true>(a, P, S) : launch_draw<DSDE_BF16, false>(a, P, S);
-  else
-    vec ? launch_draw<DSDE_FP32, true>(a, P, S) : launch_draw<DSDE_FP32, false>(a, P, S);
+  by_rows(a.dtype, rows_form(a.target, a.draft, a.dtype, a.V, a.N),
+          [&](auto dt, auto row) { launch_draw<decltype(dt)::value, decltype(row)::value>(a, P, S); });
   return hipGetLastError() == hipSuccess ? DSDE_OK : DSDE_DEVICE_ERROR;
 }
 

@@ -71,3 +71,49 @@ def test_statistics_with_and_without_the_setup_kernel(gpu_lib, B, k_max, V):
                          step.u_acc, step.u_res, k_max)
     torch.cuda.synchronize()
     assert (got["seq_err"] == 1).all() and (got["accepted"] == 0).all() and (got["tokens"] == -1).all()
+
+
+def _shifted(t, by):
+    """A contiguous copy of t that starts `by` elements into its allocation."""
+    flat = torch.empty(t.numel() + by, dtype=t.dtype, device=t.device)
+    flat[by:] = t.reshape(-1)
+    return flat[by:].view(t.shape)
+
+
+@pytest.mark.parametrize("dtype,widths", [("bf16", (8, 9, 15, 23, 8185, 8191, 8193, 8199, 10247)),
+                                          ("fp32", (4, 5, 7, 11, 8189, 8191, 8193, 8195, 10243))])
+def test_unaligned_rows(gpu_lib, dtype, widths):
+    """Row widths that are no whole number of 16-byte loads, from one load up:
+    the last load of a row starts inside the one before it."""
+    for V in widths:
+        rng = np.random.default_rng(V)
+        sls = [3, 0, 1, 4, 2]
+        target, draft, tokens, u_acc, u_res = random_arrays(rng, sls, V, sigma=1.0, noise=0.5)
+        tokens[:4] = [V - 1, V - 2, 0, V - 1]  # logits gathered from the moved last load
+        step = step_from_arrays(target, draft, sls, tokens, [1.0, 0.7, 0.0, 1.3, 0.0], u_acc, u_res, 4, dtype)
+        check_step(gpu_lib, step, f"unaligned rows V={V} {dtype}")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("V", [64, 2048, 8192, 10240, 20000])
+def test_row_alignment_changes_no_bit(gpu_lib, V, dtype):
+    """The same logits from a 16-byte aligned base and from one shifted by
+    single elements (target and draft by different ones)."""
+    rng = np.random.default_rng(V)
+    sls = [3, 0, 1, 4, 2]
+    target, draft, tokens, u_acc, u_res = random_arrays(rng, sls, V, sigma=1.0, noise=0.5)
+    step = step_from_arrays(target, draft, sls, tokens, [1.0, 0.7, 0.0, 1.3, 0.0], u_acc, u_res, 4, dtype)
+    rest = (step.sl, step.cu_sl, step.draft_tokens, step.temperature, step.u_acc, step.u_res, 4)
+
+    def run(target, draft):
+        lse = torch.zeros(step.N, 2, dtype=torch.float64, device="cuda")
+        out = gpu_lib.verify(target, draft, *rest, row_lse=lse, draft_entropy=True)
+        return dict(out, row_lse=lse)
+    want = run(step.target, step.draft)
+    for a, b in ((1, 0), (0, 3), (2, 1)):
+        got = run(_shifted(step.target, a), _shifted(step.draft, b))
+        for k in want:
+            x, y = got[k], want[k]
+            if x.dtype.is_floating_point:
+                x, y = x.view(torch.uint8), y.view(torch.uint8)
+            assert torch.equal(x, y), f"{k} differs at offsets {a}, {b}"
