@@ -131,8 +131,8 @@ __global__ __launch_bounds__(64) void shard_accept_kernel(
   }
   const int32_t s = sl[b], first = cu_sl[b];
   const float T = temperature[b], ur = u_res[b];
-  RingPrefetch rp{};  // the ring state, in flight while the slices are folded
-  if constexpr (FUSED) rp = wave_ring_prefetch(S.hist + int64_t(b) * S.W, S.head + b, S.count + b, S.W);
+  RingPrefetch<4> rp{};  // the ring state, in flight while the slices are folded
+  if constexpr (FUSED) rp = wave_ring_prefetch<4>(S.hist + int64_t(b) * S.W, S.head + b, S.count + b, S.W);
   const bool greedy = T == 0.0f;
   int32_t x = 0;
   float u = 0.f;

@@ -33,12 +33,21 @@ __global__ __launch_bounds__(kSigThreads) void kld_signal_kernel(
     float *__restrict__ wvir, float *__restrict__ sf, uint32_t *__restrict__ seq_err) {
   const int32_t b = int32_t(blockIdx.x) * (kSigThreads / 64) + int32_t(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  // the ring state does not depend on the layout: fetch it with the layout check
-  RingPrefetch rp{};
-  if (b < B) rp = wave_ring_prefetch(hist + int64_t(b) * W, head + b, count + b, W);
+  // one round trip for the ring state, this sequence's place and the layout
+  // check; a second, before the check's verdict, for its KLD values, as far as
+  // its own place lies inside the array
+  RingPrefetch<4> rp{};
+  int32_t s = 0, first = 0;
+  float lane_kld = 0.f;
+  if (b < B) {
+    rp = wave_ring_prefetch<4>(hist + int64_t(b) * W, head + b, count + b, W);
+    s = sl[b];
+    first = cu_sl[b];
+  }
   int bad = 0;
   for (int32_t q = threadIdx.x; q < B; q += blockDim.x)
     if (sl[q] < 0 || int64_t(cu_sl[q + 1]) - int64_t(cu_sl[q]) != int64_t(sl[q])) bad = 1;
+  if (first >= 0 && int64_t(first) + s <= N && lane < s) lane_kld = kld[first + lane];
   bad = __syncthreads_or(bad);
   if (cu_sl[0] != 0 || int64_t(cu_sl[B]) != N) bad = 1;
   if (b >= B) return;
@@ -49,8 +58,8 @@ __global__ __launch_bounds__(kSigThreads) void kld_signal_kernel(
     }
     return;
   }
-  const uint32_t e = wave_signal_update(sl[b], cu_sl[b], kld, 0.0f, rp, hist + int64_t(b) * W, head + b, count + b,
-                                        W, n_short, n_long, delta, eps, mu_last + b, var_short + b, var_long + b,
+  const uint32_t e = wave_signal_update(s, first, kld, lane_kld, rp, hist + int64_t(b) * W, head + b, count + b, W,
+                                        n_short, n_long, delta, eps, mu_last + b, var_short + b, var_long + b,
                                         wvir + b, sf + b);
   if (lane == 0) seq_err[b] = e;
 }

@@ -12,50 +12,19 @@ namespace dsde {
 
 __device__ __forceinline__ double wave_sum_f64(double v) { return lanes::wave_sum(v); }
 
-// Ring slots one wavefront keeps in registers: with W <= 64 * kRingRegs every
-// window entry is read from registers, larger rings are read from memory.
-constexpr int kRingRegs = 4;
+// Ring slots one wavefront keeps in registers: with W <= 64 * REGS every window
+// entry is read from registers, larger rings are read from memory where they
+// are needed.  seq_kernel, which fetches the ring ahead of its combine, has
+// registers for one slot per lane (95 of the 96 that five wavefronts per SIMD
+// leave; 99 with four).
 
 // The ring state of one sequence, fetched by one wavefront ahead of use:
 // head, count, and ring slot l + 64 k in lane l, register k.
+template <int REGS>
 struct RingPrefetch {
   int32_t head, count;
-  float slot[kRingRegs];
+  float slot[REGS];
 };
-
-__device__ __forceinline__ RingPrefetch wave_ring_prefetch(const float *ring, const int32_t *head,
-                                                           const int32_t *count, int32_t W) {
-  const int lane = threadIdx.x & 63;
-  // mbcnt over an empty mask is 0 in every lane, but the compiler treats it
-  // as lane-varying: head and count become vector loads, issued with the ring
-  // loads, instead of scalar loads competing for scalar registers
-  const uint32_t zero = __builtin_amdgcn_mbcnt_lo(0u, 0u);
-  RingPrefetch r;
-  r.head = head[zero];
-  r.count = count[zero];
-#pragma unroll
-  for (int k = 0; k < kRingRegs; ++k) {
-    const int32_t i = lane + 64 * k;
-    r.slot[k] = ring[i < W ? i : W - 1];  // clamped index: always in bounds (W >= 1)
-  }
-  return r;
-}
-
-// Value of ring slot `slot` (0 <= slot < W), in every lane that asks.  Must be
-// reached by the whole wavefront (it shuffles when the ring is in registers).
-__device__ __forceinline__ float ring_slot(const RingPrefetch &rp, const float *ring, int32_t W, int32_t slot) {
-  if (W <= 64 * kRingRegs) {
-    float v = 0.f;
-#pragma unroll
-    for (int k = 0; k < kRingRegs; ++k) {
-      if (64 * k >= W) break;  // uniform: registers past the ring hold nothing
-      const float x = __shfl(rp.slot[k], slot & 63);
-      if ((slot >> 6) == k) v = x;
-    }
-    return v;
-  }
-  return ring[slot];
-}
 
 // delta^n for n >= 0 by binary powering (a few multiplications, no pow()).
 __device__ __forceinline__ double pow_int(double x, int32_t n) {
@@ -68,6 +37,42 @@ __device__ __forceinline__ double pow_int(double x, int32_t n) {
   return r;
 }
 
+template <int REGS>
+__device__ __forceinline__ RingPrefetch<REGS> wave_ring_prefetch(const float *ring, const int32_t *head,
+                                                           const int32_t *count, int32_t W) {
+  const int lane = threadIdx.x & 63;
+  // mbcnt over an empty mask is 0 in every lane, but the compiler treats it
+  // as lane-varying: head and count become vector loads, issued with the ring
+  // loads, instead of scalar loads competing for scalar registers
+  const uint32_t zero = __builtin_amdgcn_mbcnt_lo(0u, 0u);
+  RingPrefetch<REGS> r;
+  r.head = head[zero];
+  r.count = count[zero];
+#pragma unroll
+  for (int k = 0; k < REGS; ++k) {
+    const int32_t i = lane + 64 * k;
+    r.slot[k] = k == 0 || 64 * k < W ? ring[i < W ? i : W - 1] : 0.f;  // clamped index: always in bounds (W >= 1)
+  }
+  return r;
+}
+
+// Value of ring slot `slot` (0 <= slot < W), in every lane that asks.  Must be
+// reached by the whole wavefront (it shuffles when the ring is in registers).
+template <int REGS>
+__device__ __forceinline__ float ring_slot(const RingPrefetch<REGS> &rp, const float *ring, int32_t W, int32_t slot) {
+  if (W <= 64 * REGS) {
+    float v = 0.f;
+#pragma unroll
+    for (int k = 0; k < REGS; ++k) {
+      if (64 * k >= W) break;  // uniform: registers past the ring hold nothing
+      const float x = __shfl(rp.slot[k], slot & 63);
+      if ((slot >> 6) == k) v = x;
+    }
+    return v;
+  }
+  return ring[slot];
+}
+
 // Recency-weighted means and population variances (Eqs. 6-7) of the ns and
 // nl newest ring entries (ns <= nl), evaluated together by one wavefront:
 // entry i (i = 0 newest, value h1 passed in registers) sits in ring slot
@@ -76,18 +81,26 @@ __device__ __forceinline__ double pow_int(double x, int32_t n) {
 // unchanged and gives a window of equal entries a variance of exactly 0.  The
 // means returned are those of the entries less h1.  Lane l holds entries
 // l, l + 64, ...; fixed-order sums, bitwise reproducible.
-__device__ inline void wave_windows(const RingPrefetch &rp, const float *ring, int32_t W, int32_t newest, float h1,
+template <int REGS>
+__device__ inline void wave_windows(const RingPrefetch<REGS> &rp, const float *ring, int32_t W, int32_t newest, float h1,
                                     int32_t ns, int32_t nl, double delta, double *ms, double *vs, double *ml,
                                     double *vl) {
   const int lane = threadIdx.x & 63;
-  const int32_t rounds = (nl + 63) / 64;
-  double sa_s = 0.0, sah_s = 0.0, sa_l = 0.0, sah_l = 0.0;
-  for (int32_t r = 0; r < rounds; ++r) {
-    const int32_t i = lane + 64 * r;
-    const int32_t slot = i < W ? (newest - i + W) % W : 0;
-    const float raw = ring_slot(rp, ring, W, slot);
+  // entry i's value less h1 (i < nl <= W)
+  auto entry = [&](int32_t i) {
+    int32_t slot = newest - i;
+    if (slot < 0) slot += W;
+    const float raw = ring_slot(rp, ring, W, i < W ? slot : 0);
+    return i == 0 ? 0.0 : double(raw) - double(h1);
+  };
+  // the first 64 entries stay in registers between the two passes
+  const double h0 = entry(lane), a0 = pow_int(delta, lane);
+  double sa_s = lane < ns ? a0 : 0.0, sa_l = lane < nl ? a0 : 0.0;
+  double sah_s = sa_s * h0, sah_l = sa_l * h0;
+  for (int32_t r = 64; r < nl; r += 64) {
+    const int32_t i = lane + r;
+    const double h = entry(i);
     if (i < nl) {
-      const double h = i == 0 ? 0.0 : double(raw) - double(h1);
       const double a = pow_int(delta, i);
       sa_l += a;
       sah_l += a * h;
@@ -102,13 +115,12 @@ __device__ inline void wave_windows(const RingPrefetch &rp, const float *ring, i
   sa_l = wave_sum_f64(sa_l);
   sah_l = wave_sum_f64(sah_l);
   const double mu_s = ns > 0 ? sah_s / sa_s : 0.0, mu_l = nl > 0 ? sah_l / sa_l : 0.0;
-  double sv_s = 0.0, sv_l = 0.0;
-  for (int32_t r = 0; r < rounds; ++r) {
-    const int32_t i = lane + 64 * r;
-    const int32_t slot = i < W ? (newest - i + W) % W : 0;
-    const float raw = ring_slot(rp, ring, W, slot);
+  const double ds0 = h0 - mu_s, dl0 = h0 - mu_l;
+  double sv_s = lane < ns ? a0 * ds0 * ds0 : 0.0, sv_l = lane < nl ? a0 * dl0 * dl0 : 0.0;
+  for (int32_t r = 64; r < nl; r += 64) {
+    const int32_t i = lane + r;
+    const double h = entry(i);
     if (i < nl) {
-      const double h = i == 0 ? 0.0 : double(raw) - double(h1);
       const double a = pow_int(delta, i);
       const double dl = h - mu_l;
       sv_l += a * dl * dl;
@@ -127,13 +139,14 @@ __device__ inline void wave_windows(const RingPrefetch &rp, const float *ring, i
 }
 
 // Signal update of one sequence by one wavefront (Sec. 3.1.2).  The sequence's
-// `s` KLD values are kld[first .. first + s) or, when kld is null (s <= 64),
-// the per-lane values `lane_kld` (lane j holds position j).  `rp` is the ring
+// `s` KLD values are the per-lane values `lane_kld` (lane j holds position j) and,
+// past 64, kld[first + 64 .. first + s) (kld may be null when s <= 64).  `rp` is the ring
 // state fetched by this wavefront; the ring is hist[0..W).  Returns the error
 // bits (DSDE_ERR_STATE, DSDE_ERR_SIGNAL); on error nothing is pushed and every
 // output is NaN.  Must be reached by the whole wavefront.
+template <int REGS>
 __device__ inline uint32_t wave_signal_update(int32_t s, int64_t first, const float *kld, float lane_kld,
-                                              const RingPrefetch &rp, float *ring, int32_t *head, int32_t *count,
+                                              const RingPrefetch<REGS> &rp, float *ring, int32_t *head, int32_t *count,
                                               int32_t W, int32_t n_short, int32_t n_long, float delta, float eps,
                                               float *mu_last, float *var_short, float *var_long, float *wvir,
                                               float *sf) {
@@ -143,11 +156,8 @@ __device__ inline uint32_t wave_signal_update(int32_t s, int64_t first, const fl
   if (hd < 0 || hd >= W || cnt < 0 || cnt > W) err |= DSDE_ERR_STATE;
   double mu = 0.0;
   if (!err && s > 0) {
-    double acc = 0.0;
-    if (kld)
-      for (int32_t j = lane; j < s; j += 64) acc += double(kld[first + j]);
-    else if (lane < s)
-      acc = double(lane_kld);
+    double acc = lane < s ? double(lane_kld) : 0.0;
+    for (int32_t j = lane + 64; j < s; j += 64) acc += double(kld[first + j]);
     acc = wave_sum_f64(acc);
     mu = acc / double(s);
     if (!isfinite(mu)) err |= DSDE_ERR_SIGNAL;
@@ -162,14 +172,14 @@ __device__ inline uint32_t wave_signal_update(int32_t s, int64_t first, const fl
     h1 = float(mu);
     // the older entries are read before lane 0 overwrites the slot below; the
     // pushed value itself is passed in registers
-    h = (h + 1) % W;
+    h = h + 1 < W ? h + 1 : 0;
     c = c < W ? c + 1 : W;
   } else {
-    const float newest_old = ring_slot(rp, ring, W, (h - 1 + W) % W);
+    const float newest_old = ring_slot(rp, ring, W, h > 0 ? h - 1 : W - 1);
     h1 = c > 0 ? newest_old : 0.0f;
     mu = c > 0 ? double(h1) : 0.0;
   }
-  const int32_t newest = (h - 1 + W) % W;
+  const int32_t newest = h > 0 ? h - 1 : W - 1;
   double ms, vs, ml, vl;
   wave_windows(rp, ring, W, newest, h1, n_short < c ? n_short : c, n_long < c ? n_long : c, double(delta), &ms, &vs,
                &ml, &vl);

@@ -101,6 +101,10 @@ __global__ __launch_bounds__(kSeqThreads) void seq_kernel(const StepParams P, co
   if (wave == 0 && lane < P.k_max) gz = P.gathered[slot0 + lane];
   const int32_t s = P.sl[b], first = P.cu_sl[b];
   const float T = P.temperature[b], ur = P.u_res[b];
+  RingPrefetch<1> rp{};
+  if constexpr (FUSED)
+    if (outputs && wave == kSignalWave)
+      rp = wave_ring_prefetch<1>(S.hist + int64_t(b) * S.W, S.head + b, S.count + b, S.W);
   // without a set-up kernel the outputs workgroup checks the whole layout, here
   // beside the first round trip; the streaming ones look only at what keeps
   // their own reads in bounds (their cells go unused when the layout is invalid)
@@ -158,6 +162,21 @@ __global__ __launch_bounds__(kSeqThreads) void seq_kernel(const StepParams P, co
                                     st_h, st_bad, st_arg);
   }
   __syncthreads();
+  // the outputs workgroup's last wavefront forms the KLD of every drafted
+  // position (lane j: position j), its draft entropy and row log-normalisers
+  // beside wavefront 0's acceptance, and writes them behind the barrier, where
+  // the error bits are known
+  double my_kl = 0.0, my_h = 0.0, lse_t = 0.0, lse_d = 0.0;
+  if (outputs && wave == kSignalWave && lane < s) {
+    const double sp = st_sp[lane], sq = st_sq[lane];
+    const double l2sp = log2_rowsum(sp), l2sq = log2_rowsum(sq);
+    // KL in log2 units: E_p[(z_t c - mt) - (z_d c - md)] - log2 S_p + log2 S_q
+    my_kl = (st_a[lane] * rcp_newton(sp) - l2sp + l2sq) * kLn2;
+    // draft entropy in log2 units: log2 S_q - E_q[z_d c - md]
+    my_h = (l2sq - st_h[lane] * rcp_newton(sq)) * kLn2;
+    lse_t = (double(st_mt[lane]) + l2sp) * kLn2;
+    lse_d = (double(st_md[lane]) + l2sq) * kLn2;
+  }
   if (wave == 0) {
     uint32_t err = 0;
     {  // per-sequence input checks
@@ -261,32 +280,18 @@ __global__ __launch_bounds__(kSeqThreads) void seq_kernel(const StepParams P, co
     return;
   }
   if (wave != kSignalWave) return;
-  // ---- the KLD of every drafted position (lane j: position j), its draft
-  // entropy and row log-normalisers, and in the fused step the signal update
-  // of Sec. 3.1.2 on those KLD values
-  // the ring state, fetched here: its round trip overlaps the KLD arithmetic
-  RingPrefetch rp{};
-  if constexpr (FUSED) rp = wave_ring_prefetch(S.hist + int64_t(b) * S.W, S.head + b, S.count + b, S.W);
+  // ---- the KLD outputs, and in the fused step the signal update of Sec. 3.1.2
+  // on those KLD values
   const uint32_t e_in = s_err_in, e_all = s_err;
-  float my_kld = NAN, my_h = NAN;
-  if (lane < s && !e_in) {
-    const double sp = st_sp[lane], sq = st_sq[lane];
-    const double l2sp = log2_rowsum(sp), l2sq = log2_rowsum(sq);
-    // KL in log2 units: E_p[(z_t c - mt) - (z_d c - md)] - log2 S_p + log2 S_q
-    const double kl = (st_a[lane] * rcp_newton(sp) - l2sp + l2sq) * kLn2;
-    // draft entropy in log2 units: log2 S_q - E_q[z_d c - md]
-    const double h = (l2sq - st_h[lane] * rcp_newton(sq)) * kLn2;
-    if (!e_all) {
-      my_kld = kl > 0.0 ? float(kl) : 0.0f;
-      my_h = float(h);
-    }
-    if (!st_bad[lane] && P.row_lse) {
-      P.row_lse[2 * (first + lane)] = (double(st_mt[lane]) + l2sp) * kLn2;
-      P.row_lse[2 * (first + lane) + 1] = (double(st_md[lane]) + l2sq) * kLn2;
+  const float my_kld = e_all ? NAN : my_kl > 0.0 ? float(my_kl) : 0.0f;
+  if (lane < s) {
+    P.kld[first + lane] = my_kld;
+    if (P.entropy) P.entropy[first + lane] = e_all ? NAN : float(my_h);
+    if (P.row_lse && !e_in && !st_bad[lane]) {
+      P.row_lse[2 * (first + lane)] = lse_t;
+      P.row_lse[2 * (first + lane) + 1] = lse_d;
     }
   }
-  if (lane < s) P.kld[first + lane] = my_kld;
-  if (lane < s && P.entropy) P.entropy[first + lane] = my_h;
   if constexpr (FUSED) {
     const uint32_t e = wave_signal_update(s, first, nullptr, my_kld, rp, S.hist + int64_t(b) * S.W, S.head + b,
                                           S.count + b, S.W, S.n_short, S.n_long, S.delta, S.eps, S.mu_last + b,
