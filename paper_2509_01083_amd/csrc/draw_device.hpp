@@ -109,6 +109,35 @@ __device__ __forceinline__ void fold_pair_stats(float &lmt, float &lmd, double &
   lmd = nd;
 }
 
+// The statistics of one row pair from the sets folded by the lanes of a group
+// of G (a lane without a part holds lmt = -inf): rescaled to the group's
+// largest reference shifts and summed, in every lane of the group.
+struct PairStats {
+  float mt, md;
+  double sp, sq, a, h;
+};
+template <int G>
+__device__ __forceinline__ PairStats group_pair_stats(float lmt, float lmd, double lsp, double lsq, double la,
+                                                      double lh) {
+  PairStats r;
+  r.mt = group_max<G>(lmt);
+  r.md = group_max<G>(lmd);
+  r.sp = r.sq = r.a = r.h = 0.0;
+  if (lmt != -INFINITY) {
+    const double dt = double(lmt) - double(r.mt), dd = double(lmd) - double(r.md);
+    const double ft = exp2_taylor(dt), fd = exp2_taylor(dd);
+    r.sp = lsp * ft;
+    r.sq = lsq * fd;
+    r.a = ft * (la + lsp * (dt - dd));
+    r.h = fd * (lh + lsq * dd);
+  }
+  r.sp = group_sum<G>(r.sp);
+  r.sq = group_sum<G>(r.sq);
+  r.a = group_sum<G>(r.a);
+  r.h = group_sum<G>(r.h);
+  return r;
+}
+
 // Combines the chunk partials of every drafted pair of one sequence (stored
 // under slots slot0 + j): groups of G lanes, one pair per group, lane g of a
 // group folds chunks g, g + G, ...  Results go to LDS (st_*[j] for position j;
@@ -152,20 +181,7 @@ __device__ inline void combine_pairs(const PairChunk *__restrict__ part, int64_t
         }
       }
     }
-    const float mt = group_max<G>(lmt), md = group_max<G>(lmd);
-    double tsp = 0.0, tsq = 0.0, ta = 0.0, th = 0.0;
-    if (lmt != -INFINITY) {
-      const double dt = double(lmt) - double(mt), dd = double(lmd) - double(md);
-      const double ft = exp2_taylor(dt), fd = exp2_taylor(dd);
-      tsp = lsp * ft;
-      tsq = lsq * fd;
-      ta = ft * (la + lsp * (dt - dd));
-      th = fd * (lh + lsq * dd);
-    }
-    tsp = group_sum<G>(tsp);
-    tsq = group_sum<G>(tsq);
-    ta = group_sum<G>(ta);
-    th = group_sum<G>(th);
+    const PairStats r = group_pair_stats<G>(lmt, lmd, lsp, lsq, la, lh);
     int32_t arg = 0x7fffffff;
     float zm = -INFINITY;
     if (chunk_arg) {  // the row argmax: smallest token among the chunks holding the row maximum
@@ -174,13 +190,13 @@ __device__ inline void combine_pairs(const PairChunk *__restrict__ part, int64_t
       arg = lanes::group_reduce<G>(arg, lanes::Min{});
     }
     if (j < s && g == 0) {
-      st_mt[j] = mt;
-      st_md[j] = md;
-      st_sp[j] = tsp;
-      st_sq[j] = tsq;
-      st_a[j] = ta;
-      st_h[j] = th;
-      st_bad[j] = !(isfinite(mt) && isfinite(md) && isfinite(tsp) && isfinite(tsq) && isfinite(ta));
+      st_mt[j] = r.mt;
+      st_md[j] = r.md;
+      st_sp[j] = r.sp;
+      st_sq[j] = r.sq;
+      st_a[j] = r.a;
+      st_h[j] = r.h;
+      st_bad[j] = !(isfinite(r.mt) && isfinite(r.md) && isfinite(r.sp) && isfinite(r.sq) && isfinite(r.a));
       st_arg[j] = arg;
       if (st_zmax) st_zmax[j] = zm;
     }

@@ -86,11 +86,16 @@ __device__ __forceinline__ T row_reduce(T v, OP op) {
   return v;
 }
 
-// The combination over aligned groups of G lanes (G = 16, 32 or 64), in every
-// lane of the group.
+// The combination over aligned groups of G lanes (G = 8, 16, 32 or 64), in
+// every lane of the group.
 template <int G, typename T, typename OP>
 __device__ __forceinline__ T group_reduce(T v, OP op) {
-  static_assert(G == 16 || G == 32 || G == 64, "groups of 16, 32 or 64 lanes");
+  static_assert(G == 8 || G == 16 || G == 32 || G == 64, "groups of 8, 16, 32 or 64 lanes");
+  if constexpr (G == 8) {
+    v = op(v, dpp<kQuadSwap1>(v));
+    v = op(v, dpp<kQuadSwap2>(v));
+    return op(v, dpp<kRowHalfMirror>(v));
+  }
   v = row_reduce(v, op);
   if constexpr (G == 16) return v;
   const T r0 = readlane(v, 0), r1 = readlane(v, 16), r2 = readlane(v, 32), r3 = readlane(v, 48);

@@ -8,12 +8,11 @@
 //           so tokens outside it gather nothing), then shard_combine_kernel:
 //           the chunk partials of each drafted pair folded into one slice
 //           partial.
-//   call 2  shard_accept_kernel: one wavefront per sequence folds the G slice
-//           partials in shard order (fp64), then KLD, acceptance and the draw
-//           job exactly as the per-sequence kernel of dsde_verify; fused
-//           (dsde_shard_accept_step), the same wavefront then runs the signal
-//           update on those KLD values, and the SL rule follows as in
-//           dsde_step.
+//   call 2  shard_accept_kernel: one workgroup per sequence combines the G
+//           slice partials (fp64), a group of lanes per position, then KLD,
+//           acceptance and the draw job exactly as the per-sequence kernel of
+//           dsde_verify; fused (dsde_shard_accept_step), it also runs the
+//           signal update on those KLD values, and the SL rule follows.
 //   call 3  shard_mass_kernel: one workgroup per sequence streams the draw
 //           row(s) of its slice once, keeps the unit cells in the workspace
 //           and reports the slice's mass.
@@ -104,23 +103,38 @@ __global__ __launch_bounds__(kShardThreads) void shard_combine_kernel(
 
 // ---- call 2 --------------------------------------------------------------
 
-// One wavefront per sequence; lane j holds drafted position j.
-template <bool FUSED>
-__global__ __launch_bounds__(64) void shard_accept_kernel(
+// One workgroup per sequence; GL lanes per drafted position, one slice partial
+// per lane (slices g, g + GL, ... when there are more), so that all partials
+// arrive in one round trip.  Folding the slices one after another in the lane
+// of their position took a round trip and four exponentials per slice: 11.2 us
+// at 256 sequences and 8 slices, against 7.3 us in groups.  Wavefront 0 then
+// decides the acceptance while the last one forms the KLD.
+template <int GL, bool FUSED>
+__global__ __launch_bounds__(kShardThreads) void shard_accept_kernel(
     int32_t G, const dsde_shard_partial *__restrict__ parts, int64_t N, int64_t V, int32_t k_max,
     const int32_t *__restrict__ sl, const int32_t *__restrict__ cu_sl, const int32_t *__restrict__ draft_tokens,
     const float *__restrict__ temperature, const float *__restrict__ u_acc, const float *__restrict__ u_res,
     int32_t pad_id, int32_t *__restrict__ accepted, int32_t *__restrict__ tokens, float *__restrict__ kld,
     double *__restrict__ row_lse, float *__restrict__ entropy, DrawJob *__restrict__ jobs,
     uint32_t *__restrict__ seq_err, const SignalArgs S) {
-  const int lane = threadIdx.x;
+  __shared__ PairStats st[DSDE_MAX_K + 1];
+  __shared__ float st_zt[DSDE_MAX_K + 1], st_zd[DSDE_MAX_K + 1];
+  __shared__ int32_t st_owners[DSDE_MAX_K + 1], st_arg[DSDE_MAX_K + 1], st_bad[DSDE_MAX_K + 1];
+  __shared__ uint32_t s_err_in, s_err;
+  constexpr int kLast = kShardWaves - 1;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int32_t b = blockIdx.x;
   const int32_t width = k_max + 1;
   int32_t *tok = tokens + int64_t(b) * width;
-  uint32_t err = seq_err[b];
-  if (err & DSDE_ERR_LAYOUT) {
-    if (lane < width) tok[lane] = pad_id;
-    if (lane == 0) {
+  const uint32_t err0 = seq_err[b];
+  const int32_t s = sl[b], first = cu_sl[b];
+  const float T = temperature[b], ur = u_res[b];
+  RingPrefetch<4> rp{};  // the ring state, in flight while the slices are combined
+  if constexpr (FUSED)
+    if (wave == kLast) rp = wave_ring_prefetch<4>(S.hist + int64_t(b) * S.W, S.head + b, S.count + b, S.W);
+  if (err0 & DSDE_ERR_LAYOUT) {
+    if (t < width) tok[t] = pad_id;
+    if (t == 0) {
       accepted[b] = 0;
       DrawJob j{};
       j.kind = -1;
@@ -129,116 +143,117 @@ __global__ __launch_bounds__(64) void shard_accept_kernel(
     }
     return;
   }
-  const int32_t s = sl[b], first = cu_sl[b];
-  const float T = temperature[b], ur = u_res[b];
-  RingPrefetch<4> rp{};  // the ring state, in flight while the slices are folded
-  if constexpr (FUSED) rp = wave_ring_prefetch<4>(S.hist + int64_t(b) * S.W, S.head + b, S.count + b, S.W);
   const bool greedy = T == 0.0f;
   int32_t x = 0;
   float u = 0.f;
-  if (lane < s) {
+  if (wave == 0 && lane < s) {
     x = draft_tokens[first + lane];
     u = u_acc[first + lane];
   }
-  // the slices in shard order: the statistics folded as the chunk partials are,
-  // the drafted token's logits from the one slice holding it, and (greedy) the
-  // row maximum of the first slice that reaches it
-  float mt = -INFINITY, md = -INFINITY, zt = 0.f, zd = 0.f, zbest = -INFINITY;
-  double sp = 0.0, sq = 0.0, a = 0.0, h = 0.0;
-  int32_t owners = 0, abest = 0x7fffffff;
-  int bad = 0;
-  if (lane < s) {
-    for (int32_t g = 0; g < G; ++g) {
-      const dsde_shard_partial p = parts[int64_t(g) * N + first + lane];
-      bad |= p.bad;
-      if (p.has_token) {
-        ++owners;
-        zt = p.zt;
-        zd = p.zd;
-      }
-      if (greedy && (abest == 0x7fffffff || p.zmax > zbest)) {
-        zbest = p.zmax;
-        abest = p.argmax;
-      }
-      if (g == 0) {
-        mt = p.mt;
-        md = p.md;
-        sp = p.sp;
-        sq = p.sq;
-        a = p.a;
-        h = p.h;
-      } else {
-        fold_pair_stats(mt, md, sp, sq, a, h, p.mt, p.md, p.sp, p.sq, p.a, p.h);
+  // the slices of each position: the statistics combined as the chunk partials
+  // are, the drafted token's logits from the one slice holding it, and (greedy)
+  // the row maximum with its smallest token
+  constexpr int kPos = 64 / GL;
+  for (int32_t base = 0; base < s; base += kShardWaves * kPos) {
+    const int32_t j = base + wave * kPos + lane / GL;
+    PairStats l{-INFINITY, -INFINITY, 0.0, 0.0, 0.0, 0.0};
+    float zt = 0.f, zd = 0.f, zbest = -INFINITY;
+    int32_t owners = 0, abest = 0x7fffffff, bad = 0;
+    if (j < s) {
+      for (int32_t g = lane % GL; g < G; g += GL) {
+        const dsde_shard_partial p = parts[int64_t(g) * N + first + j];
+        bad |= p.bad;
+        if (p.has_token) {
+          ++owners;
+          zt = p.zt;
+          zd = p.zd;
+        }
+        if (abest == 0x7fffffff || p.zmax > zbest) {  // slices in ascending order: on ties the earlier wins
+          zbest = p.zmax;
+          abest = p.argmax;
+        }
+        if (l.mt == -INFINITY)
+          l = PairStats{p.mt, p.md, p.sp, p.sq, p.a, p.h};
+        else
+          fold_pair_stats(l.mt, l.md, l.sp, l.sq, l.a, l.h, p.mt, p.md, p.sp, p.sq, p.a, p.h);
       }
     }
-    bad |= !(isfinite(mt) && isfinite(md) && isfinite(sp) && isfinite(sq) && isfinite(a));
-  }
-  {  // per-sequence input checks, as in dsde_verify; a token held by no slice or by several
-    uint32_t e = 0;
-    if (lane < s) {
-      if (x < 0 || int64_t(x) >= V || owners != 1) e |= DSDE_ERR_TOKEN;
-      if (!greedy && !(u >= 0.0f && u < 1.0f)) e |= DSDE_ERR_UNIFORM;
-    }
-    if (lane == 0 && !greedy) {
-      if (!(T >= kMinTemp && T <= kMaxTemp)) e |= DSDE_ERR_TEMP;
-      if (!(ur >= 0.0f && ur < 1.0f)) e |= DSDE_ERR_UNIFORM;
-    }
-    err |= lanes::wave_or(e);
-  }
-  const uint32_t e_in = err;
-  const float c = greedy ? kLog2e : kLog2e / T;  // the scale of the statistics pass
-  bool ok = false;
-  float my_kld = NAN, my_h = NAN, my_isp = 0.f, my_isq = 0.f;
-  double l2sp = 0.0, l2sq = 0.0;
-  if (lane < s && !e_in) {
-    const double rsp = rcp_newton(sp), rsq = rcp_newton(sq);
-    my_isp = float(rsp);
-    my_isq = float(rsq);
+    const PairStats r = group_pair_stats<GL>(l.mt, l.md, l.sp, l.sq, l.a, l.h);
+    owners = lanes::group_reduce<GL>(owners, lanes::Add{});
+    bad = lanes::group_reduce<GL>(bad, lanes::Or{});
+    // one owner: the other lanes add zeros (several owners are an error)
+    zt = lanes::group_reduce<GL>(zt, lanes::Add{});
+    zd = lanes::group_reduce<GL>(zd, lanes::Add{});
+    int32_t arg = 0x7fffffff;
     if (greedy) {
-      ok = x == abest;
-    } else {
-      // u < p(x) / q(x), tested as u S_p < 2^D S_q (as in dsde_verify)
-      const double D = (double(zt) * double(c) - double(mt)) - (double(zd) * double(c) - double(md));
-      ok = double(u) * sp < exp2_taylor(D) * sq;
+      const float zm = group_max<GL>(zbest);
+      arg = abest != 0x7fffffff && zbest == zm ? abest : 0x7fffffff;
+      arg = lanes::group_reduce<GL>(arg, lanes::Min{});
     }
-    l2sp = log2_rowsum(sp);
-    l2sq = log2_rowsum(sq);
-    const double kl = (a * rsp - l2sp + l2sq) * kLn2;
-    my_kld = kl > 0.0 ? float(kl) : 0.0f;
-    my_h = float((l2sq - h * rsq) * kLn2);
-  }
-  if (__ballot(bad)) err |= DSDE_ERR_LOGIT;
-  const uint64_t mask = __ballot(ok);
-  int32_t acc = int32_t(__builtin_ctzll(~mask));
-  if (acc > s) acc = s;
-  if (err) {
-    acc = 0;
-    my_kld = NAN;
-    my_h = NAN;
-  }
-  if (lane < s) {
-    kld[first + lane] = my_kld;
-    if (entropy) entropy[first + lane] = my_h;
-    if (row_lse && !e_in && !bad) {
-      row_lse[2 * (first + lane)] = (double(mt) + l2sp) * kLn2;
-      row_lse[2 * (first + lane) + 1] = (double(md) + l2sq) * kLn2;
+    if (j < s && lane % GL == 0) {
+      st[j] = r;
+      st_zt[j] = zt;
+      st_zd[j] = zd;
+      st_owners[j] = owners;
+      st_arg[j] = arg;
+      st_bad[j] = bad || !(isfinite(r.mt) && isfinite(r.md) && isfinite(r.sp) && isfinite(r.sq) && isfinite(r.a));
     }
   }
-  // fused: the signal update of the sequence on the KLD values just formed;
-  // its error bits join seq_err but, as in the separate calls, leave the
-  // acceptance and the draw alone
-  uint32_t e_sig = 0;
-  if constexpr (FUSED)
-    e_sig = wave_signal_update(s, first, nullptr, my_kld, rp, S.hist + int64_t(b) * S.W, S.head + b, S.count + b,
-                               S.W, S.n_short, S.n_long, S.delta, S.eps, S.mu_last + b, S.var_short + b,
-                               S.var_long + b, S.wvir + b, S.sf + b);
-  if (lane < width) tok[lane] = lane < acc ? x : pad_id;
-  const float a_mt = lanes::readlane(mt, acc), a_md = lanes::readlane(md, acc);
-  const float a_isp = lanes::readlane(my_isp, acc), a_isq = lanes::readlane(my_isq, acc);
-  const int32_t a_arg = lanes::readlane(abest, acc);
-  if (lane == 0) {
-    accepted[b] = acc;
-    seq_err[b] = err | e_sig;
+  __syncthreads();
+  double my_kl = 0.0, my_h = 0.0, lse_t = 0.0, lse_d = 0.0;
+  if (wave == kLast && lane < s) {
+    const PairStats r = st[lane];
+    const double l2sp = log2_rowsum(r.sp), l2sq = log2_rowsum(r.sq);
+    my_kl = (r.a * rcp_newton(r.sp) - l2sp + l2sq) * kLn2;
+    my_h = (l2sq - r.h * rcp_newton(r.sq)) * kLn2;
+    lse_t = (double(r.mt) + l2sp) * kLn2;
+    lse_d = (double(r.md) + l2sq) * kLn2;
+  }
+  if (wave == 0) {
+    uint32_t err = err0;
+    {  // per-sequence input checks, as in dsde_verify; a token held by no slice or by several
+      uint32_t e = 0;
+      if (lane < s) {
+        if (x < 0 || int64_t(x) >= V || st_owners[lane] != 1) e |= DSDE_ERR_TOKEN;
+        if (!greedy && !(u >= 0.0f && u < 1.0f)) e |= DSDE_ERR_UNIFORM;
+      }
+      if (lane == 0 && !greedy) {
+        if (!(T >= kMinTemp && T <= kMaxTemp)) e |= DSDE_ERR_TEMP;
+        if (!(ur >= 0.0f && ur < 1.0f)) e |= DSDE_ERR_UNIFORM;
+      }
+      err |= lanes::wave_or(e);
+    }
+    if (lane == 0) s_err_in = err;
+    const float c = greedy ? kLog2e : kLog2e / T;  // the scale of the statistics pass
+    bool ok = false, bad = false;
+    float mt = 0.f, md = 0.f, isp = 0.f, isq = 0.f;
+    int32_t arg = 0;
+    if (lane < s) {
+      bad = st_bad[lane] != 0;
+      mt = st[lane].mt;
+      md = st[lane].md;
+      arg = st_arg[lane];
+      const double sp = st[lane].sp, sq = st[lane].sq;
+      isp = float(rcp_newton(sp));
+      isq = float(rcp_newton(sq));
+      if (err) {
+        ok = false;
+      } else if (greedy) {
+        ok = x == arg;
+      } else {
+        // u < p(x) / q(x), tested as u S_p < 2^D S_q (as in dsde_verify)
+        const double D = (double(st_zt[lane]) * double(c) - double(mt)) - (double(st_zd[lane]) * double(c) - double(md));
+        ok = double(u) * sp < exp2_taylor(D) * sq;
+      }
+    }
+    if (__ballot(bad)) err |= DSDE_ERR_LOGIT;
+    const uint64_t mask = __ballot(ok);
+    int32_t acc = int32_t(__builtin_ctzll(~mask));
+    if (acc > s) acc = s;
+    if (err) acc = 0;
+    const float a_mt = lanes::readlane(mt, acc), a_md = lanes::readlane(md, acc);
+    const float a_isp = lanes::readlane(isp, acc), a_isq = lanes::readlane(isq, acc);
+    const int32_t a_arg = lanes::readlane(arg, acc);
     DrawJob j{};
     j.kind = -1;
     j.accepted = acc;
@@ -248,7 +263,6 @@ __global__ __launch_bounds__(64) void shard_accept_kernel(
       if (acc < s) {  // the argmax of the first rejected row is known already
         j.kind = 2;
         j.token = a_arg;
-        tok[acc] = a_arg;
       } else {
         j.kind = 3;
       }
@@ -269,7 +283,34 @@ __global__ __launch_bounds__(64) void shard_accept_kernel(
         j.draft_row = -1;
       }
     }
-    jobs[b] = j;
+    if (lane < width) tok[lane] = lane < acc ? x : j.kind == 2 && lane == acc ? j.token : pad_id;
+    if (lane == 0) {
+      accepted[b] = acc;
+      jobs[b] = j;
+      s_err = err;
+      seq_err[b] = err;
+    }
+  }
+  __syncthreads();
+  if (wave != kLast) return;
+  const uint32_t e_in = s_err_in, e_all = s_err;
+  const float my_kld = e_all ? NAN : my_kl > 0.0 ? float(my_kl) : 0.0f;
+  if (lane < s) {
+    kld[first + lane] = my_kld;
+    if (entropy) entropy[first + lane] = e_all ? NAN : float(my_h);
+    if (row_lse && !e_in && !st_bad[lane]) {
+      row_lse[2 * (first + lane)] = lse_t;
+      row_lse[2 * (first + lane) + 1] = lse_d;
+    }
+  }
+  // fused: the signal update of the sequence on the KLD values just formed;
+  // its error bits join seq_err but, as in the separate calls, leave the
+  // acceptance and the draw alone
+  if constexpr (FUSED) {
+    const uint32_t e = wave_signal_update(s, first, nullptr, my_kld, rp, S.hist + int64_t(b) * S.W, S.head + b,
+                                          S.count + b, S.W, S.n_short, S.n_long, S.delta, S.eps, S.mu_last + b,
+                                          S.var_short + b, S.var_long + b, S.wvir + b, S.sf + b);
+    if (e && lane == 0) seq_err[b] = e_all | e;
   }
 }
 
@@ -337,7 +378,13 @@ __global__ __launch_bounds__(kShardThreads) void shard_pick_kernel(
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int32_t b = blockIdx.x;
+  // one round trip: the job, the first 64 slices' masses (lane g: slice g) and
+  // the first 64 cells, whatever of them the job needs
+  const UnitCells cells{sub + int64_t(b) * nu * kSubs, ref + int64_t(b) * nu};
+  const dsde_shard_mass mass0 = masses[int64_t(lane < G ? lane : G - 1) * B + b];
+  UnitCell cell0 = load_cell(cells, lane, nu, true);
   const DrawJob job = uniform_job(jobs[b]);
+  auto mass_of = [&](int32_t g) -> dsde_shard_mass { return g < 64 ? mass0 : masses[int64_t(g) * B + b]; };
   const int32_t width = k_max + 1;
   int32_t *tok = tokens + int64_t(b) * width;
   if (job.kind < 0 || job.kind == 2) {  // flagged, or a greedy token already emitted
@@ -360,7 +407,7 @@ __global__ __launch_bounds__(kShardThreads) void shard_pick_kernel(
     int32_t bg = 0x7fffffff;
     int bd = 0;
     for (int32_t g = lane; g < G; g += 64) {
-      const dsde_shard_mass q = masses[int64_t(g) * B + b];
+      const dsde_shard_mass q = mass_of(g);
       bd |= q.bad;
       if (bg == 0x7fffffff || q.zmax > best) {
         best = q.zmax;
@@ -386,7 +433,7 @@ __global__ __launch_bounds__(kShardThreads) void shard_pick_kernel(
   if (mode == 2) {
     int bd = 0;
     for (int32_t g = lane; g < G; g += 64) {
-      const dsde_shard_mass q = masses[int64_t(g) * B + b];
+      const dsde_shard_mass q = mass_of(g);
       bd |= q.bad;
       ref_max = fmaxf(ref_max, q.ref);
     }
@@ -397,7 +444,7 @@ __global__ __launch_bounds__(kShardThreads) void shard_pick_kernel(
     }
   }
   auto weight = [&](int32_t g, int md) -> double {
-    const dsde_shard_mass q = masses[int64_t(g) * B + b];
+    const dsde_shard_mass q = mass_of(g);
     return md == 0 ? q.mass : md == 1 ? q.p_mass : q.mass * exp2_taylor(double(q.ref) - double(ref_max));
   };
   double acc = 0.0;
@@ -438,13 +485,12 @@ __global__ __launch_bounds__(kShardThreads) void shard_pick_kernel(
   const size_t esz = DT == DSDE_BF16 ? 2 : 4;
   const char *trow = (const char *)target + size_t(job.target_row) * size_t(V) * esz;
   const char *drow = job.draft_row >= 0 ? (const char *)draft + size_t(job.draft_row) * size_t(V) * esz : nullptr;
-  const UnitCells cells{sub + int64_t(b) * nu * kSubs, ref + int64_t(b) * nu};
   if (mode == 1) {  // the slice's p totals, which call 3 did not keep
     for (int32_t u = wave; u < nu; u += kShardWaves) target_p_unit<DT, ROW>(trow, V, u, job, cells);
     __syncthreads();
+    cell0 = load_cell(cells, lane, nu, false);
   }
   if (wave != 0) return;
-  const UnitCell cell0 = load_cell(cells, lane, nu, mode == 2);
   const int32_t local = draw_in_row<DT, ROW>(cells, nu, cell0, row_ref, rem, trow, drow, V, mode, job);
   if (lane == 0) {
     const int32_t token = int32_t(v_begin + local);
@@ -517,17 +563,29 @@ int launch_shard_accept(int32_t G, const dsde_shard_partial *parts, int64_t V, i
                         dsde_draw_job *jobs, uint32_t *seq_err, const SignalArgs *signal, hipStream_t stream) {
   (void)hipGetLastError();
   DrawJob *dj = reinterpret_cast<DrawJob *>(jobs);
-  if (!signal) {
-    shard_accept_kernel<false><<<dim3(unsigned(B)), dim3(64), 0, stream>>>(
-        G, parts, N, V, k_max, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, pad_id, accepted, tokens, kld,
-        row_lse, draft_entropy, dj, seq_err, SignalArgs{});
-    return hipGetLastError() == hipSuccess ? DSDE_OK : DSDE_DEVICE_ERROR;
-  }
-  const SignalArgs &S = *signal;
-  shard_accept_kernel<true><<<dim3(unsigned(B)), dim3(64), 0, stream>>>(
-      G, parts, N, V, k_max, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, pad_id, accepted, tokens, kld,
-      row_lse, draft_entropy, dj, seq_err, S);
+  const SignalArgs S = signal ? *signal : SignalArgs{};
+  auto run = [&](auto kernel) {
+    kernel<<<dim3(unsigned(B)), dim3(kShardThreads), 0, stream>>>(G, parts, N, V, k_max, sl, cu_sl, draft_tokens,
+                                                                  temperature, u_acc, u_res, pad_id, accepted, tokens,
+                                                                  kld, row_lse, draft_entropy, dj, seq_err, S);
+  };
+  auto pick = [&](auto fused) {
+    constexpr bool F = decltype(fused)::value;
+    if (G <= 8)
+      run(shard_accept_kernel<8, F>);
+    else if (G <= 16)
+      run(shard_accept_kernel<16, F>);
+    else if (G <= 32)
+      run(shard_accept_kernel<32, F>);
+    else
+      run(shard_accept_kernel<64, F>);
+  };
+  if (signal)
+    pick(std::true_type{});
+  else
+    pick(std::false_type{});
   if (hipGetLastError() != hipSuccess) return DSDE_DEVICE_ERROR;
+  if (!signal) return DSDE_OK;
   return launch_next_sl(B, S.sf, S.wvir, S.sl_max, S.sl_min, S.sl_hi, S.budget, S.sl_hat, S.sl_cap, S.sl_next,
                         seq_err, true, stream);
 }

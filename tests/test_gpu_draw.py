@@ -117,3 +117,17 @@ def test_row_alignment_changes_no_bit(gpu_lib, V, dtype):
             if x.dtype.is_floating_point:
                 x, y = x.view(torch.uint8), y.view(torch.uint8)
             assert torch.equal(x, y), f"{k} differs at offsets {a}, {b}"
+
+
+@pytest.mark.parametrize("G", [8, 9, 17, 33, 65])
+def test_shard_counts_around_the_group_sizes(gpu_lib, G):
+    """The sharded acceptance gives each position a group of 8, 16, 32 or 64
+    lanes, one slice per lane; more slices than lanes take several each."""
+    from tests.test_gpu_shard import check_sharded
+    rng = np.random.default_rng(G)
+    V = 16 * G + 3
+    sls = [5, 0, 1, 40, 3]
+    target, draft, tokens, u_acc, u_res = random_arrays(rng, sls, V, sigma=1.0, noise=0.3)
+    step = step_from_arrays(target, draft, sls, tokens, [1.0, 0.7, 0.0, 1.3, 0.0], u_acc, u_res, 40)
+    bounds = [16 * g for g in range(G)] + [V]
+    check_sharded(gpu_lib, step, list(zip(bounds[:-1], bounds[1:])), f"{G} slices")
