@@ -1,10 +1,11 @@
 """DSDE speculative-verification hot path on MI355X (gfx950).
 
 Python binding of libdsde.so (declared in include/dsde.h): the same entry
-points, taking torch tensors that already live on the GPU.  This module only
-checks shapes/dtypes and marshals pointers and the current HIP stream; every
-step of the computation runs in the library's HIP kernels.  There is no CPU
-fallback: if the library is missing, ``load`` raises.
+points, taking torch tensors that already live on the GPU.  This module makes
+missing output buffers; _binding.so (csrc/binding.cpp) checks shapes/dtypes and
+marshals pointers and the current HIP stream; every step of the computation
+runs in the library's HIP kernels.  There is no CPU fallback: if a library is
+missing, ``load`` or the first call raises.
 """
 import ctypes
 import os
@@ -28,6 +29,7 @@ EXPORTS = ("dsde_abi_version", "dsde_status_string", "dsde_verify_workspace_byte
 SHARD_PARTIAL_BYTES, DRAW_JOB_BYTES, SHARD_MASS_BYTES = 64, 44, 32
 
 _lib = None
+_native = None  # _binding, once it is loaded
 
 
 class DsdeError(RuntimeError):
@@ -91,6 +93,25 @@ def load(path: str = LIB_PATH):
     return lib
 
 
+def _bind():
+    """The marshalling extension (built beside libdsde.so); raises when it is absent."""
+    global _native
+    if _native is None:
+        load()
+        try:
+            from . import _binding
+        except ImportError as e:
+            raise DsdeError(f"_binding.so: {e}: build it with __graft_entry__.build()") from e
+        _binding.set_error(DsdeError)
+        _native = _binding
+    return _native
+
+
+def _handle(stream):
+    """Raw handle of a torch stream; None stands for the current one."""
+    return None if stream is None else stream.cuda_stream
+
+
 def _check(rc):
     if rc != OK:
         raise DsdeError(f"libdsde: {load().dsde_status_string(rc).decode()} (status {rc})")
@@ -126,100 +147,68 @@ def new_workspace(B, N, V, k_max, device="cuda"):
     return torch.empty(n, dtype=torch.uint8, device=device)
 
 
+def _new_verify_out(B, N, k_max, dev):
+    return {"accepted": torch.empty(B, dtype=torch.int32, device=dev),
+            "tokens": torch.empty((B, k_max + 1), dtype=torch.int32, device=dev),
+            "kld": torch.empty(max(N, 1), dtype=torch.float32, device=dev)[:N]}
+
+
+def _new_signal_out(out, B, dev):
+    """Adds the signal's and the SL rule's outputs that ``out`` does not hold yet."""
+    for k in ("mu_last", "var_short", "var_long", "wvir", "sf", "sl_hat"):
+        if k not in out:
+            out[k] = torch.empty(B, dtype=torch.float32, device=dev)
+    if "sl_cap" not in out:
+        out["sl_cap"] = torch.empty(1, dtype=torch.float32, device=dev)
+    if "sl_next" not in out:
+        out["sl_next"] = torch.empty(B, dtype=torch.int32, device=dev)
+
+
+def _rows(draft):
+    return int(draft.shape[0]) if draft is not None else 0
+
+
+def _with_entropy(out, wanted, N, dev):
+    if wanted and "draft_entropy" not in out:
+        out["draft_entropy"] = torch.empty(max(N, 1), dtype=torch.float32, device=dev)[:N]
+
+
 def verify(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, pad_id=-1,
            out=None, workspace=None, row_lse=None, draft_entropy=False, stream=None):
     """``dsde_verify`` on torch tensors.  Returns a dict with accepted, tokens, kld,
     seq_err (and draft_entropy when asked for); pass ``out`` (a dict with those
     keys) to reuse output buffers."""
-    lib = load()
-    dt = _logits_dtype(target)
-    V = int(target.shape[1])
-    B = int(sl.shape[0])
-    N = int(draft.shape[0]) if draft is not None else 0
-    dev = target.device
-    if draft is not None and (draft.dtype != target.dtype or (N > 0 and int(draft.shape[1]) != V)):
-        raise DsdeError("draft logits must match the target's dtype and vocabulary")
-    if int(target.shape[0]) != N + B:
-        raise DsdeError(f"target has {target.shape[0]} rows, expected N + B = {N + B}")
+    native = _native or _bind()
     if out is None:
-        out = {"accepted": torch.empty(B, dtype=torch.int32, device=dev),
-               "tokens": torch.empty((B, k_max + 1), dtype=torch.int32, device=dev),
-               "kld": torch.empty(max(N, 1), dtype=torch.float32, device=dev)[:N],
-               "seq_err": torch.empty(B, dtype=torch.int32, device=dev)}
-    if draft_entropy and "draft_entropy" not in out:
-        out["draft_entropy"] = torch.empty(max(N, 1), dtype=torch.float32, device=dev)[:N]
-    ent = out.get("draft_entropy") if draft_entropy else None
+        B = int(sl.shape[0])
+        out = _new_verify_out(B, _rows(draft), k_max, target.device)
+        out["seq_err"] = torch.empty(B, dtype=torch.int32, device=target.device)
+    if draft_entropy:
+        _with_entropy(out, True, _rows(draft), target.device)
     if workspace is None:
-        workspace = new_workspace(B, N, V, k_max, device=dev)
-    rc = lib.dsde_verify(
-        _ptr(target, name="target"), _ptr(draft, name="draft") if N > 0 else None, dt, V, B, N, k_max,
-        _ptr(sl, torch.int32, B, "sl"), _ptr(cu_sl, torch.int32, B + 1, "cu_sl"),
-        _ptr(draft_tokens, torch.int32, N, "draft_tokens") if N > 0 else None,
-        _ptr(temperature, torch.float32, B, "temperature"),
-        _ptr(u_acc, torch.float32, N, "u_acc") if N > 0 else None,
-        _ptr(u_res, torch.float32, B, "u_res"), int(pad_id),
-        _ptr(out["accepted"], torch.int32, B, "accepted"),
-        _ptr(out["tokens"], torch.int32, B * (k_max + 1), "tokens"),
-        _ptr(out["kld"], torch.float32, N, "kld") if N > 0 else None,
-        _ptr(out["seq_err"], None, B, "seq_err"),
-        _ptr(row_lse, torch.float64, 2 * N, "row_lse") if row_lse is not None else None,
-        _ptr(ent, torch.float32, N, "draft_entropy") if ent is not None and N > 0 else None,
-        _ptr(workspace, torch.uint8, None, "workspace"), workspace.numel(), _stream(stream))
-    _check(rc)
+        workspace = new_workspace(int(sl.shape[0]), _rows(draft), int(target.shape[1]), k_max, device=target.device)
+    native.verify(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, int(pad_id), out, row_lse,
+                  draft_entropy, workspace, _handle(stream))
     return out
 
 
-def _logits_dtype(target):
-    if target.dtype == torch.bfloat16:
-        return BF16
-    if target.dtype == torch.float32:
-        return FP32
-    raise DsdeError("logits must be bfloat16 or float32")
-
-
-def _step_args(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, hist, head, count,
-               sl_max, n_short, n_long, delta, eps, sl_min, sl_hi, pad_id, out, row_lse, draft_entropy, budget):
-    """Marshalled arguments of dsde_step up to seq_err (shared with dsde_step_static), and the outputs."""
-    dt = _logits_dtype(target)
-    V = int(target.shape[1])
-    B = int(sl.shape[0])
-    N = int(draft.shape[0]) if draft is not None else 0
-    W = int(hist.shape[1])
-    sl_hi = k_max if sl_hi is None else sl_hi
-    dev = target.device
-    if int(target.shape[0]) != N + B:
-        raise DsdeError(f"target has {target.shape[0]} rows, expected N + B = {N + B}")
+def _step(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, hist, head, count, sl_max,
+          n_short, n_long, delta, eps, sl_min, sl_hi, pad_id, out, workspace, row_lse, draft_entropy, budget, stream):
+    """dsde_step, or with ``workspace`` False dsde_step_static."""
+    native = _native or _bind()
     if out is None:
-        out = {"accepted": torch.empty(B, dtype=torch.int32, device=dev),
-               "tokens": torch.empty((B, k_max + 1), dtype=torch.int32, device=dev),
-               "kld": torch.empty(max(N, 1), dtype=torch.float32, device=dev)[:N],
-               "seq_err": torch.empty(B, dtype=torch.int32, device=dev),
-               "sl_cap": torch.empty(1, dtype=torch.float32, device=dev),
-               "sl_next": torch.empty(B, dtype=torch.int32, device=dev)}
-        for k in ("mu_last", "var_short", "var_long", "wvir", "sf", "sl_hat"):
-            out[k] = torch.empty(B, dtype=torch.float32, device=dev)
-    if draft_entropy and "draft_entropy" not in out:
-        out["draft_entropy"] = torch.empty(max(N, 1), dtype=torch.float32, device=dev)[:N]
-    ent = out.get("draft_entropy") if draft_entropy else None
-    f32 = torch.float32
-    args = [
-        _ptr(target, name="target"), _ptr(draft, name="draft") if N > 0 else None, dt, V, B, N, k_max,
-        _ptr(sl, torch.int32, B, "sl"), _ptr(cu_sl, torch.int32, B + 1, "cu_sl"),
-        _ptr(draft_tokens, torch.int32, N, "draft_tokens") if N > 0 else None,
-        _ptr(temperature, f32, B, "temperature"), _ptr(u_acc, f32, N, "u_acc") if N > 0 else None,
-        _ptr(u_res, f32, B, "u_res"), int(pad_id),
-        _ptr(out["accepted"], torch.int32, B), _ptr(out["tokens"], torch.int32, B * (k_max + 1)),
-        _ptr(out["kld"], f32, N) if N > 0 else None,
-        _ptr(row_lse, torch.float64, 2 * N, "row_lse") if row_lse is not None else None,
-        _ptr(ent, f32, N, "draft_entropy") if ent is not None and N > 0 else None,
-        _ptr(hist, f32, B * W, "hist"), _ptr(head, torch.int32, B, "head"), _ptr(count, torch.int32, B, "count"),
-        W, n_short, n_long, float(delta), float(eps),
-        _ptr(out["mu_last"], f32, B), _ptr(out["var_short"], f32, B), _ptr(out["var_long"], f32, B),
-        _ptr(out["wvir"], f32, B), _ptr(out["sf"], f32, B), _ptr(sl_max, f32, B, "sl_max"), float(sl_min),
-        int(sl_hi), _ptr(budget, torch.int32, B, "budget") if budget is not None else None,
-        _ptr(out["sl_hat"], f32, B), _ptr(out["sl_cap"], f32, 1), _ptr(out["sl_next"], torch.int32, B),
-        _ptr(out["seq_err"], None, B)]
-    return args, out, (B, N, V)
+        B = int(sl.shape[0])
+        out = _new_verify_out(B, _rows(draft), k_max, target.device)
+        out["seq_err"] = torch.empty(B, dtype=torch.int32, device=target.device)
+        _new_signal_out(out, B, target.device)
+    if draft_entropy:
+        _with_entropy(out, True, _rows(draft), target.device)
+    if workspace is None:
+        workspace = new_workspace(int(sl.shape[0]), _rows(draft), int(target.shape[1]), k_max, device=target.device)
+    native.step(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, int(pad_id), out, row_lse,
+                draft_entropy, hist, head, count, sl_max, n_short, n_long, delta, eps, sl_min,
+                k_max if sl_hi is None else int(sl_hi), budget, workspace, _handle(stream))
+    return out
 
 
 def step(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, hist, head, count,
@@ -229,72 +218,47 @@ def step(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_ma
     updated in place; returns a dict of every output (accepted, tokens, kld, mu_last,
     var_short, var_long, wvir, sf, sl_hat, sl_cap, sl_next, seq_err, and draft_entropy
     when asked for).  ``budget`` [B] int32: tokens each sequence may still emit."""
-    lib = load()
-    args, out, (B, N, V) = _step_args(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max,
-                                      hist, head, count, sl_max, n_short, n_long, delta, eps, sl_min, sl_hi, pad_id,
-                                      out, row_lse, draft_entropy, budget)
-    if workspace is None:
-        workspace = new_workspace(B, N, V, k_max, device=target.device)
-    rc = lib.dsde_step(*args, _ptr(workspace, torch.uint8, None, "workspace"), workspace.numel(), _stream(stream))
-    _check(rc)
-    return out
+    return _step(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, hist, head, count, sl_max,
+                 n_short, n_long, delta, eps, sl_min, sl_hi, pad_id, out, workspace, row_lse, draft_entropy, budget,
+                 stream)
 
 
 def step_static(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, hist, head, count,
                 sl_max, n_short=10, n_long=30, delta=0.85, eps=1e-6, sl_min=2.0, sl_hi=None, pad_id=-1,
                 out=None, row_lse=None, draft_entropy=False, budget=None, stream=None):
     """``dsde_step_static``: ``step`` without a workspace argument; the library's
-    per-device scratch array (STATIC_SCRATCH_BYTES) holds the scratch space, and
-    the call allocates no device memory when ``out`` is given.  Calls that may
-    overlap on one GPU share that array and must not run concurrently."""
-    lib = load()
-    args, out, _ = _step_args(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, hist, head,
-                              count, sl_max, n_short, n_long, delta, eps, sl_min, sl_hi, pad_id, out, row_lse,
-                              draft_entropy, budget)
-    _check(lib.dsde_step_static(*args, _stream(stream)))
-    return out
+    per-device scratch array holds the scratch space, and the call allocates no
+    device memory when ``out`` is given.  Calls that may overlap on one GPU share
+    that array and must not run concurrently."""
+    return _step(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, hist, head, count, sl_max,
+                 n_short, n_long, delta, eps, sl_min, sl_hi, pad_id, out, False, row_lse, draft_entropy, budget,
+                 stream)
 
 
 def kld_signal(sl, cu_sl, kld, hist, head, count, n_short=10, n_long=30, delta=0.85, eps=1e-6,
                out=None, stream=None):
     """``dsde_kld_signal``: updates hist/head/count in place; returns the outputs."""
-    lib = load()
-    B = int(sl.shape[0])
-    N = int(kld.shape[0])
-    W = int(hist.shape[1])
-    dev = sl.device
+    native = _native or _bind()
     if out is None:
+        B, dev = int(sl.shape[0]), sl.device
         out = {k: torch.empty(B, dtype=torch.float32, device=dev)
                for k in ("mu_last", "var_short", "var_long", "wvir", "sf")}
         out["seq_err"] = torch.empty(B, dtype=torch.int32, device=dev)
-    rc = lib.dsde_kld_signal(
-        B, N, _ptr(sl, torch.int32, B, "sl"), _ptr(cu_sl, torch.int32, B + 1, "cu_sl"),
-        _ptr(kld, torch.float32, N, "kld") if N > 0 else None, _ptr(hist, torch.float32, B * W, "hist"),
-        _ptr(head, torch.int32, B, "head"), _ptr(count, torch.int32, B, "count"), W, n_short, n_long,
-        float(delta), float(eps), _ptr(out["mu_last"], torch.float32, B), _ptr(out["var_short"], torch.float32, B),
-        _ptr(out["var_long"], torch.float32, B), _ptr(out["wvir"], torch.float32, B),
-        _ptr(out["sf"], torch.float32, B), _ptr(out["seq_err"], None, B), _stream(stream))
-    _check(rc)
+    native.kld_signal(sl, cu_sl, kld, hist, head, count, n_short, n_long, delta, eps, out, _handle(stream))
     return out
 
 
 def next_sl(sf, wvir, sl_max, sl_min=2.0, sl_hi=8, budget=None, out=None, stream=None):
     """``dsde_next_sl``: SL rule with the batch cap (and the optional per-sequence
     token budget); returns sl_hat, sl_cap, sl_next, seq_err."""
-    lib = load()
-    B = int(sf.shape[0])
-    dev = sf.device
+    native = _native or _bind()
     if out is None:
+        B, dev = int(sf.shape[0]), sf.device
         out = {"sl_hat": torch.empty(B, dtype=torch.float32, device=dev),
                "sl_cap": torch.empty(1, dtype=torch.float32, device=dev),
                "sl_next": torch.empty(B, dtype=torch.int32, device=dev),
                "seq_err": torch.empty(B, dtype=torch.int32, device=dev)}
-    rc = lib.dsde_next_sl(B, _ptr(sf, torch.float32, B, "sf"), _ptr(wvir, torch.float32, B, "wvir"),
-                          _ptr(sl_max, torch.float32, B, "sl_max"), float(sl_min), int(sl_hi),
-                          _ptr(budget, torch.int32, B, "budget") if budget is not None else None,
-                          _ptr(out["sl_hat"], torch.float32, B), _ptr(out["sl_cap"], torch.float32, 1),
-                          _ptr(out["sl_next"], torch.int32, B), _ptr(out["seq_err"], None, B), _stream(stream))
-    _check(rc)
+    native.next_sl(sf, wvir, sl_max, sl_min, int(sl_hi), budget, out, _handle(stream))
     return out
 
 
@@ -308,15 +272,7 @@ def new_calibration_state(B, device="cuda"):
 
 def calibration_update(sl, cu_sl, accepted, kld, seq_err, state, stream=None):
     """``dsde_calibration_update``: folds one verification step into ``state``."""
-    lib = load()
-    B = int(sl.shape[0])
-    N = int(kld.shape[0])
-    _check(lib.dsde_calibration_update(
-        B, N, _ptr(sl, torch.int32, B, "sl"), _ptr(cu_sl, torch.int32, B + 1, "cu_sl"),
-        _ptr(accepted, torch.int32, B, "accepted"), _ptr(kld, torch.float32, N, "kld") if N > 0 else None,
-        _ptr(seq_err, None, B, "seq_err"), _ptr(state["a_max"], torch.int32, B),
-        _ptr(state["kld_sum"], torch.float64, B), _ptr(state["kld_count"], torch.int64, B),
-        _ptr(state["kld_max"], torch.float32, B), _stream(stream)))
+    (_native or _bind()).calibration_update(sl, cu_sl, accepted, kld, seq_err, state, _handle(stream))
 
 
 def calibrate_sl_max(state, eps=1e-6, pooled=False, out=None, stream=None):
@@ -369,75 +325,36 @@ def new_shard_workspace(B, N, V_shard, k_max, device="cuda"):
     return torch.empty(n, dtype=torch.uint8, device=device)
 
 
-def _shard_rows(target, draft, B):
-    dt = _logits_dtype(target)
-    V_shard = int(target.shape[1])
-    N = int(draft.shape[0]) if draft is not None else 0
-    if draft is not None and (draft.dtype != target.dtype or (N > 0 and int(draft.shape[1]) != V_shard)):
-        raise DsdeError("draft slice must match the target slice's dtype and width")
-    if int(target.shape[0]) != N + B:
-        raise DsdeError(f"target slice has {target.shape[0]} rows, expected N + B = {N + B}")
-    return dt, V_shard, N
-
-
 def shard_stats(target, draft, v_begin, V, sl, cu_sl, draft_tokens, temperature, k_max, workspace,
                 part=None, seq_err=None, stream=None):
     """``dsde_shard_stats`` (call 1) on this shard's slices [rows, V_shard].  Returns
     (part [N, 64] uint8 records, seq_err [B] int32)."""
-    lib = load()
-    B = int(sl.shape[0])
-    dt, V_shard, N = _shard_rows(target, draft, B)
-    dev = target.device
+    native = _native or _bind()
     if part is None:
-        part = torch.empty((max(N, 1), SHARD_PARTIAL_BYTES), dtype=torch.uint8, device=dev)
+        part = torch.empty((max(_rows(draft), 1), SHARD_PARTIAL_BYTES), dtype=torch.uint8, device=target.device)
     if seq_err is None:
-        seq_err = torch.empty(B, dtype=torch.int32, device=dev)
-    rc = lib.dsde_shard_stats(
-        _ptr(target, name="target"), _ptr(draft, name="draft") if N > 0 else None, dt, V_shard, int(v_begin),
-        int(V), B, N, k_max, _ptr(sl, torch.int32, B, "sl"), _ptr(cu_sl, torch.int32, B + 1, "cu_sl"),
-        _ptr(draft_tokens, torch.int32, N, "draft_tokens") if N > 0 else None,
-        _ptr(temperature, torch.float32, B, "temperature"),
-        _ptr(part, torch.uint8, N * SHARD_PARTIAL_BYTES, "part") if N > 0 else None,
-        _ptr(seq_err, None, B, "seq_err"), _ptr(workspace, torch.uint8, None, "workspace"), workspace.numel(),
-        _stream(stream))
-    _check(rc)
+        seq_err = torch.empty(int(sl.shape[0]), dtype=torch.int32, device=target.device)
+    native.shard_stats(target, draft, int(v_begin), int(V), sl, cu_sl, draft_tokens, temperature, k_max, workspace,
+                       part, seq_err, _handle(stream))
     return part, seq_err
 
 
-def _shard_accept_call(parts, V, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, seq_err, pad_id,
-                       row_lse, draft_entropy, out, stream):
-    """Output buffers and the leading ctypes arguments shared by the two call-2 entry points."""
-    G = int(parts.shape[0])
-    B = int(sl.shape[0])
-    N = int(draft_tokens.shape[0]) if draft_tokens is not None else 0
-    dev = sl.device
+def _shard_accept_out(parts, sl, draft_tokens, k_max, seq_err, draft_entropy, out, stream):
+    """Output buffers and packed partials shared by the two call-2 entry points."""
+    N = _rows(draft_tokens)
     if N > 0 and (parts.dim() != 3 or int(parts.shape[1]) < N or int(parts.shape[2]) != SHARD_PARTIAL_BYTES):
         raise DsdeError("parts must be [G, N, 64] uint8")
     if out is None:
-        out = {"accepted": torch.empty(B, dtype=torch.int32, device=dev),
-               "tokens": torch.empty((B, k_max + 1), dtype=torch.int32, device=dev),
-               "kld": torch.empty(max(N, 1), dtype=torch.float32, device=dev)[:N],
-               "jobs": torch.empty((B, DRAW_JOB_BYTES), dtype=torch.uint8, device=dev)}
+        B = int(sl.shape[0])
+        out = _new_verify_out(B, N, k_max, sl.device)
+        out["jobs"] = torch.empty((B, DRAW_JOB_BYTES), dtype=torch.uint8, device=sl.device)
     out["seq_err"] = seq_err
-    if draft_entropy and "draft_entropy" not in out:
-        out["draft_entropy"] = torch.empty(max(N, 1), dtype=torch.float32, device=dev)[:N]
-    ent = out.get("draft_entropy") if draft_entropy else None
+    _with_entropy(out, draft_entropy, N, sl.device)
     if N > 0 and int(parts.shape[1]) != N:
         # the packed copy is made on the call's stream, ahead of the call
         with torch.cuda.stream(stream if stream is not None else torch.cuda.current_stream()):
             parts = parts[:, :N].contiguous()
-    args = [G, _ptr(parts, torch.uint8, G * N * SHARD_PARTIAL_BYTES, "parts") if N > 0 else None, int(V), B, N,
-            k_max, _ptr(sl, torch.int32, B, "sl"), _ptr(cu_sl, torch.int32, B + 1, "cu_sl"),
-            _ptr(draft_tokens, torch.int32, N, "draft_tokens") if N > 0 else None,
-            _ptr(temperature, torch.float32, B, "temperature"),
-            _ptr(u_acc, torch.float32, N, "u_acc") if N > 0 else None, _ptr(u_res, torch.float32, B, "u_res"),
-            int(pad_id), _ptr(out["accepted"], torch.int32, B, "accepted"),
-            _ptr(out["tokens"], torch.int32, B * (k_max + 1), "tokens"),
-            _ptr(out["kld"], torch.float32, N, "kld") if N > 0 else None,
-            _ptr(row_lse, torch.float64, 2 * N, "row_lse") if row_lse is not None else None,
-            _ptr(ent, torch.float32, N, "draft_entropy") if ent is not None and N > 0 else None,
-            _ptr(out["jobs"], torch.uint8, B * DRAW_JOB_BYTES, "jobs")]
-    return out, args, parts
+    return out, parts
 
 
 def shard_accept(parts, V, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, seq_err, pad_id=-1,
@@ -445,11 +362,10 @@ def shard_accept(parts, V, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k
     """``dsde_shard_accept`` (call 2) from the gathered partials parts [G, N, 64]
     (uint8, shard order).  seq_err (call 1's) is updated in place.  Returns a dict
     with accepted, tokens, kld, seq_err, jobs [B, 44] uint8 (and draft_entropy)."""
-    lib = load()
-    out, args, _keep = _shard_accept_call(parts, V, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max,
-                                          seq_err, pad_id, row_lse, draft_entropy, out, stream)
-    B = int(sl.shape[0])
-    _check(lib.dsde_shard_accept(*args, _ptr(seq_err, None, B, "seq_err"), _stream(stream)))
+    native = _native or _bind()
+    out, parts = _shard_accept_out(parts, sl, draft_tokens, k_max, seq_err, draft_entropy, out, stream)
+    native.shard_accept(False, parts, int(V), sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, int(pad_id),
+                        out, row_lse, draft_entropy, seq_err, _handle(stream))
     return out
 
 
@@ -460,46 +376,21 @@ def shard_accept_step(parts, V, sl, cu_sl, draft_tokens, temperature, u_acc, u_r
     fused behind it (hist/head/count updated in place).  Returns the outputs of
     shard_accept plus mu_last, var_short, var_long, wvir, sf, sl_hat, sl_cap,
     sl_next."""
-    lib = load()
-    out, args, _keep = _shard_accept_call(parts, V, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max,
-                                          seq_err, pad_id, row_lse, draft_entropy, out, stream)
-    B = int(sl.shape[0])
-    W = int(hist.shape[1])
-    sl_hi = k_max if sl_hi is None else sl_hi
-    dev = sl.device
-    f32 = torch.float32
-    for k in ("mu_last", "var_short", "var_long", "wvir", "sf", "sl_hat"):
-        if k not in out:
-            out[k] = torch.empty(B, dtype=f32, device=dev)
-    if "sl_cap" not in out:
-        out["sl_cap"] = torch.empty(1, dtype=f32, device=dev)
-    if "sl_next" not in out:
-        out["sl_next"] = torch.empty(B, dtype=torch.int32, device=dev)
-    rc = lib.dsde_shard_accept_step(
-        *args, _ptr(hist, f32, B * W, "hist"), _ptr(head, torch.int32, B, "head"),
-        _ptr(count, torch.int32, B, "count"), W, n_short, n_long, float(delta), float(eps),
-        _ptr(out["mu_last"], f32, B), _ptr(out["var_short"], f32, B), _ptr(out["var_long"], f32, B),
-        _ptr(out["wvir"], f32, B), _ptr(out["sf"], f32, B), _ptr(sl_max, f32, B, "sl_max"), float(sl_min),
-        int(sl_hi), _ptr(budget, torch.int32, B, "budget") if budget is not None else None,
-        _ptr(out["sl_hat"], f32, B), _ptr(out["sl_cap"], f32, 1), _ptr(out["sl_next"], torch.int32, B),
-        _ptr(seq_err, None, B, "seq_err"), _stream(stream))
-    _check(rc)
+    native = _native or _bind()
+    out, parts = _shard_accept_out(parts, sl, draft_tokens, k_max, seq_err, draft_entropy, out, stream)
+    _new_signal_out(out, int(sl.shape[0]), sl.device)
+    native.shard_accept(True, parts, int(V), sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, int(pad_id),
+                        out, row_lse, draft_entropy, seq_err, hist, head, count, sl_max, n_short, n_long, delta, eps,
+                        sl_min, k_max if sl_hi is None else int(sl_hi), budget, _handle(stream))
     return out
 
 
 def shard_draw_mass(target, draft, v_begin, part, jobs, k_max, workspace, mass=None, stream=None):
     """``dsde_shard_draw_mass`` (call 3).  Returns mass [B, 32] uint8 records."""
-    lib = load()
-    B = int(jobs.shape[0])
-    dt, V_shard, N = _shard_rows(target, draft, B)
+    native = _native or _bind()
     if mass is None:
-        mass = torch.empty((B, SHARD_MASS_BYTES), dtype=torch.uint8, device=target.device)
-    rc = lib.dsde_shard_draw_mass(
-        _ptr(target, name="target"), _ptr(draft, name="draft") if N > 0 else None, dt, V_shard, int(v_begin), B, N,
-        k_max, _ptr(part, torch.uint8, N * SHARD_PARTIAL_BYTES, "part") if N > 0 else None,
-        _ptr(jobs, torch.uint8, B * DRAW_JOB_BYTES, "jobs"), _ptr(mass, torch.uint8, B * SHARD_MASS_BYTES, "mass"),
-        _ptr(workspace, torch.uint8, None, "workspace"), workspace.numel(), _stream(stream))
-    _check(rc)
+        mass = torch.empty((int(jobs.shape[0]), SHARD_MASS_BYTES), dtype=torch.uint8, device=target.device)
+    native.shard_draw_mass(target, draft, int(v_begin), part, jobs, k_max, workspace, mass, _handle(stream))
     return mass
 
 
@@ -509,20 +400,11 @@ def shard_draw_pick(g, masses, target, draft, v_begin, jobs, k_max, accepted, to
     [G, B, 32] (uint8, shard order).  accepted, tokens and seq_err are updated in
     place; returns drawn [B] int32 (the token where this shard determined it,
     else -1)."""
-    lib = load()
-    G = int(masses.shape[0])
-    B = int(jobs.shape[0])
-    dt, V_shard, N = _shard_rows(target, draft, B)
+    native = _native or _bind()
     if drawn is None:
-        drawn = torch.empty(B, dtype=torch.int32, device=target.device)
-    rc = lib.dsde_shard_draw_pick(
-        G, int(g), _ptr(masses, torch.uint8, G * B * SHARD_MASS_BYTES, "masses"), _ptr(target, name="target"),
-        _ptr(draft, name="draft") if N > 0 else None, dt, V_shard, int(v_begin), B, N, k_max,
-        _ptr(jobs, torch.uint8, B * DRAW_JOB_BYTES, "jobs"), int(pad_id),
-        _ptr(accepted, torch.int32, B, "accepted"), _ptr(tokens, torch.int32, B * (k_max + 1), "tokens"),
-        _ptr(drawn, torch.int32, B, "drawn"), _ptr(seq_err, None, B, "seq_err"),
-        _ptr(workspace, torch.uint8, None, "workspace"), workspace.numel(), _stream(stream))
-    _check(rc)
+        drawn = torch.empty(int(jobs.shape[0]), dtype=torch.int32, device=target.device)
+    native.shard_draw_pick(int(g), masses, target, draft, int(v_begin), jobs, k_max, int(pad_id), accepted, tokens,
+                           drawn, seq_err, workspace, _handle(stream))
     return drawn
 
 

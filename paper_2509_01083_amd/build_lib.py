@@ -14,6 +14,10 @@ beside this file:
 After linking, the device code in the library is disassembled and the build
 fails if any packed FP32 arithmetic instruction is found
 (``packed_fp32_instructions``; a CPU test runs the same check).
+
+``build`` then compiles the Python binding's marshalling code
+(csrc/binding.cpp, host code only) against torch's headers and links it to the
+library beside it.
 """
 import os
 import re
@@ -24,6 +28,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdsde.so")
+BINDING = os.path.join(HERE, "_binding.so")
 BUILD = os.path.join(ROOT, "_build")
 SOURCES = ["api.hip", "stats.hip", "verify.hip", "shard.hip", "signal.hip", "probe.hip"]
 
@@ -65,7 +70,24 @@ def build(verbose: bool = False) -> str:
         os.remove(tmp)
         raise RuntimeError("packed FP32 instructions in the device code: " + "; ".join(bad[:5]))
     os.replace(tmp, LIB)
+    build_binding(verbose)
     return LIB
+
+
+def build_binding(verbose: bool = False) -> str:
+    """The marshalling extension, linked to the libdsde.so in its own folder."""
+    import sysconfig
+
+    from torch.utils import cpp_extension
+    includes = [x for p in cpp_extension.include_paths("cuda") for x in ("-isystem", p)]
+    libs = [x for p in cpp_extension.library_paths("cpu") for x in ("-L", p)]
+    tmp = BINDING + ".tmp"
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+          "-I", os.path.join(ROOT, "include"), "-isystem", sysconfig.get_paths()["include"], *includes,
+          os.path.join(CSRC, "binding.cpp"), "-o", tmp, "-L", HERE, "-l:libdsde.so", "-Wl,-rpath,$ORIGIN", *libs,
+          "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"], verbose)
+    os.replace(tmp, BINDING)
+    return BINDING
 
 
 def _fatbin_section(path):
