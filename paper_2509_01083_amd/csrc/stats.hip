@@ -345,11 +345,12 @@ __global__ __launch_bounds__(kThreads) void stats_kernel_generic(const void *__r
 // start event attached to a dispatch is stamped when the packet is
 // processed, which can be while the previous kernel still runs).
 template <typename K, typename... Args>
-static void launch_timed(K kernel, dim3 grid, dim3 block, hipStream_t stream, hipEvent_t done, Args... args) {
+static void launch_timed(K kernel, dim3 grid, dim3 block, size_t lds, hipStream_t stream, hipEvent_t done,
+                         Args... args) {
   if (done)
-    hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, nullptr, done, 0, args...);
+    hipExtLaunchKernelGGL(kernel, grid, block, lds, stream, nullptr, done, 0, args...);
   else
-    hipLaunchKernelGGL(kernel, grid, block, 0, stream, args...);
+    hipLaunchKernelGGL(kernel, grid, block, lds, stream, args...);
 }
 
 // Whether the statistics pass runs without the set-up kernel, on a grid over
@@ -383,8 +384,17 @@ static void launch_rows(const VerifyArgs &a, const WorkItem *w, PairChunk *part,
   const BatchLayout L{a.sl, a.cu_sl, a.temperature, a.N, a.k_max, k_rcp};
   by_rows(a.dtype, rows_form(a.target, a.draft, a.dtype, a.V, a.N), [&](auto dt, auto row) {
     constexpr int DT = decltype(dt)::value, ROW = decltype(row)::value;
+    // The memory system serves about 160-200 KB of outstanding loads per CU
+    // best: five bf16 workgroups of 32 KB (four: +4%, six: +3% on a 124 us
+    // step), but only three fp32 ones of 64 KB, which LDS asked for and not
+    // used holds them to (512 sequences at V = 100,001: step 346 -> 334 us, four
+    // 343, two 365; 64 at V = 128,256: 64.4 -> 63.2).  Passes of less than four
+    // rounds gain nothing (32 sequences: 42.4 -> 42.9).
+    constexpr size_t kThreePerCu = 50000;
+    constexpr int64_t kFourRounds = 4 * 3 * 256;
+    const size_t lds = DT == DSDE_FP32 && ROW != kScalarRows && a.N * nc >= kFourRounds ? kThreePerCu : 0;
     auto run = [&](auto kernel) {
-      launch_timed(kernel, grid, block, a.stream, done, T, D, V, nc, w, L, tokens, base, part, gath, chunk_arg);
+      launch_timed(kernel, grid, block, lds, a.stream, done, T, D, V, nc, w, L, tokens, base, part, gath, chunk_arg);
     };
     if constexpr (DT == DSDE_FP32 || ROW == kScalarRows)
       run(stats_kernel_generic<DT, ROW, LOOKUP>);
@@ -402,7 +412,7 @@ void launch_stats_pass(const VerifyArgs &a, bool lookup, WorkItem *work, PairChu
     if (a.N > 0) launch_rows<true>(a, nullptr, part, gath, chunk_arg, entropy, nullptr);
     return;
   }
-  launch_timed(setup_kernel, dim3(1), dim3(1024), a.stream, prof ? a.prof_start : nullptr, a.B, a.N, a.k_max,
+  launch_timed(setup_kernel, dim3(1), dim3(1024), 0, a.stream, prof ? a.prof_start : nullptr, a.B, a.N, a.k_max,
                a.sl, a.cu_sl, a.temperature, a.seq_err, work);
   if (a.N > 0) launch_rows<false>(a, work, part, gath, chunk_arg, entropy, prof ? a.prof_stop : nullptr);
 }
