@@ -92,19 +92,35 @@ __global__ __launch_bounds__(kSigThreads) void calibration_update_kernel(
     const int32_t *__restrict__ accepted, const float *__restrict__ kld, const uint32_t *__restrict__ seq_err,
     int32_t *__restrict__ a_max, double *__restrict__ kld_sum, int64_t *__restrict__ kld_count,
     float *__restrict__ kld_max) {
+  const int32_t b = int32_t(blockIdx.x) * (kSigThreads / 64) + int32_t(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  // one round trip for the sequence's place and its statistics beside the
+  // layout check, a second, before the check's verdict, for its KLD values
+  int32_t s = 0, first = 0, acc_n = 0, top = 0;
+  uint32_t err = 1u;
+  double sum = 0.0;
+  int64_t cnt = 0;
+  float kmax = 0.0f, v0 = 0.0f;
+  if (b < B) {
+    s = sl[b];
+    first = cu_sl[b];
+    err = seq_err[b];
+    acc_n = accepted[b];
+    top = a_max[b];
+    sum = kld_sum[b];
+    cnt = kld_count[b];
+    kmax = kld_max[b];
+  }
   int bad = 0;
   for (int32_t q = threadIdx.x; q < B; q += blockDim.x)
     if (sl[q] < 0 || int64_t(cu_sl[q + 1]) - int64_t(cu_sl[q]) != int64_t(sl[q])) bad = 1;
+  if (first >= 0 && int64_t(first) + s <= N && lane < s) v0 = kld[first + lane];
   bad = __syncthreads_or(bad);
   if (bad || cu_sl[0] != 0 || int64_t(cu_sl[B]) != N) return;
-  const int32_t b = int32_t(blockIdx.x) * (kSigThreads / 64) + int32_t(threadIdx.x >> 6);
-  if (b >= B || seq_err[b] != 0) return;
-  const int lane = threadIdx.x & 63;
-  const int32_t s = sl[b];
-  const int64_t first = cu_sl[b];
-  double acc = 0.0;
-  float mx = 0.0f;
-  for (int32_t j = lane; j < s; j += 64) {
+  if (b >= B || err != 0) return;
+  double acc = double(v0);
+  float mx = fmaxf(0.0f, v0);
+  for (int32_t j = lane + 64; j < s; j += 64) {
     const float v = kld[first + j];
     acc += double(v);
     mx = fmaxf(mx, v);
@@ -112,10 +128,10 @@ __global__ __launch_bounds__(kSigThreads) void calibration_update_kernel(
   acc = wave_sum_f64(acc);
   mx = wave_max_f32(mx);
   if (lane == 0) {
-    a_max[b] = accepted[b] > a_max[b] ? accepted[b] : a_max[b];
-    kld_sum[b] += acc;
-    kld_count[b] += s;
-    kld_max[b] = fmaxf(kld_max[b], mx);
+    a_max[b] = acc_n > top ? acc_n : top;
+    kld_sum[b] = sum + acc;
+    kld_count[b] = cnt + s;
+    kld_max[b] = fmaxf(kmax, mx);
   }
 }
 
