@@ -63,7 +63,7 @@ struct StepParams {
 // acceptance, outputs and draw weights
 // ---------------------------------------------------------------------------
 
-// Workgroup (x, y) works on sequence x of the pass; y = 0 writes the outputs,
+// Workgroup (x, y) works on one sequence of the pass; y = 0 writes the outputs,
 // y = 1 .. gridDim.y - 1 take a share of the draw's units each.  All of them
 // repeat the acceptance: it takes about 3 us of latency and few instructions,
 // where handing its result to other workgroups would take a kernel boundary.
@@ -82,7 +82,9 @@ __global__ __launch_bounds__(kSeqThreads) void seq_kernel(const StepParams P, co
   __shared__ DrawJob s_job;
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);  // uniform: unit indices and addresses stay scalar
-  const int32_t lb = blockIdx.x, b = P.first_seq + lb;
+  // last sequence first: its rows are what the statistics pass read last, and
+  // the last-level cache still holds some of them
+  const int32_t lb = int32_t(gridDim.x) - 1 - int32_t(blockIdx.x), b = P.first_seq + lb;
   const bool outputs = blockIdx.y == 0;
   const int32_t width = P.k_max + 1;
   int32_t *tok = P.tokens + int64_t(b) * width;
