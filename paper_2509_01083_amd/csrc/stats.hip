@@ -131,14 +131,14 @@ __device__ __forceinline__ void wave_chunk_argmax(float M, float tmax, Z z, int6
       if (z(i) == M) first = i;
     if (first >= 0) best = uint32_t(Layout<DT, VEC>::index(chunk, first, t));
   }
-  if (__ballot(best != 0xffffffffu)) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const uint32_t y = __shfl_xor(best, o);
-      best = y < best ? y : best;
-    }
+  // nearly always one lane of one wavefront holds it: take the lanes one by one
+  // (six shuffles in a row would hold the workgroup up at its last barrier)
+  uint32_t least = 0xffffffffu;
+  for (uint64_t holders = __ballot(best != 0xffffffffu); holders; holders &= holders - 1) {
+    const uint32_t y = uint32_t(__builtin_amdgcn_readlane(int(best), int(__builtin_ctzll(holders))));
+    least = y < least ? y : least;
   }
-  if (lane == 0) red[wave] = best;
+  if (lane == 0) red[wave] = least;
 }
 
 // Sum over the 64 lanes of a wavefront of four fp64 values at once (a
