@@ -62,13 +62,14 @@ def parse():
 
 
 def stats_kernel_name(esz, V):
-    """The statistics kernel the library dispatches for this row layout (the
-    bench's tensors are 16-byte aligned): the bf16 vector kernel in its form
-    without the draft-entropy accumulator (the step asks for no entropy), else
-    the generic one instantiated for the dtype and vector width."""
+    """The statistics kernel the library dispatches for this row layout while
+    profiling events are set (the bench's tensors are 16-byte aligned): the bf16
+    kernel in its form without the draft-entropy accumulator (the step asks for
+    no entropy), else the fp32 one; the row form is 2 for whole 16-byte loads,
+    1 for rows that end inside one."""
     if esz == 2:
-        return "stats_kernel_bf16<false>" if V % 8 == 0 else "stats_kernel_generic<bf16, scalar>"
-    return "stats_kernel_generic<fp32, vec4>" if V % 4 == 0 else "stats_kernel_generic<fp32, scalar>"
+        return f"stats_kernel_bf16<false, false, {2 if V % 8 == 0 else 1}>"
+    return f"stats_kernel_generic<0, {2 if V % 4 == 0 else 1}, false>"
 
 
 def main():

@@ -81,7 +81,7 @@ extern "C" {
 /* Largest supported speculation length bound (one wavefront lane per drafted position). */
 #define DSDE_MAX_K 63
 /* Largest supported vocabulary (512 chunks of 8192 logits; the draw keeps one
- * total per chunk on chip). */
+ * cell per 2048 logits in the workspace). */
 #define DSDE_MAX_VOCAB 4194304
 
 /* The ABI version this library implements (DSDE_ABI_VERSION). */
@@ -207,8 +207,8 @@ int32_t dsde_next_sl(int32_t B, const float *sf, const float *wvir, const float 
 /*
  * The whole step fused: dsde_verify, then dsde_kld_signal on the KLD it
  * produces, then dsde_next_sl on the signal it produces, with the arguments
- * of those three calls (see them for meaning and layout), in four kernel
- * launches instead of five.  Outputs are bit-identical to the three calls made
+ * of those three calls (see them for meaning and layout), in three kernel
+ * launches for small batches and four for larger ones, instead of five or six.  Outputs are bit-identical to the three calls made
  * in sequence; seq_err is the OR of their error bits, except that a layout
  * error (DSDE_ERR_LAYOUT) also skips the signal update.
  * For serving loops that run the complete verification step.
@@ -227,13 +227,15 @@ int32_t dsde_step(const void *target_logits, const void *draft_logits, int32_t d
  * dsde_step without a caller workspace, for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops, harnesses
  * that forbid hipMalloc): the same kernels and bit-identical outputs, with the
- * scratch space in a device array of DSDE_STATIC_SCRATCH_BYTES that the
- * library holds, one copy per device, until the process ends.  The call
- * allocates nothing; its first call on a device looks up that device's copy.
+ * scratch space in a device array that the library holds, one copy per device,
+ * until the process ends.  The call allocates nothing; its first call on a
+ * device looks up that device's copy.
  *
  * Arguments as in dsde_step, less workspace and workspace_bytes.  Returns
- * DSDE_WORKSPACE_TOO_SMALL when dsde_verify_workspace_bytes(B, N, V, k_max)
- * exceeds DSDE_STATIC_SCRATCH_BYTES (nothing is enqueued), and
+ * DSDE_WORKSPACE_TOO_SMALL when the scratch space of the statistics pass
+ * (64 bytes per slot b * k_max + j and 8192 logits, or less, and 16 per drafted
+ * position) exceeds DSDE_STATIC_SCRATCH_BYTES (nothing is enqueued; the rest of
+ * dsde_verify_workspace_bytes is bounded and held besides), and
  * DSDE_DEVICE_ERROR when the device copy cannot be found.  Every call on one
  * device uses the same array: calls that may overlap on one device (several
  * streams or threads) race and must be serialised by the caller.  No part of
@@ -308,7 +310,7 @@ int32_t dsde_calibrate_sl_max(int32_t B, const int32_t *a_max, const double *kld
  * there), or fused behind call 2 (dsde_shard_accept_step).  Every pointer,
  * layout and error rule of dsde_verify applies; the
  * calls of one shard share its workspace (dsde_shard_workspace_bytes), whose
- * contents pass from call 1 to 2 (none), 3 to 4 (the slice's chunk totals).
+ * contents pass from call 1 to 2 (none), 3 to 4 (the slice's unit totals).
  */
 typedef struct {
   float mt, md;      /* the slice's largest z c of the target and the draft row (log2 domain) */
@@ -406,7 +408,7 @@ int32_t dsde_shard_accept_step(int32_t G, const dsde_shard_partial *parts, int64
 /*
  * Call 3: this slice's share of each sequence's draw weight (it reads the
  * slice of the first rejected pair, or of the bonus row, once) into mass [B];
- * the slice's chunk totals stay in the workspace for call 4.
+ * the slice's unit totals stay in the workspace for call 4.
  *   part [N]                    this shard's call-1 output
  *   jobs [B]                    call 2's output
  */
@@ -418,7 +420,7 @@ int32_t dsde_shard_draw_mass(const void *target_logits, const void *draft_logits
 /*
  * Call 4: the draw.  From the gathered masses [G][B] every shard finds the
  * slice holding u'_b Z_b (a fixed-order fp64 prefix over the slices, the rule
- * of dsde_verify's draw); that shard scans its slice (chunk totals from call
+ * of dsde_verify's draw); that shard scans its slice (unit totals from call
  * 3, the fallback to p computed here when it is needed).
  *   g                           this shard's index (0 <= g < G)
  *   drawn [B]                   output: the token, or -1 (see above)
@@ -449,10 +451,11 @@ int32_t dsde_stream_read(const void *buf, int64_t bytes, uint32_t *out, void *st
 /*
  * Profiling hook: when both events are non-NULL (hipEvent_t, created with
  * timing enabled), every later dsde_verify or dsde_step with N > 0 attaches
- * `start` to the completion of its set-up kernel and `stop` to the completion
- * of its row statistics kernel (the pass that reads every drafted row pair
- * once), which runs right after it on the same stream; the elapsed time
- * between them is that kernel's execution time.  Events created with
+ * `start` to the completion of its set-up kernel (which small batches run only
+ * then) and `stop` to the completion of its row statistics kernel (the pass
+ * that reads every drafted row pair once), which runs right after it on the
+ * same stream; the elapsed time between them is that kernel's execution time.
+ * Events created with
  * hipEventDisableSystemFence add no gap to the stream.  Passing NULLs turns it
  * off.  Process-wide; not thread-safe.
  */

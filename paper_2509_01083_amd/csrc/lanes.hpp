@@ -2,7 +2,7 @@
 // from DPP moves inside rows of 16 lanes and v_readlane across the four rows.
 // A ds_bpermute-based shuffle takes a round trip through the LDS unit per
 // step; these take a few VALU cycles per step, which matters where a
-// reduction or scan sits on a latency-bound path (the per-sequence kernel).
+// reduction or scan sits on a latency-bound path (the per-sequence kernels).
 // The bandwidth-bound row passes keep their ds_bpermute butterflies: there the
 // LDS unit runs them beside the VALU work, and the DPP forms measured slower.
 //

@@ -27,10 +27,6 @@ __device__ __forceinline__ uint4 stream_load(const uint4 *p) {
   const u32x4_t w = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(p));
   return make_uint4(w.x, w.y, w.z, w.w);
 }
-__device__ __forceinline__ float4 stream_load(const float4 *p) {
-  const f32x4_t w = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t *>(p));
-  return make_float4(w.x, w.y, w.z, w.w);
-}
 
 // 2^x on the transcendental unit (about 1 ulp; results below 2^-126 flush to 0).
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -38,11 +34,6 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  return v;
-}
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
   return v;
 }
 
