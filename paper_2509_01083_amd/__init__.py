@@ -218,6 +218,8 @@ def step(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_ma
     updated in place; returns a dict of every output (accepted, tokens, kld, mu_last,
     var_short, var_long, wvir, sf, sl_hat, sl_cap, sl_next, seq_err, and draft_entropy
     when asked for).  ``budget`` [B] int32: tokens each sequence may still emit."""
+    if workspace is False:  # the marshalling's mark of dsde_step_static
+        raise DsdeError("workspace must be a GPU tensor")
     return _step(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, hist, head, count, sl_max,
                  n_short, n_long, delta, eps, sl_min, sl_hi, pad_id, out, workspace, row_lse, draft_entropy, budget,
                  stream)

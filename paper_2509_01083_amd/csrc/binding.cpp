@@ -111,18 +111,27 @@ int64_t size_of(PyObject *o, int64_t dim, const char *name) {
   if (t.dim() <= dim) fail(std::string(name) + " has too few dimensions");
   return t.size(dim);
 }
-// Outputs are taken from the caller's dict by key.
-PyObject *item(PyObject *dict, const char *key) {
-  PyObject *o = PyDict_GetItemString(dict, key);
-  if (!o) {
-    PyErr_SetString(PyExc_KeyError, key);
-    throw Failed{};
-  }
-  return o;
-}
+// Outputs are taken from the caller's dict, or other mapping, by key.  A
+// mapping's item is a new reference, dropped once its pointer is known (as
+// with the inputs, the caller keeps the tensor itself alive).
 template <typename T>
 T *out(PyObject *dict, const char *key, int type, int64_t n) {
-  return static_cast<T *>(ptr(item(dict, key), type, n, key));
+  if (PyDict_CheckExact(dict)) {
+    PyObject *o = PyDict_GetItemString(dict, key);
+    if (!o) {
+      PyErr_SetString(PyExc_KeyError, key);
+      throw Failed{};
+    }
+    return static_cast<T *>(ptr(o, type, n, key));
+  }
+  struct Ref {
+    PyObject *o;
+    ~Ref() { Py_XDECREF(o); }
+  };
+  const Ref k{PyUnicode_FromString(key)};
+  const Ref o{k.o ? PyObject_GetItem(dict, k.o) : nullptr};
+  if (!o.o) throw Failed{};
+  return static_cast<T *>(ptr(o.o, type, n, key));
 }
 
 int32_t logits_type(const at::Tensor &t) {
@@ -441,8 +450,7 @@ PyObject *py_shard_accept(PyObject *, PyObject *const *args, Py_ssize_t n) {
     const int32_t k_max = a.int32(), pad = a.int32();
     PyObject *dict = a.next(), *lse = a.next();
     const VerifyOut o = take_verify_out(dict, lse, a.flag(), B, N, k_max);
-    auto *jobs = static_cast<dsde_draw_job *>(
-        ptr(item(dict, "jobs"), kU8, B * int64_t(sizeof(dsde_draw_job)), "jobs"));
+    auto *jobs = out<dsde_draw_job>(dict, "jobs", kU8, B * int64_t(sizeof(dsde_draw_job)));
     uint32_t *err = take<uint32_t>(a, kAny, B, "seq_err");
     Signal s{};
     if (fused) s = take_signal(a, dict, B);

@@ -1,4 +1,6 @@
 """The binding's marshalling: the stream a call runs on, and what it refuses."""
+import collections
+
 import pytest
 import torch
 
@@ -79,4 +81,27 @@ def test_refusals(gpu_lib):
     small = torch.empty(64, dtype=torch.uint8, device="cuda")
     with pytest.raises(gpu_lib.DsdeError, match="workspace too small"):
         gpu_lib.step(*args, *_ring(st), st.sl_max, workspace=small)
+    with pytest.raises(gpu_lib.DsdeError, match="workspace must be a GPU tensor"):
+        gpu_lib.step(*args, *_ring(st), st.sl_max, workspace=False)
     torch.cuda.synchronize()
+
+
+def test_outputs_in_any_mapping(gpu_lib):
+    """Outputs are looked up by key: a mapping that is no dict, or a dict with a
+    lookup of its own, serves as well as a dict."""
+    step, st, args = _case()
+    want = gpu_lib.step(*args, *_ring(st), st.sl_max)
+
+    class Upper(dict):
+        def __getitem__(self, key):
+            return super().__getitem__(key.upper())
+
+    for out in (collections.UserDict({k: torch.zeros_like(want[k]) for k in NAMES}),
+                Upper({k.upper(): torch.zeros_like(want[k]) for k in NAMES})):
+        got = gpu_lib.step(*args, *_ring(st), st.sl_max, out=out)
+        torch.cuda.synchronize()
+        assert got is out
+        for k in NAMES:
+            assert torch.equal(out[k].view(torch.int32), want[k].view(torch.int32)), k
+    with pytest.raises(KeyError):
+        gpu_lib.step(*args, *_ring(st), st.sl_max, out=collections.UserDict())
