@@ -93,10 +93,12 @@ __device__ inline void wave_windows(const RingPrefetch<REGS> &rp, const float *r
     const float raw = ring_slot(rp, ring, W, i < W ? slot : 0);
     return i == 0 ? 0.0 : double(raw) - double(h1);
   };
-  // the first 64 entries stay in registers between the two passes
+  // the first 64 entries stay in registers between the two passes; a lane past
+  // a window adds nothing by selection, not by a weight of 0: its slot may never
+  // have been written, and 0 times what it holds can be NaN
   const double h0 = entry(lane), a0 = pow_int(delta, lane);
   double sa_s = lane < ns ? a0 : 0.0, sa_l = lane < nl ? a0 : 0.0;
-  double sah_s = sa_s * h0, sah_l = sa_l * h0;
+  double sah_s = lane < ns ? a0 * h0 : 0.0, sah_l = lane < nl ? a0 * h0 : 0.0;
   for (int32_t r = 64; r < nl; r += 64) {
     const int32_t i = lane + r;
     const double h = entry(i);
