@@ -5,6 +5,7 @@
 // and the inverse-CDF search over what those passes left behind.
 #pragma once
 
+#include <float.h>
 #include <math.h>
 
 #include "common.hpp"
@@ -349,9 +350,21 @@ __device__ __forceinline__ void target_p_unit(const char *trow, int64_t V, int32
   store_totals(unit_totals([&](int i) { return target_p_weight(t.at(i), job); }), c.sub, unit);
 }
 
+// The reference of a unit's exponentials: its largest z c.  Units that a
+// vocabulary mask covers whole need care: the rounding of a mask's z c (512 at
+// -1e10) is what the largest weight's exponent comes out as, so where it would
+// be large the reference is rounded up instead, which can only take such a unit's
+// weights to 0; and the type's lowest value times c can overflow.
+__device__ __forceinline__ float unit_reference(float M, float scale) {
+  const float ref = fmaxf(M * scale, -FLT_MAX);
+  if (fmaf(M, scale, -ref) <= 64.0f) return ref;
+  return __uint_as_float(__float_as_uint(ref) + (ref < 0.f ? -1 : 1));
+}
+
 // Bonus row, one unit: the exponentials 2^(z c - ref) against the unit's own
 // reference.  +inf shows in the maximum, -inf in the minimum, NaN in the
-// totals; padding is finite.
+// totals; padding is finite.  Where the row's last unit holds only logits below
+// the padding, the padding's weights are taken out.
 template <int DT, int ROW>
 __device__ __forceinline__ void bonus_unit(const char *trow, int64_t V, int32_t unit, float scale,
                                            const UnitCells &c) {
@@ -366,9 +379,14 @@ __device__ __forceinline__ void bonus_unit(const char *trow, int64_t V, int32_t 
     m = fmaxf(m, z);
     lo = fminf(lo, z);
   }
-  const float ref = lanes::wave_max(m) * scale;
-  const float w = unit_totals([&](int i) { return bonus_weight(t.at(i), scale, ref); });
-  const bool bad = __ballot(m == INFINITY || lo == -INFINITY || !isfinite(w)) != 0 || !isfinite(ref);
+  const float M = lanes::wave_max(m);
+  float ref = unit_reference(M, scale);
+  float w = unit_totals([&](int i) { return bonus_weight(t.at(i), scale, ref); });
+  if (M == kPadF32 && int64_t(unit) * kUnit + kUnit > V) {
+    w *= 0.0f;  // NaN stays NaN
+    ref = -FLT_MAX;
+  }
+  const bool bad = __ballot(m == INFINITY || lo == -INFINITY || !isfinite(w)) != 0 || ref == INFINITY;
   store_totals(w, c.sub, unit);
   if (lane == 0) c.ref[unit] = UnitRef{bad ? NAN : ref, 0};
 }

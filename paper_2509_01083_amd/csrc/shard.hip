@@ -456,6 +456,10 @@ __global__ __launch_bounds__(kShardThreads) void shard_pick_kernel(
     for (int32_t g = lane; g < G; g += 64) acc += weight(g, 1);
     Z = wave_sum_f64(acc);
   }
+  if (mode == 2 && !(Z > 0.0)) {  // a bonus row without weight
+    if (wave == 0) withhold();
+    return;
+  }
   const double target_mass = double(job.u) * Z;
   int32_t best = -1;
   double best_excl = 0.0, base = 0.0;

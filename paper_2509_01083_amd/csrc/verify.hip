@@ -333,12 +333,17 @@ __global__ __launch_bounds__(kCapThreads) void pick_kernel(const StepParams P, c
   int32_t *tok = P.tokens + int64_t(b) * width;
   int mode = job.kind == 0 ? 0 : 2;  // 0: residual weights, 1: p of the rejected pair, 2: bonus exponentials
   float row_ref = 0.f;
+  double Z = 0.0;  // the row's total weight
   if (job.kind != 0) {
     bool bad;
     row_ref = row_reference(cells, P.nu, cell0, &bad);
     if (wave != 0) return;
+    if (job.kind == 1) {
+      Z = row_total(cells, P.nu, cell0, mode, row_ref);
+      bad |= !(Z > 0.0);
+    }
     if (bad) {
-      // a NaN or infinite logit in the bonus row: no token is emitted
+      // a NaN or infinite logit in the bonus row, or no weight in it: no token is emitted
       if (lane < width) tok[lane] = P.pad_id;
       if (lane == 0) {
         P.accepted[b] = 0;
@@ -356,7 +361,7 @@ __global__ __launch_bounds__(kCapThreads) void pick_kernel(const StepParams P, c
   const char *trow = (const char *)P.target + size_t(job.target_row) * size_t(P.V) * esz;
   const char *drow =
       job.kind == 0 ? (const char *)P.draft + size_t(job.draft_row) * size_t(P.V) * esz : nullptr;
-  double Z = row_total(cells, P.nu, cell0, mode, row_ref);
+  if (mode == 0) Z = row_total(cells, P.nu, cell0, mode, row_ref);
   if (mode == 0 && !(Z > 0.0)) {  // no residual mass (the same in every wavefront): p of the same target row
     mode = 1;
     __syncthreads();  // every wavefront has read the residual's cells, which p's now replace

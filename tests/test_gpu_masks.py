@@ -2,7 +2,9 @@
 mask value on most tokens), where most of a row is one value."""
 import numpy as np
 import pytest
+import torch
 
+from tests.test_gpu_shard import check_sharded
 from tests.test_gpu_verify import check_step, random_arrays, step_from_arrays
 
 pytestmark = pytest.mark.gpu
@@ -40,3 +42,35 @@ def test_greedy_ties_over_whole_chunks(gpu_lib, V, dtype):
     got, _, _ = check_step(gpu_lib, step, f"greedy ties, rejected V={V} {dtype}")
     assert (got["accepted"] == 0).all()
     assert got["tokens"][:, 0].tolist() == want[bonus - np.asarray(sls)].tolist()
+
+
+@pytest.mark.parametrize("mask", ["lowest", -1e18, -1e10, -3e9])
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("V", [3000, 8192, 8200, 25000])
+def test_masked_units_of_a_bonus_row_weigh_nothing(gpu_lib, V, dtype, mask):
+    """Bonus rows under a mask that covers whole units of the draw, down to the
+    type's lowest value, whose product with log2(e) / T overflows or rounds by far
+    more than any exponent: such units weigh nothing and are not an error."""
+    value = float(torch.finfo(torch.bfloat16 if dtype == "bf16" else torch.float32).min) if mask == "lowest" else mask
+    rng = np.random.default_rng(V)
+    B = 15
+    none = np.zeros((0, V), np.float32)
+    target = np.full((B, V), value, np.float32)
+    allowed = sorted({0, 700, min(8191, V - 1), min(8192, V - 1), V - 1} | set(range(8192 + 100, V, 8192)))
+    for b in range(B):
+        keep = allowed if b < 8 else allowed[b % 3::2]  # from 8 on, some chunks hold no token at all
+        target[b, keep] = rng.normal(0, 1, len(keep))
+    temps = [(0.7, 1.0, 1.3, 2.0, 0.0)[b % 5] for b in range(B)]
+    step = step_from_arrays(target, none, [0] * B, [], temps, [], rng.random(B), 2, dtype)
+    got, _, rep = check_step(gpu_lib, step, f"mask {mask} V={V} {dtype}")
+    assert rep["errored"] == 0
+    check_sharded(gpu_lib, step, gpu_lib.slice_bounds(V, 3), f"mask {mask}, slices V={V} {dtype}")
+    # nothing unmasked: an error, or a token of the row
+    target[:] = value
+    temps = [(0.7, 1.0, 1.3, 2.0)[b % 4] for b in range(B)]
+    step = step_from_arrays(target, none, [0] * B, [], temps, [], rng.random(B), 2, dtype)
+    out = gpu_lib.verify(step.target, step.draft, step.sl, step.cu_sl, step.draft_tokens, step.temperature,
+                         step.u_acc, step.u_res, 2)
+    err, drawn = out["seq_err"].cpu().numpy(), out["tokens"][:, 0].cpu().numpy()
+    assert np.isin(err, (0, 4)).all()
+    assert (drawn[err != 0] == -1).all() and (drawn[err == 0] >= 0).all() and (drawn[err == 0] < V).all()
