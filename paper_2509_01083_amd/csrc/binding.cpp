@@ -146,7 +146,10 @@ struct Rows {
   int32_t dtype;
   int64_t V, N;
 };
-Rows take_rows(Args &a, int64_t B, bool check_draft, const char *what) {
+// A draft that does not match the target is refused: the kernels index both with
+// the target's element size and width.  `empty` refuses one without rows too,
+// which nothing reads.
+Rows take_rows(Args &a, int64_t B, const char *what, bool empty = true) {
   PyObject *t = a.next(), *d = a.next();
   const int64_t rows = size_of(t, 0, "target"), V = size_of(t, 1, "target");
   const at::Tensor &tt = THPVariable_Unpack(t);
@@ -154,7 +157,7 @@ Rows take_rows(Args &a, int64_t B, bool check_draft, const char *what) {
   r.dtype = logits_type(tt);
   r.V = V;
   r.N = d == Py_None ? 0 : size_of(d, 0, "draft");
-  if (check_draft && d != Py_None) {
+  if (d != Py_None && (empty || r.N > 0)) {
     const at::Tensor &dt = THPVariable_Unpack(d);
     if (dt.scalar_type() != tt.scalar_type() || (r.N > 0 && size_of(d, 1, "draft") != V))
       fail(std::string("draft ") + what + " must match the target's dtype and vocabulary");
@@ -275,7 +278,7 @@ PyObject *py_verify(PyObject *, PyObject *const *args, Py_ssize_t n) {
     if (n < 8) a.at = a.end;
     PyObject *const *batch = args + 2;
     const int64_t B = n < 8 ? 0 : size_of(batch[0], 0, "sl");
-    const Rows r = take_rows(a, B, true, "logits");
+    const Rows r = take_rows(a, B, "logits");
     const Batch x = take_batch(batch, B, r.N);
     a.at += 6;
     const int32_t k_max = a.int32(), pad = a.int32();
@@ -301,7 +304,7 @@ PyObject *py_step(PyObject *, PyObject *const *args, Py_ssize_t n) {
     if (n < 8) a.at = a.end;
     PyObject *const *batch = args + 2;
     const int64_t B = n < 8 ? 0 : size_of(batch[0], 0, "sl");
-    const Rows r = take_rows(a, B, false, "logits");
+    const Rows r = take_rows(a, B, "logits", false);
     const Batch x = take_batch(batch, B, r.N);
     a.at += 6;
     const int32_t k_max = a.int32(), pad = a.int32();
@@ -408,7 +411,7 @@ PyObject *py_shard_stats(PyObject *, PyObject *const *args, Py_ssize_t n) {
   return guarded(args, n, [&](Args &a) {
     if (n < 8) a.at = a.end;
     const int64_t B = n < 8 ? 0 : size_of(args[4], 0, "sl");
-    const Rows r = take_rows(a, B, true, "slice");
+    const Rows r = take_rows(a, B, "slice");
     const int64_t v_begin = a.integer(), V = a.integer();
     const int32_t *sl = take<int32_t>(a, kI32, B, "sl"), *cu = take<int32_t>(a, kI32, B + 1, "cu_sl");
     PyObject *tok_o = a.next();
@@ -475,7 +478,7 @@ PyObject *py_shard_draw_mass(PyObject *, PyObject *const *args, Py_ssize_t n) {
   return guarded(args, n, [&](Args &a) {
     if (n < 5) a.at = a.end;
     const int64_t B = n < 5 ? 0 : size_of(args[4], 0, "jobs");
-    const Rows r = take_rows(a, B, true, "slice");
+    const Rows r = take_rows(a, B, "slice");
     const int64_t v_begin = a.integer();
     PyObject *part_o = a.next();
     void *part = r.N > 0 ? ptr(part_o, kU8, r.N * int64_t(sizeof(dsde_shard_partial)), "part") : nullptr;
@@ -501,7 +504,7 @@ PyObject *py_shard_draw_pick(PyObject *, PyObject *const *args, Py_ssize_t n) {
     PyObject *masses_o = a.next();
     if (n < 6) a.at = a.end;
     const int64_t G = size_of(masses_o, 0, "masses"), B = n < 6 ? 0 : size_of(args[5], 0, "jobs");
-    const Rows r = take_rows(a, B, true, "slice");
+    const Rows r = take_rows(a, B, "slice");
     const auto *masses = static_cast<const dsde_shard_mass *>(
         ptr(masses_o, kU8, G * B * int64_t(sizeof(dsde_shard_mass)), "masses"));
     const int64_t v_begin = a.integer();
