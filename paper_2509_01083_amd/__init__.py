@@ -7,6 +7,7 @@ marshals pointers and the current HIP stream; every step of the computation
 runs in the library's HIP kernels.  There is no CPU fallback: if a library is
 missing, ``load`` or the first call raises.
 """
+import contextlib
 import ctypes
 import os
 
@@ -112,6 +113,20 @@ def _handle(stream):
     return None if stream is None else stream.cuda_stream
 
 
+_HERE = contextlib.nullcontext()
+
+
+def _on(stream):
+    """Context for the buffers a call makes itself, its workspace above all, which is
+    given back when the call returns, while its kernels run: made on the call's
+    stream, the allocator reuses them only behind those kernels."""
+    if stream is None:
+        return _HERE
+    if not isinstance(stream, torch.cuda.Stream):  # any object with the raw handle
+        stream = torch.cuda.ExternalStream(stream.cuda_stream)
+    return torch.cuda.stream(stream)
+
+
 def _check(rc):
     if rc != OK:
         raise DsdeError(f"libdsde: {load().dsde_status_string(rc).decode()} (status {rc})")
@@ -173,20 +188,29 @@ def _with_entropy(out, wanted, N, dev):
         out["draft_entropy"] = torch.empty(max(N, 1), dtype=torch.float32, device=dev)[:N]
 
 
+def _buffers(target, draft, sl, k_max, out, workspace, draft_entropy, signal):
+    """The outputs and the workspace of a verify or step call, made where the caller gave none."""
+    B, N, dev = int(sl.shape[0]), _rows(draft), target.device
+    if out is None:
+        out = _new_verify_out(B, N, k_max, dev)
+        out["seq_err"] = torch.empty(B, dtype=torch.int32, device=dev)
+        if signal:
+            _new_signal_out(out, B, dev)
+    _with_entropy(out, draft_entropy, N, dev)
+    if workspace is None:
+        workspace = new_workspace(B, N, int(target.shape[1]), k_max, device=dev)
+    return out, workspace
+
+
 def verify(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, pad_id=-1,
            out=None, workspace=None, row_lse=None, draft_entropy=False, stream=None):
     """``dsde_verify`` on torch tensors.  Returns a dict with accepted, tokens, kld,
     seq_err (and draft_entropy when asked for); pass ``out`` (a dict with those
     keys) to reuse output buffers."""
     native = _native or _bind()
-    if out is None:
-        B = int(sl.shape[0])
-        out = _new_verify_out(B, _rows(draft), k_max, target.device)
-        out["seq_err"] = torch.empty(B, dtype=torch.int32, device=target.device)
-    if draft_entropy:
-        _with_entropy(out, True, _rows(draft), target.device)
-    if workspace is None:
-        workspace = new_workspace(int(sl.shape[0]), _rows(draft), int(target.shape[1]), k_max, device=target.device)
+    if out is None or workspace is None or draft_entropy:
+        with _on(stream):
+            out, workspace = _buffers(target, draft, sl, k_max, out, workspace, draft_entropy, False)
     native.verify(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, int(pad_id), out, row_lse,
                   draft_entropy, workspace, _handle(stream))
     return out
@@ -196,15 +220,9 @@ def _step(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_m
           n_short, n_long, delta, eps, sl_min, sl_hi, pad_id, out, workspace, row_lse, draft_entropy, budget, stream):
     """dsde_step, or with ``workspace`` False dsde_step_static."""
     native = _native or _bind()
-    if out is None:
-        B = int(sl.shape[0])
-        out = _new_verify_out(B, _rows(draft), k_max, target.device)
-        out["seq_err"] = torch.empty(B, dtype=torch.int32, device=target.device)
-        _new_signal_out(out, B, target.device)
-    if draft_entropy:
-        _with_entropy(out, True, _rows(draft), target.device)
-    if workspace is None:
-        workspace = new_workspace(int(sl.shape[0]), _rows(draft), int(target.shape[1]), k_max, device=target.device)
+    if out is None or workspace is None or draft_entropy:
+        with _on(stream):
+            out, workspace = _buffers(target, draft, sl, k_max, out, workspace, draft_entropy, True)
     native.step(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, int(pad_id), out, row_lse,
                 draft_entropy, hist, head, count, sl_max, n_short, n_long, delta, eps, sl_min,
                 k_max if sl_hi is None else int(sl_hi), budget, workspace, _handle(stream))
@@ -243,9 +261,10 @@ def kld_signal(sl, cu_sl, kld, hist, head, count, n_short=10, n_long=30, delta=0
     native = _native or _bind()
     if out is None:
         B, dev = int(sl.shape[0]), sl.device
-        out = {k: torch.empty(B, dtype=torch.float32, device=dev)
-               for k in ("mu_last", "var_short", "var_long", "wvir", "sf")}
-        out["seq_err"] = torch.empty(B, dtype=torch.int32, device=dev)
+        with _on(stream):
+            out = {k: torch.empty(B, dtype=torch.float32, device=dev)
+                   for k in ("mu_last", "var_short", "var_long", "wvir", "sf")}
+            out["seq_err"] = torch.empty(B, dtype=torch.int32, device=dev)
     native.kld_signal(sl, cu_sl, kld, hist, head, count, n_short, n_long, delta, eps, out, _handle(stream))
     return out
 
@@ -256,10 +275,11 @@ def next_sl(sf, wvir, sl_max, sl_min=2.0, sl_hi=8, budget=None, out=None, stream
     native = _native or _bind()
     if out is None:
         B, dev = int(sf.shape[0]), sf.device
-        out = {"sl_hat": torch.empty(B, dtype=torch.float32, device=dev),
-               "sl_cap": torch.empty(1, dtype=torch.float32, device=dev),
-               "sl_next": torch.empty(B, dtype=torch.int32, device=dev),
-               "seq_err": torch.empty(B, dtype=torch.int32, device=dev)}
+        with _on(stream):
+            out = {"sl_hat": torch.empty(B, dtype=torch.float32, device=dev),
+                   "sl_cap": torch.empty(1, dtype=torch.float32, device=dev),
+                   "sl_next": torch.empty(B, dtype=torch.int32, device=dev),
+                   "seq_err": torch.empty(B, dtype=torch.int32, device=dev)}
     native.next_sl(sf, wvir, sl_max, sl_min, int(sl_hi), budget, out, _handle(stream))
     return out
 
@@ -282,7 +302,8 @@ def calibrate_sl_max(state, eps=1e-6, pooled=False, out=None, stream=None):
     lib = load()
     B = int(state["a_max"].shape[0])
     if out is None:
-        out = torch.empty(B, dtype=torch.float32, device=state["a_max"].device)
+        with _on(stream):
+            out = torch.empty(B, dtype=torch.float32, device=state["a_max"].device)
     _check(lib.dsde_calibrate_sl_max(
         B, _ptr(state["a_max"], torch.int32, B), _ptr(state["kld_sum"], torch.float64, B),
         _ptr(state["kld_count"], torch.int64, B), _ptr(state["kld_max"], torch.float32, B), float(eps),
@@ -332,17 +353,21 @@ def shard_stats(target, draft, v_begin, V, sl, cu_sl, draft_tokens, temperature,
     """``dsde_shard_stats`` (call 1) on this shard's slices [rows, V_shard].  Returns
     (part [N, 64] uint8 records, seq_err [B] int32)."""
     native = _native or _bind()
-    if part is None:
-        part = torch.empty((max(_rows(draft), 1), SHARD_PARTIAL_BYTES), dtype=torch.uint8, device=target.device)
-    if seq_err is None:
-        seq_err = torch.empty(int(sl.shape[0]), dtype=torch.int32, device=target.device)
+    if part is None or seq_err is None:
+        with _on(stream):
+            if part is None:
+                part = torch.empty((max(_rows(draft), 1), SHARD_PARTIAL_BYTES), dtype=torch.uint8,
+                                   device=target.device)
+            if seq_err is None:
+                seq_err = torch.empty(int(sl.shape[0]), dtype=torch.int32, device=target.device)
     native.shard_stats(target, draft, int(v_begin), int(V), sl, cu_sl, draft_tokens, temperature, k_max, workspace,
                        part, seq_err, _handle(stream))
     return part, seq_err
 
 
-def _shard_accept_out(parts, sl, draft_tokens, k_max, seq_err, draft_entropy, out, stream):
-    """Output buffers and packed partials shared by the two call-2 entry points."""
+def _shard_accept_out(parts, sl, draft_tokens, k_max, seq_err, draft_entropy, out, signal):
+    """Output buffers and packed partials shared by the two call-2 entry points (the
+    packed copy is made on the call's stream, ahead of the call)."""
     N = _rows(draft_tokens)
     if N > 0 and (parts.dim() != 3 or int(parts.shape[1]) < N or int(parts.shape[2]) != SHARD_PARTIAL_BYTES):
         raise DsdeError("parts must be [G, N, 64] uint8")
@@ -352,10 +377,10 @@ def _shard_accept_out(parts, sl, draft_tokens, k_max, seq_err, draft_entropy, ou
         out["jobs"] = torch.empty((B, DRAW_JOB_BYTES), dtype=torch.uint8, device=sl.device)
     out["seq_err"] = seq_err
     _with_entropy(out, draft_entropy, N, sl.device)
+    if signal:
+        _new_signal_out(out, int(sl.shape[0]), sl.device)
     if N > 0 and int(parts.shape[1]) != N:
-        # the packed copy is made on the call's stream, ahead of the call
-        with torch.cuda.stream(stream if stream is not None else torch.cuda.current_stream()):
-            parts = parts[:, :N].contiguous()
+        parts = parts[:, :N].contiguous()
     return out, parts
 
 
@@ -365,7 +390,8 @@ def shard_accept(parts, V, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k
     (uint8, shard order).  seq_err (call 1's) is updated in place.  Returns a dict
     with accepted, tokens, kld, seq_err, jobs [B, 44] uint8 (and draft_entropy)."""
     native = _native or _bind()
-    out, parts = _shard_accept_out(parts, sl, draft_tokens, k_max, seq_err, draft_entropy, out, stream)
+    with _on(stream):
+        out, parts = _shard_accept_out(parts, sl, draft_tokens, k_max, seq_err, draft_entropy, out, False)
     native.shard_accept(False, parts, int(V), sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, int(pad_id),
                         out, row_lse, draft_entropy, seq_err, _handle(stream))
     return out
@@ -379,8 +405,8 @@ def shard_accept_step(parts, V, sl, cu_sl, draft_tokens, temperature, u_acc, u_r
     shard_accept plus mu_last, var_short, var_long, wvir, sf, sl_hat, sl_cap,
     sl_next."""
     native = _native or _bind()
-    out, parts = _shard_accept_out(parts, sl, draft_tokens, k_max, seq_err, draft_entropy, out, stream)
-    _new_signal_out(out, int(sl.shape[0]), sl.device)
+    with _on(stream):
+        out, parts = _shard_accept_out(parts, sl, draft_tokens, k_max, seq_err, draft_entropy, out, True)
     native.shard_accept(True, parts, int(V), sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, int(pad_id),
                         out, row_lse, draft_entropy, seq_err, hist, head, count, sl_max, n_short, n_long, delta, eps,
                         sl_min, k_max if sl_hi is None else int(sl_hi), budget, _handle(stream))
@@ -391,7 +417,8 @@ def shard_draw_mass(target, draft, v_begin, part, jobs, k_max, workspace, mass=N
     """``dsde_shard_draw_mass`` (call 3).  Returns mass [B, 32] uint8 records."""
     native = _native or _bind()
     if mass is None:
-        mass = torch.empty((int(jobs.shape[0]), SHARD_MASS_BYTES), dtype=torch.uint8, device=target.device)
+        with _on(stream):
+            mass = torch.empty((int(jobs.shape[0]), SHARD_MASS_BYTES), dtype=torch.uint8, device=target.device)
     native.shard_draw_mass(target, draft, int(v_begin), part, jobs, k_max, workspace, mass, _handle(stream))
     return mass
 
@@ -404,7 +431,8 @@ def shard_draw_pick(g, masses, target, draft, v_begin, jobs, k_max, accepted, to
     else -1)."""
     native = _native or _bind()
     if drawn is None:
-        drawn = torch.empty(int(jobs.shape[0]), dtype=torch.int32, device=target.device)
+        with _on(stream):
+            drawn = torch.empty(int(jobs.shape[0]), dtype=torch.int32, device=target.device)
     native.shard_draw_pick(int(g), masses, target, draft, int(v_begin), jobs, k_max, int(pad_id), accepted, tokens,
                            drawn, seq_err, workspace, _handle(stream))
     return drawn

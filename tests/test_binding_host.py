@@ -51,3 +51,91 @@ def test_step_takes_an_empty_draft_of_any_type(dsde):
     for draft in (torch.zeros(0, 64), torch.zeros(0, 0, dtype=torch.bfloat16), None):
         with pytest.raises(dsde.DsdeError, match="target must be a GPU tensor"):
             call(dsde, "step", dict(args, draft=draft))
+
+
+class Recorder(torch.overrides.TorchFunctionMode):
+    """The stream in force at every allocation of a call."""
+
+    def __init__(self, stack):
+        super().__init__()
+        self.stack, self.seen = stack, []
+
+    def __torch_function__(self, func, types, args=(), kwargs=None):
+        if func in (torch.empty, torch.Tensor.contiguous):
+            self.seen.append(self.stack[-1])
+        return func(*args, **(kwargs or {}))
+
+
+class FakeStream:
+    cuda_stream = 77
+
+
+class RawStream:  # an object with the raw handle alone
+    cuda_stream = 78
+
+
+class FakeNative:
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def calls_with_own_buffers(dsde):
+    """Every call that makes buffers of its own, as (name, function of the stream, allocations)."""
+    a = step_args()
+    rows = tuple(a[k] for k in VERIFY)
+    batch, k = rows[2:8], a["k_max"]
+    ring = (a["hist"], a["head"], a["count"])
+    u8 = dict(dtype=torch.uint8)
+    parts, jobs = torch.zeros(2, 4, 64, **u8), torch.zeros(3, 44, **u8)
+    err, ws = torch.zeros(3, dtype=torch.int32), torch.zeros(4096, **u8)
+    out = dict(accepted=err, tokens=err, kld=a["u_acc"], seq_err=err, jobs=jobs)
+    return [
+        ("verify", lambda s: dsde.verify(*rows, stream=s), 5),
+        ("verify, entropy", lambda s: dsde.verify(*rows, out=dict(out), draft_entropy=True, workspace=ws, stream=s), 1),
+        ("verify, workspace", lambda s: dsde.verify(*rows, out=out, stream=s), 1),
+        ("step", lambda s: dsde.step(*rows, *ring, a["sl_max"], draft_entropy=True, stream=s), 14),
+        ("step_static", lambda s: dsde.step_static(*rows, *ring, a["sl_max"], stream=s), 12),
+        ("kld_signal", lambda s: dsde.kld_signal(rows[2], rows[3], a["u_acc"], *ring, stream=s), 6),
+        ("next_sl", lambda s: dsde.next_sl(a["u_res"], a["u_res"], a["sl_max"], stream=s), 4),
+        ("shard_stats", lambda s: dsde.shard_stats(*rows[:2], 0, 64, *batch[:4], k, ws, stream=s), 2),
+        ("shard_accept", lambda s: dsde.shard_accept(torch.zeros(2, 6, 64, **u8), 64, *batch, k, err, stream=s), 5),
+        ("shard_accept_step", lambda s: dsde.shard_accept_step(parts, 64, *batch, k, err, *ring, a["sl_max"],
+                                                               stream=s), 12),
+        ("shard_draw_mass", lambda s: dsde.shard_draw_mass(*rows[:2], 0, parts[0], jobs, k, ws, stream=s), 1),
+        ("shard_draw_pick", lambda s: dsde.shard_draw_pick(0, jobs, *rows[:2], 0, jobs, k, err, err, err, ws,
+                                                           stream=s), 1),
+    ]
+
+
+@pytest.mark.parametrize("stream", [None, FakeStream(), RawStream()])
+def test_own_buffers_belong_to_the_calls_stream(dsde, monkeypatch, stream):
+    """A workspace that a call makes goes back to the allocator when the call
+    returns, with its kernels still to run: unless it was made on their stream,
+    the next tensor of the current stream can take its memory from under them."""
+    stack = ["current"]
+
+    class On:
+        def __init__(self, s):
+            self.s = s
+
+        def __enter__(self):
+            stack.append(self.s)
+
+        def __exit__(self, *exc):
+            stack.pop()
+
+    monkeypatch.setattr(dsde, "_native", FakeNative())
+    monkeypatch.setattr(torch.cuda, "stream", On)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: "current")
+    monkeypatch.setattr(torch.cuda, "Stream", FakeStream)
+    monkeypatch.setattr(torch.cuda, "ExternalStream", lambda handle: handle)
+    want = "current" if stream is None else 78 if isinstance(stream, RawStream) else stream
+    for name, f, n in calls_with_own_buffers(dsde):
+        with Recorder(stack) as seen:
+            f(stream)
+        assert seen.seen == [want] * n, name
+        assert stack == ["current"]
+    with Recorder(stack) as seen:  # calibrate_sl_max calls the library itself, which refuses the CPU's tensors
+        with pytest.raises(dsde.DsdeError, match="GPU tensor"):
+            dsde.calibrate_sl_max(dsde.new_calibration_state(3, device="cpu"), stream=stream)
+    assert seen.seen == [want]

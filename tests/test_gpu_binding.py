@@ -35,6 +35,7 @@ def test_calls_follow_the_current_stream(gpu_lib):
     ws = gpu_lib.new_workspace(step.B, step.N, step.V, step.k_max)
     out = {k: torch.zeros_like(want[k]) for k in NAMES}
     side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())  # the copies and the fills above
     with torch.cuda.stream(side):
         gpu_lib.step(*args, *ring, st.sl_max, out=out, workspace=ws)
     side.synchronize()
@@ -52,10 +53,14 @@ def test_calls_follow_the_current_stream(gpu_lib):
         torch.cuda.synchronize()
         for k in NAMES:
             assert torch.equal(out[k].view(torch.int32), want[k].view(torch.int32)), k
-    given = gpu_lib.step(*args, *_ring(st), st.sl_max, stream=side)
+    ring = _ring(st)
+    side.wait_stream(torch.cuda.current_stream())
+    given = gpu_lib.step(*args, *ring, st.sl_max, stream=side)  # outputs and workspace made by the call
+    taken = [torch.full_like(ws, 255) for _ in range(4)]  # the current stream's next tensors of that size
     side.synchronize()
     for k in NAMES:
         assert torch.equal(given[k].view(torch.int32), want[k].view(torch.int32)), k
+    del taken
 
 
 def test_refusals(gpu_lib):
