@@ -95,15 +95,17 @@ def load(path: str = LIB_PATH):
 
 
 def _bind():
-    """The marshalling extension (built beside libdsde.so); raises when it is absent."""
+    """The marshalling extension (built beside libdsde.so), calling the loaded
+    library; raises when it is absent."""
     global _native
     if _native is None:
-        load()
+        lib = load()
         try:
             from . import _binding
         except ImportError as e:
             raise DsdeError(f"_binding.so: {e}: build it with __graft_entry__.build()") from e
         _binding.set_error(DsdeError)
+        _binding.set_library(lib._handle)
         _native = _binding
     return _native
 

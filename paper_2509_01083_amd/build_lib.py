@@ -16,8 +16,8 @@ fails if any packed FP32 arithmetic instruction is found
 (``packed_fp32_instructions``; a CPU test runs the same check).
 
 ``build`` then compiles the Python binding's marshalling code
-(csrc/binding.cpp, host code only) against torch's headers and links it to the
-library beside it.
+(csrc/binding.cpp, host code only) against torch's headers; it takes its entry
+points from the library that the package loads.
 """
 import os
 import re
@@ -75,7 +75,7 @@ def build(verbose: bool = False) -> str:
 
 
 def build_binding(verbose: bool = False) -> str:
-    """The marshalling extension, linked to the libdsde.so in its own folder."""
+    """The marshalling extension."""
     import sysconfig
 
     from torch.utils import cpp_extension
@@ -84,8 +84,8 @@ def build_binding(verbose: bool = False) -> str:
     tmp = BINDING + ".tmp"
     _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
           "-I", os.path.join(ROOT, "include"), "-isystem", sysconfig.get_paths()["include"], *includes,
-          os.path.join(CSRC, "binding.cpp"), "-o", tmp, "-L", HERE, "-l:libdsde.so", "-Wl,-rpath,$ORIGIN", *libs,
-          "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"], verbose)
+          os.path.join(CSRC, "binding.cpp"), "-o", tmp, *libs,
+          "-ldl", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"], verbose)
     os.replace(tmp, BINDING)
     return BINDING
 

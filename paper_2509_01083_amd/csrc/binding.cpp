@@ -7,6 +7,7 @@
 // step's kernels take in small batches.
 #include <Python.h>
 #include <c10/hip/HIPStream.h>
+#include <dlfcn.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <string>
@@ -16,6 +17,18 @@
 namespace {
 
 PyObject *g_error = nullptr;  // paper_2509_01083_amd.DsdeError
+
+// The entry points, looked up in the library that the package has loaded
+// (set_library), which need not be the one beside this file.
+#define DSDE_ENTRIES(X)                                                                                         \
+  X(dsde_status_string)                                                                                         \
+  X(dsde_verify) X(dsde_step) X(dsde_step_static) X(dsde_kld_signal) X(dsde_next_sl) X(dsde_calibration_update) \
+  X(dsde_shard_stats) X(dsde_shard_accept) X(dsde_shard_accept_step) X(dsde_shard_draw_mass) X(dsde_shard_draw_pick)
+struct Library {
+#define X(name) decltype(&::name) name;
+  DSDE_ENTRIES(X)
+#undef X
+} g_lib;
 
 struct Failed {};  // a Python exception is set
 
@@ -252,7 +265,7 @@ void call(F f) {
   int32_t rc;
   Py_BEGIN_ALLOW_THREADS rc = f();
   Py_END_ALLOW_THREADS if (rc != DSDE_OK)
-      fail(std::string("libdsde: ") + dsde_status_string(rc) + " (status " + std::to_string(rc) + ")");
+      fail(std::string("libdsde: ") + g_lib.dsde_status_string(rc) + " (status " + std::to_string(rc) + ")");
 }
 
 // Runs one function body; C++ exceptions become Python ones.
@@ -289,7 +302,7 @@ PyObject *py_verify(PyObject *, PyObject *const *args, Py_ssize_t n) {
     void *ws = take_workspace(a, &bytes), *stream = a.stream();
     a.done();
     call([&] {
-      return dsde_verify(r.target, r.draft, r.dtype, r.V, int32_t(B), r.N, k_max, x.sl, x.cu_sl, x.tokens,
+      return g_lib.dsde_verify(r.target, r.draft, r.dtype, r.V, int32_t(B), r.N, k_max, x.sl, x.cu_sl, x.tokens,
                          x.temperature, x.u_acc, x.u_res, pad, o.accepted, o.tokens, o.kld, err, o.row_lse, o.entropy,
                          ws, bytes, stream);
     });
@@ -323,12 +336,12 @@ PyObject *py_step(PyObject *, PyObject *const *args, Py_ssize_t n) {
     a.done();
     call([&] {
       if (fixed)
-        return dsde_step_static(r.target, r.draft, r.dtype, r.V, int32_t(B), r.N, k_max, x.sl, x.cu_sl, x.tokens,
+        return g_lib.dsde_step_static(r.target, r.draft, r.dtype, r.V, int32_t(B), r.N, k_max, x.sl, x.cu_sl, x.tokens,
                                 x.temperature, x.u_acc, x.u_res, pad, o.accepted, o.tokens, o.kld, o.row_lse,
                                 o.entropy, s.hist, s.head, s.count, s.W, s.n_short, s.n_long, s.delta, s.eps,
                                 s.mu_last, s.var_short, s.var_long, s.wvir, s.sf, s.sl_max, s.sl_min, s.sl_hi,
                                 s.budget, s.sl_hat, s.sl_cap, s.sl_next, err, stream);
-      return dsde_step(r.target, r.draft, r.dtype, r.V, int32_t(B), r.N, k_max, x.sl, x.cu_sl, x.tokens,
+      return g_lib.dsde_step(r.target, r.draft, r.dtype, r.V, int32_t(B), r.N, k_max, x.sl, x.cu_sl, x.tokens,
                        x.temperature, x.u_acc, x.u_res, pad, o.accepted, o.tokens, o.kld, o.row_lse, o.entropy, s.hist,
                        s.head, s.count, s.W, s.n_short, s.n_long, s.delta, s.eps, s.mu_last, s.var_short, s.var_long,
                        s.wvir, s.sf, s.sl_max, s.sl_min, s.sl_hi, s.budget, s.sl_hat, s.sl_cap, s.sl_next, err, ws,
@@ -357,7 +370,7 @@ PyObject *py_kld_signal(PyObject *, PyObject *const *args, Py_ssize_t n) {
     void *stream = a.stream();
     a.done();
     call([&] {
-      return dsde_kld_signal(int32_t(B), N, sl, cu, kld, hist, head, count, int32_t(W), n_short, n_long, delta, eps, mu,
+      return g_lib.dsde_kld_signal(int32_t(B), N, sl, cu, kld, hist, head, count, int32_t(W), n_short, n_long, delta, eps, mu,
                              vs, vl, wvir, sf, err, stream);
     });
   });
@@ -380,7 +393,7 @@ PyObject *py_next_sl(PyObject *, PyObject *const *args, Py_ssize_t n) {
     void *stream = a.stream();
     a.done();
     call([&] {
-      return dsde_next_sl(int32_t(B), sf, wvir, sl_max, sl_min, sl_hi, budget, hat, cap, next, err, stream);
+      return g_lib.dsde_next_sl(int32_t(B), sf, wvir, sl_max, sl_min, sl_hi, budget, hat, cap, next, err, stream);
     });
   });
 }
@@ -402,7 +415,7 @@ PyObject *py_calibration_update(PyObject *, PyObject *const *args, Py_ssize_t n)
     float *kmax = out<float>(d, "kld_max", kF32, B);
     void *stream = a.stream();
     a.done();
-    call([&] { return dsde_calibration_update(int32_t(B), N, sl, cu, acc, kld, err, a_max, sum, cnt, kmax, stream); });
+    call([&] { return g_lib.dsde_calibration_update(int32_t(B), N, sl, cu, acc, kld, err, a_max, sum, cnt, kmax, stream); });
   });
 }
 
@@ -426,7 +439,7 @@ PyObject *py_shard_stats(PyObject *, PyObject *const *args, Py_ssize_t n) {
     void *stream = a.stream();
     a.done();
     call([&] {
-      return dsde_shard_stats(r.target, r.draft, r.dtype, r.V, v_begin, V, int32_t(B), r.N, k_max, sl, cu, tok, temp,
+      return g_lib.dsde_shard_stats(r.target, r.draft, r.dtype, r.V, v_begin, V, int32_t(B), r.N, k_max, sl, cu, tok, temp,
                               static_cast<dsde_shard_partial *>(part), err, ws, bytes, stream);
     });
   });
@@ -461,10 +474,10 @@ PyObject *py_shard_accept(PyObject *, PyObject *const *args, Py_ssize_t n) {
     a.done();
     call([&] {
       if (!fused)
-        return dsde_shard_accept(int32_t(G), parts, V, int32_t(B), N, k_max, x.sl, x.cu_sl, x.tokens, x.temperature,
+        return g_lib.dsde_shard_accept(int32_t(G), parts, V, int32_t(B), N, k_max, x.sl, x.cu_sl, x.tokens, x.temperature,
                                  x.u_acc, x.u_res, pad, o.accepted, o.tokens, o.kld, o.row_lse, o.entropy, jobs, err,
                                  stream);
-      return dsde_shard_accept_step(int32_t(G), parts, V, int32_t(B), N, k_max, x.sl, x.cu_sl, x.tokens, x.temperature,
+      return g_lib.dsde_shard_accept_step(int32_t(G), parts, V, int32_t(B), N, k_max, x.sl, x.cu_sl, x.tokens, x.temperature,
                                     x.u_acc, x.u_res, pad, o.accepted, o.tokens, o.kld, o.row_lse, o.entropy, jobs,
                                     s.hist, s.head, s.count, s.W, s.n_short, s.n_long, s.delta, s.eps, s.mu_last,
                                     s.var_short, s.var_long, s.wvir, s.sf, s.sl_max, s.sl_min, s.sl_hi, s.budget,
@@ -490,7 +503,7 @@ PyObject *py_shard_draw_mass(PyObject *, PyObject *const *args, Py_ssize_t n) {
     void *stream = a.stream();
     a.done();
     call([&] {
-      return dsde_shard_draw_mass(r.target, r.draft, r.dtype, r.V, v_begin, int32_t(B), r.N, k_max,
+      return g_lib.dsde_shard_draw_mass(r.target, r.draft, r.dtype, r.V, v_begin, int32_t(B), r.N, k_max,
                                   static_cast<const dsde_shard_partial *>(part), jobs, mass, ws, bytes, stream);
     });
   });
@@ -517,7 +530,7 @@ PyObject *py_shard_draw_pick(PyObject *, PyObject *const *args, Py_ssize_t n) {
     void *ws = take_workspace(a, &bytes), *stream = a.stream();
     a.done();
     call([&] {
-      return dsde_shard_draw_pick(int32_t(G), g, masses, r.target, r.draft, r.dtype, r.V, v_begin, int32_t(B), r.N,
+      return g_lib.dsde_shard_draw_pick(int32_t(G), g, masses, r.target, r.draft, r.dtype, r.V, v_begin, int32_t(B), r.N,
                                   k_max, jobs, pad, accepted, tokens, drawn, err, ws, bytes, stream);
     });
   });
@@ -528,6 +541,25 @@ PyObject *py_set_error(PyObject *, PyObject *type) {
   Py_INCREF(type);
   Py_XDECREF(g_error);
   g_error = type;
+  Py_RETURN_NONE;
+}
+
+// set_library(handle): takes the entry points from a library's dlopen handle
+PyObject *py_set_library(PyObject *, PyObject *handle) {
+  void *h = PyLong_AsVoidPtr(handle);
+  if (!h) {
+    if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "no library handle");
+    return nullptr;
+  }
+  Library lib;
+#define X(name)                                                                      \
+  if (!(lib.name = reinterpret_cast<decltype(lib.name)>(dlsym(h, #name)))) {         \
+    PyErr_SetString(g_error ? g_error : PyExc_RuntimeError, "libdsde lacks " #name); \
+    return nullptr;                                                                  \
+  }
+  DSDE_ENTRIES(X)
+#undef X
+  g_lib = lib;
   Py_RETURN_NONE;
 }
 
@@ -545,6 +577,7 @@ PyMethodDef g_methods[] = {entry("verify", py_verify),
                            entry("shard_draw_mass", py_shard_draw_mass),
                            entry("shard_draw_pick", py_shard_draw_pick),
                            {"set_error", py_set_error, METH_O, nullptr},
+                           {"set_library", py_set_library, METH_O, nullptr},
                            {nullptr, nullptr, 0, nullptr}};
 PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, g_methods};
 

@@ -1,5 +1,9 @@
 """Host-side checks of the Python binding (no GPU needed): what it refuses before
 it looks at a device pointer."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -139,3 +143,18 @@ def test_own_buffers_belong_to_the_calls_stream(dsde, monkeypatch, stream):
         with pytest.raises(dsde.DsdeError, match="GPU tensor"):
             dsde.calibrate_sl_max(dsde.new_calibration_state(3, device="cpu"), stream=stream)
     assert seen.seen == [want]
+
+
+def test_the_loaded_library_serves_every_call(dsde, tmp_path):
+    """load(path) decides which library runs, for the marshalled calls too: with a
+    copy loaded from elsewhere the package's own is not even mapped."""
+    copy = tmp_path / "copy_of_the_library.so"
+    copy.write_bytes(open(dsde.LIB_PATH, "rb").read())
+    code = ("import sys, torch, paper_2509_01083_amd as d\n"
+            "d.load(sys.argv[1]); d._bind()\n"
+            "print([l.split()[-1] for l in open('/proc/self/maps') if 'r-xp' in l and l.rstrip().endswith('.so')])\n")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    maps = subprocess.run([sys.executable, "-c", code, str(copy)], cwd=root, capture_output=True, text=True,
+                          check=True).stdout
+    assert str(copy) in maps
+    assert dsde.LIB_PATH not in maps
