@@ -8,7 +8,7 @@ namespace dsde {
 
 // One shard's workspace: the statistics pass's buffers for the slice width,
 // then the draw's unit cells of every sequence (call 3 writes them, call 4
-// reads them).
+// reads them) where the unsharded draw's jobs and cells would lie.
 struct ShardLayout {
   WorkspaceLayout stats;
   size_t sub, ref, total;
@@ -18,7 +18,7 @@ inline ShardLayout shard_layout(int32_t B, int64_t N, int64_t V_shard, int32_t k
   ShardLayout L;
   L.stats = workspace_layout(B, N, V_shard, k_max);
   const size_t cells = size_t(B) * size_t(num_units(V_shard));
-  size_t off = L.stats.total;
+  size_t off = L.stats.stats_total;
   L.sub = off;
   off += align_up(4 * sizeof(float) * cells);
   L.ref = off;

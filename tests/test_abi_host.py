@@ -163,7 +163,13 @@ def test_calibrate_sl_max_rejects_invalid_arguments(lib, over):
 def test_shard_workspace_sizes(lib):
     ws = lib.dsde_shard_workspace_bytes
     assert ws(256, 1152, 16032, 8) > 0
-    assert ws(256, 1152, 16032, 8) > lib.dsde_verify_workspace_bytes(256, 1152, 16032, 8)
+    # work items, and per slot b * k_max + j the gathered logits and per chunk of 8192 a
+    # partial and an argmax; then the cells of every sequence's units of 2048; each of
+    # the six regions padded to 256 bytes, and nothing besides
+    for B, N, V, k in ((256, 1152, 16032, 8), (1, 5, 128256, 5), (4096, 8192, 16032, 4), (3, 0, 100, 0)):
+        slots, nc, nu = max(B * k, 1), -(-V // 8192), -(-V // 2048)
+        least = 16 * max(N, 1) + slots * (8 + nc * (48 + 8)) + B * nu * (16 + 8)
+        assert least <= ws(B, N, V, k) < least + 6 * 256
     for bad in ((0, 0, 10, 4), (4, 0, 0, 4), (4, 0, 4194305, 4), (4, 17, 10, 4), (4, 0, 10, 64)):
         assert ws(*bad) == 0, bad
 
