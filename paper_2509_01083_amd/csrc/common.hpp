@@ -122,7 +122,12 @@ inline WorkspaceLayout workspace_layout(int32_t B, int64_t N, int64_t V, int32_t
   L.chunk_arg = off;
   off += align_up(sizeof(ChunkArg) * slots * size_t(nc));
   L.stats_total = off;
-  const size_t seqs = size_t(draw_seqs_per_pass(B, V)), cells = seqs * size_t(num_units(V));
+  // bounds of a pass's sequences and units that grow with B and with V, so that a
+  // workspace sized for the largest shapes serves all smaller ones (a pass of a
+  // wider vocabulary has fewer sequences)
+  const int64_t all_units = int64_t(B) * num_units(V);
+  const size_t seqs = size_t(B < kMaxDrawSeqs ? B : kMaxDrawSeqs);
+  const size_t cells = size_t(all_units < kMaxDrawCells ? all_units : kMaxDrawCells);
   L.jobs = off;
   off += align_up(sizeof(DrawJob) * seqs);
   L.sub = off;

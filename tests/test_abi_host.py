@@ -58,6 +58,22 @@ def test_workspace_sizes(lib):
         assert ws(*bad) == 0, bad
 
 
+def test_workspace_sizes_grow_with_every_argument(lib):
+    """A workspace sized for the largest B, N, V and k_max of a program serves every
+    smaller shape, across the bounds of the draw's passes too."""
+    widths = [1, 2048, 2049, 8192, 10240, 12288, 30720, 32000, 126976, 128256, 131072, 152064, 600000, 4194304]
+    for ws in (lib.dsde_verify_workspace_bytes, lib.dsde_shard_workspace_bytes):
+        for B in (1, 64, 2080, 2115, 4096, 26215, 32768, 40000):
+            for k in (0, 1):
+                sizes = [ws(B, 0, V, k) for V in widths]
+                sizes = [x for x in sizes if x > 0]
+                assert len(sizes) >= 2 and sizes == sorted(sizes), (B, k, sizes)
+        for V in widths[:-1]:
+            sizes = [ws(B, B, V, 2) for B in (1, 64, 2080, 2115, 4096)]
+            assert 0 < sizes[0] and sizes == sorted(sizes), (V, sizes)
+        assert ws(64, 10, 32000, 4) <= ws(64, 200, 32000, 4) <= ws(64, 200, 32000, 8)
+
+
 FAKE = ctypes.c_void_p(0x1000)  # never dereferenced: validation fails first
 
 
