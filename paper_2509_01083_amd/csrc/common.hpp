@@ -90,9 +90,11 @@ inline int64_t num_chunks(int64_t V) { return (V + kChunk - 1) / kChunk; }
 
 // The draw's cells (24 bytes per unit) and jobs pass from one kernel to the
 // next through the workspace.  Their space is bounded: batches with more than
-// kMaxDrawCells units, or more than kMaxDrawSeqs sequences, run the two draw
-// kernels over several ranges of sequences one after another.
-constexpr int64_t kMaxDrawCells = 131072;
+// kMaxDrawCells units (8,322 sequences at V = 128,256), or more than kMaxDrawSeqs
+// sequences, run the two draw kernels over several ranges of sequences one after
+// another; each range costs two launches and a last round of workgroups (4,096
+// sequences in two ranges instead of one: 2 % of the step).
+constexpr int64_t kMaxDrawCells = 524288;
 constexpr int32_t kMaxDrawSeqs = 32768;
 inline int32_t draw_seqs_per_pass(int32_t B, int64_t V) {
   int64_t n = kMaxDrawCells / num_units(V);

@@ -64,7 +64,8 @@ struct StepParams {
 // ---------------------------------------------------------------------------
 
 // Workgroup (x, y) works on one sequence of the pass; y = 0 writes the outputs,
-// y = 1 .. gridDim.y - 1 take a share of the draw's units each.  All of them
+// y = 1 .. gridDim.y - 1 take a share of the draw's units each (MERGED, for many
+// sequences: y = 0 too).  All of them
 // repeat the acceptance: it takes about 3 us of latency and few instructions,
 // where handing its result to other workgroups would take a kernel boundary.
 // A row dealt to one workgroup per sequence is bound by that CU's VALU (two
@@ -73,7 +74,7 @@ struct StepParams {
 // streamed and drew in one workgroup per sequence: 21.7 -> 6.6 us for one
 // sequence (V = 128,256 bf16), 65.4 -> 14.6 us for 64 in fp32,
 // 29.8 -> 25.8 us for 256 in bf16 (18 us of bytes).
-template <int DT, int ROW, bool FUSED>
+template <int DT, int ROW, bool FUSED, bool MERGED>
 __global__ __launch_bounds__(kSeqThreads) void seq_kernel(const StepParams P, const SignalArgs S) {
   __shared__ float st_mt[DSDE_MAX_K + 1], st_md[DSDE_MAX_K + 1];
   __shared__ double st_sp[DSDE_MAX_K + 1], st_sq[DSDE_MAX_K + 1], st_a[DSDE_MAX_K + 1], st_h[DSDE_MAX_K + 1];
@@ -82,8 +83,9 @@ __global__ __launch_bounds__(kSeqThreads) void seq_kernel(const StepParams P, co
   __shared__ DrawJob s_job;
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);  // uniform: unit indices and addresses stay scalar
-  // last sequence first: its rows are what the statistics pass read last, and
-  // the last-level cache still holds some of them
+  // last sequence first: its rows are what the statistics pass read last.  Worth
+  // 0.5 % of a 256-sequence step; second reads of rows come at the speed of the
+  // first, so it is not the last-level cache serving them that gives it.
   const int32_t lb = int32_t(gridDim.x) - 1 - int32_t(blockIdx.x), b = P.first_seq + lb;
   const bool outputs = blockIdx.y == 0;
   const int32_t width = P.k_max + 1;
@@ -266,20 +268,22 @@ __global__ __launch_bounds__(kSeqThreads) void seq_kernel(const StepParams P, co
         else if (err)
           atomicOr(&P.seq_err[b], err);
       }
+      if constexpr (MERGED)
+        if (lane == 0) s_job = j;
     } else if (lane == 0) {
       s_job = j;
     }
   }
   __syncthreads();
 
-  if (!outputs) {
+  if (MERGED || !outputs) {
     // ---- this workgroup's share of the draw's units
     const DrawJob job = uniform_job(s_job);
     const UnitCells cells{P.sub + int64_t(lb) * P.nu * kSubs, P.ref + int64_t(lb) * P.nu};
-    const int32_t gw = (int32_t(blockIdx.y) - 1) * kSeqWaves + wave;
+    const int32_t gw = (int32_t(blockIdx.y) - !MERGED) * kSeqWaves + wave;
     draw_units<DT, ROW>(job, (const char *)P.target, (const char *)P.draft, P.V, P.nu, gw,
-                        (int32_t(gridDim.y) - 1) * kSeqWaves, cells);
-    return;
+                        (int32_t(gridDim.y) - !MERGED) * kSeqWaves, cells);
+    if (!outputs) return;
   }
   if (wave != kSignalWave) return;
   // ---- the KLD outputs, and in the fused step the signal update of Sec. 3.1.2
@@ -378,10 +382,21 @@ __global__ __launch_bounds__(kCapThreads) void pick_kernel(const StepParams P, c
 
 }  // namespace
 
-// Streaming workgroups per sequence: about kStreamWorkgroups in all (four of
-// these workgroups fill a CU's registers), but no wavefront without a unit.
+// Streaming workgroups per sequence.  Up to kStreamWorkgroups sequences: about
+// that many workgroups in all, but no wavefront without a unit.  Five of them fit
+// a CU by registers (aligned rows), 1,280 the chip, where the outputs workgroups
+// need places too: 1,280 and 2,048 streaming ones were slower (256 sequences at
+// V = 128,256: 127.5 and 128.9 us a step against 125.8; 512 long drafts: 490 and
+// 487 against 483; 1,024 of 2-3 drafts: 298 and 299 against 290).
+// More sequences: the outputs workgroups stream as well (MERGED), since a round of
+// workgroups that only decide, ahead of those that stream, leaves memory idle, and
+// each workgroup takes about 32 units, so that the acceptance it repeats stays small
+// and the last round of workgroups short.  V = 128,256, 1-2 drafts: 1,536
+// sequences 316 -> 302 us, 2,048 410 -> 400, 4,096 830 -> 790; V = 32,000, 1-4
+// drafts: 4,096 323 -> 314 us; 65,536 at V = 512: 1,277 -> 1,086 us.
 constexpr int32_t kStreamWorkgroups = 1024;
 static int32_t stream_parts(int32_t seqs, int32_t nu) {
+  if (seqs > kStreamWorkgroups) return nu < 48 ? 1 : (nu + 16) / 32;
   const int32_t most = (nu + kSeqWaves - 1) / kSeqWaves;
   const int32_t want = (kStreamWorkgroups + seqs - 1) / seqs;
   return want < most ? want : most;
@@ -394,11 +409,13 @@ static void launch_draw(const VerifyArgs &a, StepParams P, const SignalArgs &S) 
     const int32_t seqs = a.B - b0 < per_pass ? a.B - b0 : per_pass;
     const bool last = b0 + seqs == a.B;
     P.first_seq = b0;
-    const dim3 grid(unsigned(seqs), unsigned(1 + stream_parts(seqs, P.nu)));
+    const bool merged = seqs > kStreamWorkgroups;
+    const dim3 grid(unsigned(seqs), unsigned(stream_parts(seqs, P.nu) + !merged));
+    auto run = [&](auto kernel) { kernel<<<grid, dim3(kSeqThreads), 0, a.stream>>>(P, S); };
     if (a.signal)
-      seq_kernel<DT, ROW, true><<<grid, dim3(kSeqThreads), 0, a.stream>>>(P, S);
+      merged ? run(seq_kernel<DT, ROW, true, true>) : run(seq_kernel<DT, ROW, true, false>);
     else
-      seq_kernel<DT, ROW, false><<<grid, dim3(kSeqThreads), 0, a.stream>>>(P, S);
+      merged ? run(seq_kernel<DT, ROW, false, true>) : run(seq_kernel<DT, ROW, false, false>);
     // the SL rule needs every sequence's signal: behind the last pass
     const bool rule = a.signal && last;
     pick_kernel<DT, ROW><<<dim3(unsigned(seqs + rule)), dim3(kCapThreads), 0, a.stream>>>(P, S, rule);

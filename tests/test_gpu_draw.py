@@ -54,6 +54,22 @@ def test_draw_in_two_passes(gpu_lib):
     assert torch.equal(got["sl_next"], rule["sl_next"])
 
 
+@pytest.mark.parametrize("B", [1024, 1025])
+def test_draw_around_the_merged_workgroups(gpu_lib, B):
+    """On both sides of the number of sequences above which the workgroups that
+    write the outputs stream as well, with rows of two workgroups' units there."""
+    rng = np.random.default_rng(B)
+    V = 100008
+    sls = (rng.integers(0, 3, B) * (rng.random(B) < 0.2)).tolist()
+    # peaked rows: in flat ones (sigma 1) a token weighs about 1e-5, of which the tie
+    # band around its boundaries (1e-6 on each side) takes a fifth
+    target, draft, tokens, u_acc, u_res = random_arrays(rng, sls, V, sigma=4.0, noise=1.5)
+    temps = rng.choice([0.0, 0.7, 1.0], B).tolist()
+    step = step_from_arrays(target, draft, sls, tokens, temps, u_acc, u_res, 2)
+    _, _, rep = check_step(gpu_lib, step, f"merged workgroups B={B} V={V}")
+    assert rep["compared"] >= 0.9 * B
+
+
 @pytest.mark.parametrize("B,k_max,V", [(64, 8, 8192), (1024, 4, 9000), (1024, 5, 8192), (1025, 1, 512)])
 def test_statistics_with_and_without_the_setup_kernel(gpu_lib, B, k_max, V):
     """Batches on both sides of the rule that drops the set-up kernel (at most
