@@ -147,3 +147,46 @@ def test_shard_counts_around_the_group_sizes(gpu_lib, G):
     step = step_from_arrays(target, draft, sls, tokens, [1.0, 0.7, 0.0, 1.3, 0.0], u_acc, u_res, 40)
     bounds = [16 * g for g in range(G)] + [V]
     check_sharded(gpu_lib, step, list(zip(bounds[:-1], bounds[1:])), f"{G} slices")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("V", [5, 1001, 2048, 3000, 10248, 2048 * 70 + 8, 2048 * 70 + 3])
+def test_draw_without_residual_mass(gpu_lib, V, dtype):
+    """A rejected pair whose residual has no mass at all: the draw falls back to p of
+    the target row.  Target and draft are equal (one weight on some tokens, none on
+    the rest, so that p - q is exactly 0) but for the drafted token, of weight 0 in
+    both and e times more likely under the draft, which u = 0.9 rejects.  u' lies
+    in the middle of each token's interval."""
+    from tests.test_gpu_shard import check_sharded
+    rng = np.random.default_rng(V)
+    edges = {0, 1, 511, 512, 2047, 2048, 2049, 8191, 8192, 64 * 2048 - 1, 64 * 2048, V // 3, V - 2, V - 1}
+    x = 2 if V < 100 else 700  # the drafted token
+    hot = np.array(sorted(t for t in edges if t < V and t != x))
+    H = len(hot)
+    B = 2 * H
+    sls = [1] * H + [2] * H  # the second half accepts a draft first
+    seq = np.repeat(np.arange(B), sls)
+    N = len(seq)
+    target, draft = np.full((N + B, V), -100.0, np.float32), np.full((N, V), -100.0, np.float32)
+    target[:, hot] = 0.0
+    draft[:, hot] = 0.0
+    tokens, u_acc = np.full(N, x), np.full(N, 0.9, np.float32)
+    for b in range(H, B):
+        first = H + 2 * (b - H)
+        tokens[first], u_acc[first] = hot[b % H], 0.5
+    at = np.nonzero(tokens == x)[0]
+    draft[at, x] = -99.0
+    u_res = ((np.arange(B) % H + 0.5) / H).astype(np.float32)
+    temps = [1.0, 0.9] * H
+    step = step_from_arrays(target, draft, sls, tokens, temps, u_acc, u_res, 2, dtype)
+    want = [0] * H + [1] * H
+
+    def check(got, rep):
+        assert got["accepted"].tolist() == want and rep["compared"] == B
+        assert got["tokens"][np.arange(B), want].tolist() == hot[np.arange(B) % H].tolist()
+    got, _, rep = check_step(gpu_lib, step, f"no residual mass V={V} {dtype}")
+    check(got, rep)
+    for G in (1, 3, 70):
+        slices = gpu_lib.slice_bounds(V, G)
+        got, _, rep = check_sharded(gpu_lib, step, slices, f"no residual mass, {len(slices)} slices V={V} {dtype}")
+        check(got, rep)

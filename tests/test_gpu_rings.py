@@ -5,6 +5,8 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
+from tests.test_gpu_signal import close, compare_signal
 from tests.test_gpu_verify import random_arrays, step_from_arrays
 
 pytestmark = pytest.mark.gpu
@@ -88,3 +90,38 @@ def test_entries_past_the_short_window_leave_it_alone(gpu_lib, call):
     got, _ = run(gpu_lib, call, step, [torch.as_tensor(hist, device="cuda"), *ring[1:]], n_short=3, n_long=12)
     assert same_bits(got["var_short"], want["var_short"])
     assert np.isnan(got["var_long"]).all()
+
+
+@pytest.mark.parametrize("W_, n_short, n_long", [(64, 10, 64), (65, 10, 30), (100, 70, 90), (256, 10, 200),
+                                                 (257, 64, 65), (300, 10, 300)])
+def test_rings_above_a_wavefronts_registers(gpu_lib, W_, n_short, n_long):
+    """Rings of more than 64 entries (the fused step keeps 64 in registers, the other
+    calls 256) and windows of more than 64: the oracle's signal, and the same bits
+    from every call."""
+    step = make_step()
+    counts = [0, 1, 5, 63, 64, 65 % (W_ + 1), W_ - 1, W_]
+    ring = make_ring(W_, counts, 0.0)
+    want, ring_want = run(gpu_lib, "kld_signal", step, ring, n_short, n_long)
+    v = gpu_lib.verify(step.target, step.draft, step.sl, step.cu_sl, step.draft_tokens, step.temperature, step.u_acc,
+                       step.u_res, step.k_max)
+    ref = oracle.kld_signal(step.sl.cpu().numpy(), step.cu_sl.cpu().numpy(), v["kld"].cpu().numpy().astype(np.float64),
+                            *[t.cpu().numpy() for t in ring], n_short, n_long)
+    compare_signal(want, ref, f"ring {W_}")
+    close(ring_want[0], ref["hist"], rel=1e-7, label="ring")  # one rounding to fp32
+    assert np.array_equal(ring_want[1], ref["head"]) and np.array_equal(ring_want[2], ref["count"])
+    for call in CALLS[1:3]:
+        got, ring_got = run(gpu_lib, call, step, ring, n_short, n_long)
+        for k in SIGNAL:
+            assert same_bits(got[k], want[k]), (call, k)
+        for a, b in zip(ring_got, ring_want):
+            assert same_bits(a, b), call
+    # the sharded KLD is summed slice by slice: its own signal, from the separate calls on it
+    base = gpu_lib.verify_sharded(step.target, step.draft, step.sl, step.cu_sl, step.draft_tokens, step.temperature,
+                                  step.u_acc, step.u_res, step.k_max, gpu_lib.slice_bounds(step.V, 2))
+    ring_a = [t.clone() for t in ring]
+    sig = gpu_lib.kld_signal(step.sl, step.cu_sl, base["kld"], *ring_a, n_short, n_long)
+    got, ring_got = run(gpu_lib, "shard_accept_step", step, ring, n_short, n_long)
+    for k in ("mu_last", "var_short", "var_long", "wvir", "sf"):
+        assert same_bits(got[k], sig[k].cpu().numpy()), k
+    for a, b in zip(ring_got, ring_a):
+        assert same_bits(a, b.cpu().numpy())
