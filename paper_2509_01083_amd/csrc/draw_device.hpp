@@ -80,7 +80,7 @@ __device__ __forceinline__ double rcp_newton(double s) {
   return r;
 }
 
-// reductions inside aligned groups of G lanes (G = 16, 32 or 64)
+// reductions inside aligned groups of G lanes (G = 8, 16, 32 or 64)
 template <int G>
 __device__ __forceinline__ float group_max(float v) {
   return lanes::group_reduce<G>(v, lanes::Max{});

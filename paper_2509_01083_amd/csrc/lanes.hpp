@@ -6,8 +6,9 @@
 // The bandwidth-bound row passes keep their ds_bpermute butterflies: there the
 // LDS unit runs them beside the VALU work, and the DPP forms measured slower.
 //
-// Every reduction leaves the same bits in every lane (of the group), and each
-// one evaluates in a fixed order, so results are reproducible run to run.
+// Every reduction but wave_sum4 leaves the same bits in every lane (of the
+// group), and each one evaluates in a fixed order, so results are reproducible
+// run to run.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -111,7 +112,8 @@ __device__ __forceinline__ T wave_sum(T v) { return group_reduce<64>(v, Add{}); 
 // sum over the 64 lanes of a[i % 4].  Two exchanges inside each quad leave one
 // entry per lane, two row rotations add the quads of a row of 16, and two
 // shuffles (through the LDS unit) add the four rows: 7 additions for the work
-// of four 64-lane sums.
+// of four 64-lane sums.  Lanes that hold the same entry may differ in its last bits
+// (the rotations start from different quads): take it from lanes 0 to 3.
 __device__ __forceinline__ float wave_sum4(const float (&a)[4]) {
   const int l = threadIdx.x;
   const bool b0 = l & 1, b1 = l & 2;

@@ -62,8 +62,9 @@ def test_workload_parity_sharded(gpu_lib, name, G):
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 def test_ragged_and_unaligned_slices(gpu_lib, dtype):
-    """Slices of widths that are not multiples of the vector width (the scalar
-    row path), a slice narrower than one sub-block, and one wider than a chunk."""
+    """Slices of widths that are not a whole number of 16-byte loads, one narrower
+    than a load (rows read one logit at a time), one narrower than a sub-block, and
+    one wider than a chunk."""
     import paper_2509_01083_amd as dsde
     rng = np.random.default_rng(21)
     V = 20011

@@ -84,10 +84,10 @@ def test_large_vocab(gpu_lib, V, dtype):
 
 @pytest.mark.parametrize("V,dtype", [(300, "bf16"), (512, "bf16"), (512, "fp32"), (301, "fp32")])
 def test_large_batch(gpu_lib, V, dtype):
-    """More sequences than CUs and than the set-up kernel has threads (the
-    256-thread per-sequence kernel and the set-up's looping path), ragged SL
-    including 0, mixed temperatures and greedy sequences; vectorised (V a
-    multiple of the vector width) and scalar row paths."""
+    """More sequences than the set-up kernel has threads (its looping path, and
+    the workgroups that write the outputs and stream the draw), ragged SL
+    including 0, mixed temperatures and greedy sequences; rows of a whole number
+    of 16-byte loads and others."""
     rng = np.random.default_rng(1500 + V)
     B = 1500
     sls = rng.integers(0, 4, B).tolist()
@@ -170,7 +170,7 @@ def test_bad_layout(gpu_lib):
     assert (got["seq_err"] == 1).all() and (got["accepted"] == 0).all() and (got["tokens"] == -1).all()
 
 
-def test_unaligned_rows_take_the_scalar_path(gpu_lib):
+def test_rows_off_the_16_byte_alignment(gpu_lib):
     rng = np.random.default_rng(8)
     sls = [3, 1, 4]
     V = 4096
@@ -312,8 +312,8 @@ def test_draw_at_sub_block_and_chunk_boundaries(gpu_lib, V, dtype):
     token's CDF interval.  Every sequence rejects its one draft (q is one-hot on
     a token p does not hold) or accepts it and draws from the bonus row, so the
     residual and the bonus draws are both checked, against the oracle and
-    against the token the construction fixes.  V = 8k + 704 takes the
-    vectorised paths, V = 8k + 705 the scalar ones."""
+    against the token the construction fixes.  V = 8k + 704 is a
+    whole number of 16-byte loads, V = 8k + 705 is not."""
     hot = np.array([0, 511, 512, 1023, 4095, 8191, 8192, 8703, 16383, 16384, 24575, 24576, V - 1])
     H = len(hot)
     B = 2 * H
