@@ -210,7 +210,7 @@ def verify(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_
     seq_err (and draft_entropy when asked for); pass ``out`` (a dict with those
     keys) to reuse output buffers."""
     native = _native or _bind()
-    if out is None or workspace is None or draft_entropy:
+    if out is None or workspace is None or (draft_entropy and "draft_entropy" not in out):
         with _on(stream):
             out, workspace = _buffers(target, draft, sl, k_max, out, workspace, draft_entropy, False)
     native.verify(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, int(pad_id), out, row_lse,
@@ -222,7 +222,7 @@ def _step(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_m
           n_short, n_long, delta, eps, sl_min, sl_hi, pad_id, out, workspace, row_lse, draft_entropy, budget, stream):
     """dsde_step, or with ``workspace`` False dsde_step_static."""
     native = _native or _bind()
-    if out is None or workspace is None or draft_entropy:
+    if out is None or workspace is None or (draft_entropy and "draft_entropy" not in out):
         with _on(stream):
             out, workspace = _buffers(target, draft, sl, k_max, out, workspace, draft_entropy, True)
     native.step(target, draft, sl, cu_sl, draft_tokens, temperature, u_acc, u_res, k_max, int(pad_id), out, row_lse,
